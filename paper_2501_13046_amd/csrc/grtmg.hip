@@ -21,6 +21,7 @@
 #include "grtmg.h"
 #include "mg_kernels.hpp"
 #include "mg_tiled.hpp"
+#include "mg_brick.hpp"
 #include "mg_cttk.hpp"
 #include "mg_refine.hpp"
 #include "mg_fourier.hpp"
@@ -88,6 +89,10 @@ constexpr int kBrickPsi = 4;
 constexpr int kBrickW = 2;
 // marched columns of 64-cell rows (levels whose side is a multiple of 64 but
 // not of 128): x planes per column of the W pass and of the W defect restriction
+// planes of a psi brick of the defect restriction
+constexpr int kBrickDefect = 4;
+// and of the residual without W (FP64 staging)
+constexpr int kBrickResidual = 2;
 constexpr int kMarch64Pass = 1;
 constexpr int kMarch64Defect = 2;
 constexpr int kBrickR = 2;
@@ -129,6 +134,7 @@ struct mg_ctx {
     float2 *specZ;               // complex buffer of that solve on 32^3 and 64^3 levels (3 n^3)
     void *pd0[kMaxLevels], *pd1[kMaxLevels], *pr[kMaxLevels], *pc[kMaxLevels];
     void *wd0[kMaxLevels], *wd1[kMaxLevels], *wr[kMaxLevels];
+    double *gw[kMaxLevels];    // ghost weights per level (Robin contexts; see mg_brick.hpp)
     double *part;
     double *part_w; // the W step's partial sums while it runs beside the psi step
     double *scal;
@@ -255,6 +261,7 @@ void carve(mg_ctx *c, Carver &cv)
         } else {
             c->wd0[l] = c->wd1[l] = c->wr[l] = nullptr;
         }
+        c->gw[l] = p.bc == MG_BC_ROBIN ? (double *)cv.take(12 * (size_t)n * n * sizeof(double)) : nullptr;
         n /= 2;
     }
     const int ls = spectral_level(c);
@@ -338,6 +345,7 @@ void init_geo(mg_ctx *c)
 {
     for (int l = 0; l < c->L; l++) {
         c->geo[l] = make_geo(c->n[l], c->p.bc, c->p.length, c->p.origin, c->p.puncture_pos);
+        c->geo[l].gw = c->gw[l];
         c->tile[l] = make_tilemap<kBrickPsi>(c->n[l]);
         c->tileW[l] = w_tileable(c->n[l]) ? make_tilemap<kBrickW>(c->n[l]) : TileMap{0, 0, 0, 0};
     }
@@ -510,16 +518,53 @@ void coarse_W(mg_ctx *c, const T *r, T *x)
 
 // ---- psi V-cycle ----------------------------------------------------------------------
 
-template <int BC, typename T>
+// psi kernels on bricks (mg_brick.hpp) from this side on (the wrapped overhang of a brick stays
+// inside grids of at least 18 cells per axis); rows of 64 cells where they divide the side,
+// else of 32.  Below, one thread per z pair: its single round of loads takes 3.0-4.7 us up to
+// 64^3 (FP32) where a brick's two rounds took 5.4-8.5; at 80^3 the brick is level with it (6.7
+// against 6.2 us) and at 160^3 ahead (18.0 against 28.3).
+constexpr int kBrickMin = 72;
+bool psi_bricks(int n) { return n % 2 == 0 && n >= kBrickMin; }
+bool brick_rows_64(int n) { return n % 64 == 0; }
+
+// f(std::integral_constant<int, BZ>{}) with the row length of a level of n cells per axis.
+template <typename F>
+void with_rows(int n, F &&f)
+{
+    if (brick_rows_64(n))
+        f(std::integral_constant<int, 64>{});
+    else
+        f(std::integral_constant<int, 32>{});
+}
+
+// f(std::integral_constant<int, kBc...>{}) with the context's boundary rule.
+template <typename F>
+void with_rule(int bc, F &&f)
+{
+    if (bc == MG_BC_PERIODIC)
+        f(std::integral_constant<int, kBcPeriodic>{});
+    else
+        with_bc(bc, f);
+}
+
+template <typename T>
 void launch_psi_tiled(hipStream_t s, const Geo &g, const TileMap &tm, const T *in, T *out, const T *r, const T *cf,
                       int colour)
 {
     const dim3 blk(kLanes, kTY), grid(ntiles(tm), 1, g.gz);
     switch (tm.tx) {
-    case 2: hipLaunchKernelGGL((k_pass_psi_tiled<BC, T, 2>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
-    case 8: hipLaunchKernelGGL((k_pass_psi_tiled<BC, T, 8>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
-    default: hipLaunchKernelGGL((k_pass_psi_tiled<BC, T, 4>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
+    case 2: hipLaunchKernelGGL((k_pass_psi_tiled<kBcPeriodic, T, 2>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
+    case 8: hipLaunchKernelGGL((k_pass_psi_tiled<kBcPeriodic, T, 8>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
+    default: hipLaunchKernelGGL((k_pass_psi_tiled<kBcPeriodic, T, 4>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
     }
+}
+
+template <int BC, typename T, int TX, int BZ>
+void launch_psi_brick(hipStream_t s, const Geo &g, const T *in, T *out, const T *r, const T *cf, int colour)
+{
+    const TileMap tm = make_brickmap<TX, BZ>(g.n);
+    hipLaunchKernelGGL((k_pass_psi_brick<BC, T, TX, BZ>), dim3(ntiles(tm), 1, g.gz), dim3(kLanes, kTY), 0, s, g, tm,
+                       in, out, r, cf, colour);
 }
 
 template <typename T>
@@ -527,31 +572,30 @@ void pass_psi(mg_ctx *c, int l, const T *in, T *out, int colour)
 {
     Probe pr(c, MG_PROBE_PASS_PSI, l);
     const Geo &g = c->geo[l];
-    const unsigned nb = nblk(c->cells[l]);
-    const TileMap &tm = c->tile[l];
-    if (tm.tx > 0) {
-        const T *r = (const T *)c->pr[l], *cf = (const T *)c->pc[l];
-        if (c->p.bc == MG_BC_PERIODIC)
-            launch_psi_tiled<kBcPeriodic, T>(c->s, g, tm, in, out, r, cf, colour);
-        else
-            with_bc(c->p.bc, [&](auto bcx) {
-                constexpr int BCX = decltype(bcx)::value;
-                launch_psi_tiled<BCX, T>(c->s, g, tm, in, out, r, cf, colour);
-            });
-        return;
-    }
-    if (c->p.bc == MG_BC_PERIODIC && c->n[l] % 2 == 0)
-        hipLaunchKernelGGL(k_pass_psi_pairs<T>, dim3(nblk(c->cells[l] / 2), 1, c->gz), dim3(kBlock), 0, c->s, g, in, out,
-                           (const T *)c->pr[l], (const T *)c->pc[l], colour);
-    else if (c->p.bc == MG_BC_PERIODIC)
-        hipLaunchKernelGGL((k_pass_psi<kBcPeriodic, T>), dim3(nb, 1, c->gz), dim3(kBlock), 0, c->s, g, in, out,
-                           (const T *)c->pr[l], (const T *)c->pc[l], colour);
-    else
-        with_bc(c->p.bc, [&](auto bcx) {
+    const int tx = c->tile[l].tx; // 0: no choice of depth on this level
+    const T *r = (const T *)c->pr[l], *cf = (const T *)c->pc[l];
+    const bool periodic = c->p.bc == MG_BC_PERIODIC;
+    if (periodic && tx > 0) {
+        launch_psi_tiled<T>(c->s, g, c->tile[l], in, out, r, cf, colour);
+    } else if (psi_bricks(c->n[l])) {
+        with_rule(c->p.bc, [&](auto bcx) {
             constexpr int BCX = decltype(bcx)::value;
-            hipLaunchKernelGGL((k_pass_psi<BCX, T>), dim3(nb, 1, c->gz), dim3(kBlock), 0, c->s, g, in, out,
-                               (const T *)c->pr[l], (const T *)c->pc[l], colour);
+            if (tx == 2)
+                launch_psi_brick<BCX, T, 2, 64>(c->s, g, in, out, r, cf, colour);
+            else if (tx == 8)
+                launch_psi_brick<BCX, T, 8, 64>(c->s, g, in, out, r, cf, colour);
+            else
+                with_rows(c->n[l], [&](auto bz) {
+                    launch_psi_brick<BCX, T, 4, decltype(bz)::value>(c->s, g, in, out, r, cf, colour);
+                });
         });
+    } else { // smoothed levels are even
+        with_rule(c->p.bc, [&](auto bcx) {
+            constexpr int BCX = decltype(bcx)::value;
+            hipLaunchKernelGGL((k_pass_psi_pairs<BCX, T>), dim3(nblk(c->cells[l] / 2), 1, c->gz), dim3(kBlock), 0, c->s,
+                               g, in, out, r, cf, colour);
+        });
+    }
 }
 
 template <typename T>
@@ -572,28 +616,21 @@ void defect_restrict_psi(mg_ctx *c, int l, const T *d, const T *r, const T *cf, 
     Probe pr(c, MG_PROBE_DEFECT_RESTRICT_PSI, l);
     const Geo &g = c->geo[l], &gc = c->geo[l + 1];
     if (!cc) d1 = nullptr;
-    if (fine_threads(c->n[l])) {
-        const unsigned nb = nblk(8 * c->cells[l + 1]);
-        if (c->p.bc == MG_BC_PERIODIC)
-            hipLaunchKernelGGL((k_defect_restrict_psi_fine<kBcPeriodic, T>), dim3(nb, 1, c->gz), dim3(kBlock), 0, c->s, g, d, r,
-                               cf, rc, cc, d1, gc);
-        else
-            with_bc(c->p.bc, [&](auto bcx) {
-                constexpr int BCX = decltype(bcx)::value;
-                hipLaunchKernelGGL((k_defect_restrict_psi_fine<BCX, T>), dim3(nb, 1, c->gz), dim3(kBlock), 0, c->s, g, d, r,
-                                   cf, rc, cc, d1, gc);
+    if (psi_bricks(c->n[l])) {
+        with_rule(c->p.bc, [&](auto bcx) {
+            with_rows(c->n[l], [&](auto bz) {
+                constexpr int BCX = decltype(bcx)::value, BZ = decltype(bz)::value;
+                const TileMap tm = make_brickmap<kBrickDefect, BZ>(c->n[l]);
+                hipLaunchKernelGGL((k_defect_restrict_psi_brick<BCX, T, kBrickDefect, BZ>), dim3(ntiles(tm), 1, c->gz),
+                                   dim3(kLanes, kTY), 0, c->s, g, tm, d, r, cf, rc, cc, d1, gc);
             });
+        });
     } else {
-        const unsigned nb = nblk(c->cells[l + 1]);
-        if (c->p.bc == MG_BC_PERIODIC)
-            hipLaunchKernelGGL((k_defect_restrict_psi<kBcPeriodic, T>), dim3(nb, 1, c->gz), dim3(kBlock), 0, c->s, g, d, r, cf,
-                               rc, cc, d1, gc);
-        else
-            with_bc(c->p.bc, [&](auto bcx) {
-                constexpr int BCX = decltype(bcx)::value;
-                hipLaunchKernelGGL((k_defect_restrict_psi<BCX, T>), dim3(nb, 1, c->gz), dim3(kBlock), 0, c->s, g, d, r, cf,
-                                   rc, cc, d1, gc);
-            });
+        with_rule(c->p.bc, [&](auto bcx) {
+            constexpr int BCX = decltype(bcx)::value;
+            hipLaunchKernelGGL((k_defect_restrict_psi_fine<BCX, T>), dim3(nblk(8 * c->cells[l + 1]), 1, c->gz),
+                               dim3(kBlock), 0, c->s, g, d, r, cf, rc, cc, d1, gc);
+        });
     }
 }
 
@@ -626,22 +663,18 @@ void prolong_add(mg_ctx *c, int lc, const T *coarse, T *fine, int ncomp)
     Probe pr(c, MG_PROBE_PROLONG, lc - 1);
     const Geo &gc = c->geo[lc];
     if (c->p.flags & MG_FLAG_CUBIC_PROLONG) {
-        const int nc = c->n[lc];
-        const bool staged = nc % kCubZ == 0 && nc % kCubY == 0 && nc % kCubX == 0;
-        const unsigned nbk = staged ? (unsigned)((nc / kCubX) * (nc / kCubY) * (nc / kCubZ)) : nblk(c->cells[lc]);
-        auto launch = [&](auto bcx) {
+        with_rule(c->p.bc, [&](auto bcx) {
             constexpr int BCX = decltype(bcx)::value;
-            if (staged)
-                hipLaunchKernelGGL((k_prolong_cubic_add_staged<BCX, T>), dim3(nbk, 1, c->gz), dim3(kBlock), 0, c->s, gc,
-                                   coarse, fine, ncomp);
+            auto launch = [&](auto cz) {
+                constexpr int CZ = decltype(cz)::value;
+                hipLaunchKernelGGL((k_prolong_cubic_add_staged<BCX, T, CZ>), dim3(CubicTile<CZ>::blocks(c->n[lc]), ncomp, c->gz),
+                                   dim3(kBlock), 0, c->s, gc, coarse, fine);
+            };
+            if (c->n[lc] > kCubicRow8Max)
+                launch(std::integral_constant<int, 16>{});
             else
-                hipLaunchKernelGGL((k_prolong_cubic_add<BCX, T>), dim3(nbk, 1, c->gz), dim3(kBlock), 0, c->s, gc,
-                                   coarse, fine, ncomp);
-        };
-        if (c->p.bc == MG_BC_PERIODIC)
-            launch(std::integral_constant<int, kBcPeriodic>{});
-        else
-            with_bc(c->p.bc, launch);
+                launch(std::integral_constant<int, 8>{});
+        });
         return;
     }
     const unsigned nb = nblk(c->cells[lc - 1]);
@@ -971,9 +1004,20 @@ void residual(mg_ctx *c, const double *u, const double *W, bool want_M, double *
     {
         Probe pr(c, MG_PROBE_RESIDUAL, 0);
         TileMap tm = c->tileR;
+        const int n = c->n[0];
         // marched columns carry no background fields: bricks of depth 2 instead
         if (tm.tx >= 8 && (c->bg_psi0 || c->bg_A2)) tm = rtilemap_rt(c->n[0], 2);
-        if (tm.tx > 0) {
+        if (!W && !want_M && psi_bricks(n) && (double)n * n * n * sizeof(double) < 4294967296.0) {
+            with_rule(c->p.bc, [&](auto bcx) {
+                with_rows(n, [&](auto bz) {
+                    constexpr int BCX = decltype(bcx)::value, BZ = decltype(bz)::value;
+                    const TileMap bm = make_brickmap<kBrickResidual, BZ>(n);
+                    nb = ntiles(bm);
+                    hipLaunchKernelGGL((k_residual_psi_brick<BCX, T, kBrickResidual, BZ>), dim3(nb, 1, c->gz),
+                                       dim3(kLanes, kTY), 0, c->s, c->geo[0], bm, a);
+                });
+            });
+        } else if (tm.tx > 0) {
             nb = ntiles(tm);
             if (c->p.bc == MG_BC_PERIODIC)
                 launch_residual_tiled<kBcPeriodic, T>(c->s, c->geo[0], tm, a, W != nullptr);
@@ -1794,6 +1838,9 @@ mg_status ctx_create(const mg_params *p, void *d_workspace, size_t bytes, hipStr
     }
     enter(c);
     fill<double>(c->s, c->scal, S_COUNT, 0.0);
+    for (int l = 0; l < c->L && c->p.bc == MG_BC_ROBIN; l++)
+        hipLaunchKernelGGL(k_ghost_weights, dim3(nblk((int64_t)c->n[l] * c->n[l]), 12), dim3(kBlock), 0, c->s,
+                           c->geo[l], c->gw[l]);
     if (c->momentum) {
         const int m = c->m_W;
         fill<double>(c->s, c->A_W, (int64_t)m * m, 0.0);

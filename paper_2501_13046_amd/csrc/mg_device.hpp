@@ -39,6 +39,9 @@ struct Geo {
     // for a single instance.
     int gz;
     long long zs;
+    // Robin weights of the level's ghosts across each face (k_ghost_weights; null elsewhere):
+    // layer l (0: next to the face) of face f (x-, x+, y-, y+, z-, z+) at (2 f + l) n^2
+    const double *gw;
 };
 
 __host__ __device__ inline Geo make_geo(int n, int bc, double length, const double org[3],
@@ -57,6 +60,7 @@ __host__ __device__ inline Geo make_geo(int n, int bc, double length, const doub
     }
     g.gz = 1;
     g.zs = 0;
+    g.gw = nullptr;
     return g;
 }
 
@@ -159,17 +163,6 @@ struct Acc {
     }
 };
 
-// Weight with which the boundary-ruled value at (i,j,k)+offset depends on the
-// stored value at (i,j,k) itself (1 for the centre tap).
-template <int BC>
-__device__ __forceinline__ double self_weight(const Geo &g, int i, int j, int k, int di, int dj,
-                                              int dk)
-{
-    int bi, bj, bk;
-    const double w = ghost_source<BC>(g, i + di, j + dj, k + dk, bi, bj, bk);
-    return (bi == i && bj == j && bk == k) ? w : 0.0;
-}
-
 // ---- stencils (unscaled sums; the caller multiplies by 1/(12h) or 1/(12h^2)) ----
 
 template <int AX>
@@ -241,15 +234,22 @@ __device__ __forceinline__ double lap_diag_sum(const Geo &g, int i, int j, int k
     } else {
         const int n = g.n;
         double s = -90.0;
-        // only cells on the boundary see their own value through a ghost
-        if (i == 0 || i == n - 1 || j == 0 || j == n - 1 || k == 0 || k == n - 1) {
-            const double w[5] = {-1.0, 16.0, 0.0, 16.0, -1.0};
+        // only cells on the boundary see their own value through a ghost: both layers of a
+        // face under the Robin and extrapolating rules, the first one under the mirror rule
+        if constexpr (BC != kBcZero) {
+            const int p[3] = {i, j, k}, a[3] = {j, i, i}, b[3] = {k, k, j};
 #pragma unroll
-            for (int d = -2; d <= 2; d++) {
-                if (d == 0) continue;
-                s += w[d + 2] * self_weight<BC>(g, i, j, k, d, 0, 0);
-                s += w[d + 2] * self_weight<BC>(g, i, j, k, 0, d, 0);
-                s += w[d + 2] * self_weight<BC>(g, i, j, k, 0, 0, d);
+            for (int ax = 0; ax < 3; ax++) {
+                if (p[ax] != 0 && p[ax] != n - 1) continue;
+                if constexpr (BC == kBcReflect) {
+                    s += 16.0;
+                } else if constexpr (BC == kBcExtrap) {
+                    s += 15.0;
+                } else {
+                    const size_t nn = (size_t)n * n;
+                    const double *w = g.gw + (2 * ax + (p[ax] ? 1 : 0)) * 2 * nn + (unsigned)(a[ax] * n + b[ax]);
+                    s += 16.0 * w[0] - w[nn];
+                }
             }
         }
         return s;

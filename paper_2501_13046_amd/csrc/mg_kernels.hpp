@@ -302,46 +302,72 @@ __global__ void __launch_bounds__(kBlock) k_reduce_final(const double *partials,
             out[q] = ((max_mask >> q) & 1u) || scale == 0.0 ? res[q] : res[q] * scale;
 }
 
+// The taps of the axis operator at cell (i, j, k) under a non-periodic rule: per axis the values at
+// -2, -1, +1, +2 (t[axis][0..3]), all loads independent of each other, and the diagonal of the
+// unscaled Laplacian sum there (-90 plus what the cell sees of itself through its ghosts).
+// Robin weights come from the level's table.  Grids of at least 4 cells per axis: no cell is
+// within two cells of both faces.
+template <int BC, typename T>
+__device__ __forceinline__ T axis_taps(const Geo &g, const T *a, int i, int j, int k, T (&t)[3][4], double &diag)
+{
+    const int n = g.n;
+    const int pos[3] = {i, j, k}, A[3] = {j, i, i}, B[3] = {k, k, j};
+    const unsigned stride[3] = {(unsigned)(n * n), (unsigned)n, 1u};
+    const unsigned q = ((unsigned)i * (unsigned)n + (unsigned)j) * (unsigned)n + (unsigned)k;
+    const T v = elt(a, q);
+    constexpr int dof[4] = {-2, -1, 1, 2};
+#pragma unroll
+    for (int ax = 0; ax < 3; ax++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const int p = pos[ax] + dof[e];
+            const int src = BC == kBcReflect ? mirror(p, n) : clampc(p, n);
+            t[ax][e] = elt(a, q + (unsigned)(src - pos[ax]) * stride[ax]);
+        }
+    diag = -90.0;
+#pragma unroll
+    for (int ax = 0; ax < 3; ax++) {
+        const int p = pos[ax];
+        const bool hi = p >= n - 2, edge = p == 0 || p == n - 1;
+        if constexpr (BC == kBcReflect) {
+            diag += edge ? 16.0 : 0.0;
+        } else if constexpr (BC == kBcExtrap) {
+            diag += edge ? 15.0 : 0.0;
+        } else if (p < 2 || hi) {
+            T &t1 = hi ? t[ax][2] : t[ax][1], &t2 = hi ? t[ax][3] : t[ax][0];
+            if constexpr (BC == kBcZero) {
+                t2 = T(0);
+                if (edge) t1 = T(0);
+            } else {
+                const size_t nn = (size_t)n * n;
+                const double *w = g.gw + (2 * ax + (hi ? 1 : 0)) * 2 * nn + (unsigned)(A[ax] * n + B[ax]);
+                const double w1 = w[0], w2 = w[nn];
+                t2 = (T)((double)t2 * (edge ? w2 : w1));
+                if (edge) {
+                    t1 = (T)((double)t1 * w1);
+                    diag += 16.0 * w1 - w2;
+                }
+            }
+        }
+    }
+    return v;
+}
+
+// Unscaled Laplacian sum from axis_taps.
+template <typename T>
+__device__ __forceinline__ T lap_of_taps(const T (&t)[3][4], T v)
+{
+    T s[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ax++) s[ax] = T(16) * (t[ax][1] + t[ax][2]) - (t[ax][0] + t[ax][3]) - T(30) * v;
+    return s[0] + s[1] + s[2];
+}
+
 // ---------------------------------------------------------------------------------------
 // Smoothers: one colour pass of double-buffered red-black Gauss-Seidel.  Cells
 // of the active colour ((i+j+k) mod 2) get d + (r - A d)/diag(A); the others
 // are copied.  Every read is from `in` (the state before the pass).
 // ---------------------------------------------------------------------------------------
-// One colour pass of the psi smoother at cell q = (i, j, k) (double-buffered:
-// reads in, writes out; the other colour is copied).
-template <int BC, typename T>
-__device__ __forceinline__ void psi_pass_cell(const Geo &g, const T *__restrict__ in, T *__restrict__ out,
-                                              const T *__restrict__ r, const T *__restrict__ c, int colour,
-                                              int64_t q, int i, int j, int k)
-{
-    const T x = in[q];
-    if (((i + j + k) & 1) != colour) {
-        out[q] = x;
-        return;
-    }
-    Acc<BC, T> D{in, g};
-    const T cv = c[q];
-    const T h2 = (T)g.inv12h2;
-    const T Ad = lap_sum<T>(D, i, j, k, x) * h2 + cv * x;
-    const T diag = pinned((T)(lap_diag_sum<BC>(g, i, j, k) * g.inv12h2)) + cv;
-    out[q] = x + (r[q] - Ad) / diag;
-}
-
-template <int BC, typename T>
-__global__ void __launch_bounds__(kBlock) k_pass_psi(Geo g, const T *__restrict__ in,
-                                                     T *__restrict__ out, const T *__restrict__ r,
-                                                     const T *__restrict__ c, int colour)
-{
-    in = zsh(in, g.zs);
-    out = zsh(out, g.zs);
-    r = zsh(r, g.zs);
-    c = zsh(c, g.zs);
-    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int i, j, k;
-    if (!cell_of(tid, g.n, i, j, k)) return;
-    psi_pass_cell<BC, T>(g, in, out, r, c, colour, tid, i, j, k);
-}
-
 // (Delta_L d)_a at a cell for the three components (periodic), from taps at
 // wrapped offsets computed once per cell.
 template <typename T>
@@ -537,7 +563,9 @@ __global__ void __launch_bounds__(kBlock) k_defect_restrict_W_quad(Geo g, const 
     }
 }
 
-template <typename T>
+// psi colour pass, one thread per z pair: a single round of independent loads, which is what
+// small levels are bound by.
+template <int BC, typename T>
 __global__ void __launch_bounds__(kBlock) k_pass_psi_pairs(Geo g, const T *__restrict__ in, T *__restrict__ out,
                                                            const T *__restrict__ r, const T *__restrict__ c,
                                                            int colour)
@@ -551,14 +579,25 @@ __global__ void __launch_bounds__(kBlock) k_pass_psi_pairs(Geo g, const T *__res
     if (!pair_of(blockIdx.x * kBlock + threadIdx.x, n, colour, i, j, ka, kb)) return;
     const unsigned row = ((unsigned)i * n + (unsigned)j) * (unsigned)n;
     const unsigned qa = row + (unsigned)ka, qb = row + (unsigned)kb;
-    const WrapOff o(n, i, j, ka);
-    RegTaps<T, false> D;
-    D.get_lap(WrapTaps<T>{in, o});
-    const T v = D.c(), cv = elt(c, qa);
-    const T Ad = (D.dxx(v) + D.dyy(v) + D.dzz(v)) * (T)g.inv12h2 + cv * v;
-    const T diag = pinned((T)(-90.0 * g.inv12h2)) + cv;
-    elt(out, qb) = elt(in, qb);
-    elt(out, qa) = v + (elt(r, qa) - Ad) / diag;
+    if constexpr (BC == kBcPeriodic) {
+        const WrapOff o(n, i, j, ka);
+        RegTaps<T, false> D;
+        D.get_lap(WrapTaps<T>{in, o});
+        const T v = D.c(), cv = elt(c, qa);
+        const T Ad = (D.dxx(v) + D.dyy(v) + D.dzz(v)) * (T)g.inv12h2 + cv * v;
+        const T diag = pinned((T)(-90.0 * g.inv12h2)) + cv;
+        elt(out, qb) = elt(in, qb);
+        elt(out, qa) = v + (elt(r, qa) - Ad) / diag;
+    } else {
+        const T cv = elt(c, qa), rv = elt(r, qa), other = elt(in, qb);
+        T t[3][4];
+        double ds;
+        const T v = axis_taps<BC, T>(g, in, i, j, ka, t, ds);
+        const T Ad = lap_of_taps(t, v) * (T)g.inv12h2 + cv * v;
+        const T diag = pinned((T)(ds * g.inv12h2)) + cv;
+        elt(out, qb) = other;
+        elt(out, qa) = v + (rv - Ad) / diag;
+    }
 }
 
 template <typename T>
@@ -604,11 +643,6 @@ __device__ __forceinline__ bool child_of(int64_t tid, int nc, int64_t &qc, int &
     return true;
 }
 
-// Defect r - A d restricted to the coarse grid (8-child average), and the
-// coefficient c restricted the same way (cc_out may be null).  Two forms:
-// one thread per coarse cell (the 8 children's overlapping stencils share
-// loads in registers: large grids), or one thread per fine cell with a lane
-// group per coarse cell (8x the parallelism: small, latency-bound grids).
 // First colour pass of the coarse level from a zero correction at coarse cell
 // (I, J, K): r / diag on colour 0 and 0 on colour 1, with the diagonal as the
 // pass kernels form it.
@@ -624,57 +658,11 @@ __device__ __forceinline__ T first_pass_psi(const Geo &gc, int I, int J, int K, 
     return T(0) + (rcv - T(0)) / diag;
 }
 
-template <int BC, typename T>
-__device__ __forceinline__ void defect_restrict_psi_coarse(const Geo &g, const T *__restrict__ d, const T *__restrict__ r,
-                                                           const T *__restrict__ c, T *__restrict__ rc_out,
-                                                           T *__restrict__ cc_out, int64_t qc, int I, int J, int K,
-                                                           T *__restrict__ d1_out = nullptr, const Geo *gc = nullptr)
-{
-    Acc<BC, T> D{d, g};
-    const T h2 = (T)g.inv12h2;
-    T sd = T(0), sc = T(0);
-#pragma unroll
-    for (int di = 0; di < 2; di++)
-#pragma unroll
-        for (int dj = 0; dj < 2; dj++)
-#pragma unroll
-            for (int dk = 0; dk < 2; dk++) {
-                const int i = 2 * I + di, j = 2 * J + dj, k = 2 * K + dk;
-                const int64_t q = lidx(g.n, i, j, k);
-                const T x = d[q], cv = c[q];
-                sd += r[q] - (lap_sum<T>(D, i, j, k, x) * h2 + cv * x);
-                sc += cv;
-            }
-    const T rcv = sd * T(0.125), ccv = sc * T(0.125);
-    rc_out[qc] = rcv;
-    if (cc_out) cc_out[qc] = ccv;
-    if (d1_out) d1_out[qc] = first_pass_psi<BC, T>(*gc, I, J, K, rcv, ccv);
-}
-
-// d1_out (may be null; needs cc_out): the coarse level's first colour pass
-// from zero, so that its smoothing starts with the second pass.
-template <int BC, typename T>
-__global__ void __launch_bounds__(kBlock) k_defect_restrict_psi(Geo g, const T *__restrict__ d,
-                                                                const T *__restrict__ r,
-                                                                const T *__restrict__ c,
-                                                                T *__restrict__ rc_out,
-                                                                T *__restrict__ cc_out, T *__restrict__ d1_out,
-                                                                Geo gc)
-{
-    d = zsh(d, g.zs);
-    r = zsh(r, g.zs);
-    c = zsh(c, g.zs);
-    rc_out = zsh(rc_out, g.zs);
-    cc_out = zsh(cc_out, g.zs);
-    d1_out = zsh(d1_out, g.zs);
-    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int I, J, K;
-    if (!cell_of(tid, g.n / 2, I, J, K)) return;
-    defect_restrict_psi_coarse<BC, T>(g, d, r, c, rc_out, cc_out, tid, I, J, K, d1_out, &gc);
-}
-
-// Fine-cell form: fine cell tid of the grid of 8 nc^3 threads (child_of), group
-// sums in a fixed order; lane 8 qc writes coarse cell qc.
+// Defect r - A d restricted to the coarse grid (8-child average), and the coefficient c
+// restricted the same way (cc_out may be null), on small, latency-bound grids: one thread per
+// fine cell (child_of), group sums in a fixed order; lane 8 qc writes coarse cell qc.  d1_out
+// (may be null; needs cc_out): the coarse level's first colour pass from zero, so that its
+// smoothing starts with the second pass.
 template <int BC, typename T>
 __device__ __forceinline__ void defect_restrict_psi_child(const Geo &g, const T *__restrict__ d, const T *__restrict__ r,
                                                           const T *__restrict__ c, T *__restrict__ rc_out,
@@ -686,12 +674,18 @@ __device__ __forceinline__ void defect_restrict_psi_child(const Geo &g, const T 
     const bool live = child_of(tid, g.n / 2, qc, i, j, k);
     T sd = T(0), cv = T(0);
     if (live) {
-        Acc<BC, T> D{d, g};
-        const T h2 = (T)g.inv12h2;
         const int64_t q = lidx(g.n, i, j, k);
-        const T x = d[q];
         cv = c[q];
-        sd = r[q] - (lap_sum<T>(D, i, j, k, x) * h2 + cv * x);
+        if constexpr (BC == kBcPeriodic) {
+            const T x = d[q];
+            sd = r[q] - (lap_sum<T>(Acc<BC, T>{d, g}, i, j, k, x) * (T)g.inv12h2 + cv * x);
+        } else {
+            const T rv = r[q];
+            T t[3][4];
+            double ds;
+            const T x = axis_taps<BC, T>(g, d, i, j, k, t, ds);
+            sd = rv - (lap_of_taps(t, x) * (T)g.inv12h2 + cv * x);
+        }
     }
     sd = child_sum(sd);
     const T sc = child_sum(cv);
@@ -969,59 +963,49 @@ __device__ __forceinline__ void cubic_children_add(const Src &S, T *__restrict__
         }
 }
 
-// Any coarse size: one thread per coarse cell, neighbours through the boundary rule.
-template <int BC, typename T>
-__global__ void __launch_bounds__(kBlock) k_prolong_cubic_add(Geo gc, const T *__restrict__ coarse,
-                                                              T *__restrict__ fine, int ncomp)
-{
-    coarse = zsh(coarse, gc.zs);
-    fine = zsh(fine, gc.zs);
-    const int nc = gc.n, nf = 2 * nc;
-    const int64_t mc = (int64_t)nc * nc * nc, mf = 8 * mc;
-    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int I, J, K;
-    if (!cell_of(tid, nc, I, J, K)) return;
-    for (int s = 0; s < ncomp; s++) {
-        const Acc<BC, T> C{coarse + s * mc, gc};
-        cubic_children_add<T>([&](int a, int b, int e) { return C(I - 2 + a, J - 2 + b, K - 2 + e); }, fine + s * mf,
-                              nf, I, J, K);
-    }
-}
-
-// Coarse sizes divisible by 16: a block of 4 x 4 x 16 coarse cells stages their 8 x 8 x 20
-// neighbourhood in LDS (each value loaded once) and reads the 5^3 taps from there.  A wave
-// reads four z rows of 16 values at once; with rows kCubSZP = 48 values apart the rows
-// served together land on disjoint banks (float: word offsets 0, 48, 96, 144 fill four
-// distinct 16-bank quarters of 64 banks; double: consecutive rows 96 words apart fill the
-// two halves), where the unpadded stride of 20 put 2-4 rows on the same banks.
-constexpr int kCubX = 4, kCubY = 4, kCubZ = 16;
-constexpr int kCubSX = kCubX + 4, kCubSY = kCubY + 4, kCubSZ = kCubZ + 4, kCubSZP = 48;
-template <int BC, typename T>
+// A block stages the 2-cell neighbourhood of its tile of coarse cells in LDS (each value, its
+// boundary rule included, formed once; a thread per coarse cell reading its 125 neighbours
+// through the rule took 60 us on any small Robin level, two square roots and a division per
+// ghost) and every thread reads its cell's 5^3 taps from there.  Tiles are CZ cells deep in z:
+// 4 x 4 x 16, or 4 x 8 x 8 on levels of at most kCubicRow8Max cells per axis, whose rows would
+// leave most of a 16-row empty.  Tiles may overhang the grid; positions past its ghosts are
+// neither staged nor read.  A wave reads rows of CZ values; rows kSZP apart put the rows
+// served together on disjoint banks (CZ = 16, float: word offsets 0 and 48; CZ = 8: 0, 40, 16
+// and 56 of 64 banks).
+constexpr int kCubicRow8Max = 8;
+template <int CZ>
+struct CubicTile {
+    static constexpr int kX = 4, kZ = CZ, kY = kBlock / (kX * kZ);
+    static constexpr int kSX = kX + 4, kSY = kY + 4, kSZ = kZ + 4, kSZP = CZ == 16 ? 48 : 40;
+    static int per(int nc, int t) { return (nc + t - 1) / t; }
+    static unsigned blocks(int nc) { return (unsigned)(per(nc, kX) * per(nc, kY) * per(nc, kZ)); }
+};
+template <int BC, typename T, int CZ>
 __global__ void __launch_bounds__(kBlock) k_prolong_cubic_add_staged(Geo gc, const T *__restrict__ coarse,
-                                                                     T *__restrict__ fine, int ncomp)
+                                                                     T *__restrict__ fine)
 {
-    static_assert(kCubX * kCubY * kCubZ == kBlock, "one coarse cell per thread");
+    using Q = CubicTile<CZ>;
     coarse = zsh(coarse, gc.zs);
     fine = zsh(fine, gc.zs);
-    __shared__ T S[kCubSX][kCubSY][kCubSZP];
+    __shared__ T S[Q::kSX][Q::kSY][Q::kSZP];
     const int nc = gc.n, nf = 2 * nc;
     const int64_t mc = (int64_t)nc * nc * nc, mf = 8 * mc;
-    const int nby = nc / kCubY, nbz = nc / kCubZ;
+    const int nby = (nc + Q::kY - 1) / Q::kY, nbz = (nc + Q::kZ - 1) / Q::kZ;
     const int bz = blockIdx.x % nbz, by = (blockIdx.x / nbz) % nby, bx = blockIdx.x / (nbz * nby);
-    const int I0 = bx * kCubX, J0 = by * kCubY, K0 = bz * kCubZ;
-    const int t = threadIdx.x, kz = t % kCubZ, jy = (t / kCubZ) % kCubY, ix = t / (kCubZ * kCubY);
-    constexpr int kStaged = kCubSX * kCubSY * kCubSZ;
-    for (int s = 0; s < ncomp; s++) {
-        const Acc<BC, T> C{coarse + s * mc, gc};
-        if (s > 0) __syncthreads(); // the previous component's taps are read
-        for (int q = t; q < kStaged; q += kBlock) {
-            const int a = q / (kCubSY * kCubSZ), rem = q % (kCubSY * kCubSZ), b = rem / kCubSZ, e = rem % kCubSZ;
-            S[a][b][e] = C(I0 - 2 + a, J0 - 2 + b, K0 - 2 + e);
-        }
-        __syncthreads();
-        cubic_children_add<T>([&](int a, int b, int e) { return S[ix + a][jy + b][kz + e]; }, fine + s * mf, nf,
-                              I0 + ix, J0 + jy, K0 + kz);
+    const int I0 = bx * Q::kX, J0 = by * Q::kY, K0 = bz * Q::kZ;
+    const int t = threadIdx.x, kz = t % Q::kZ, jy = (t / Q::kZ) % Q::kY, ix = t / (Q::kZ * Q::kY);
+    constexpr int kStaged = Q::kSX * Q::kSY * Q::kSZ;
+    const int s = blockIdx.y; // component
+    const Acc<BC, T> C{coarse + s * mc, gc};
+    for (int q = t; q < kStaged; q += kBlock) {
+        const int a = q / (Q::kSY * Q::kSZ), rem = q % (Q::kSY * Q::kSZ), b = rem / Q::kSZ, e = rem % Q::kSZ;
+        const int I = I0 - 2 + a, J = J0 - 2 + b, K = K0 - 2 + e;
+        if (I < nc + 2 && J < nc + 2 && K < nc + 2) S[a][b][e] = C(I, J, K);
     }
+    __syncthreads();
+    if (I0 + ix < nc && J0 + jy < nc && K0 + kz < nc)
+        cubic_children_add<T>([&](int a, int b, int e) { return S[ix + a][jy + b][kz + e]; }, fine + s * mf, nf, I0 + ix,
+                              J0 + jy, K0 + kz);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -492,7 +492,7 @@ constexpr int kRing = 6;
 
 template <int BZ>
 struct ZGeom {
-    static_assert(BZ == 128 || BZ == 64, "brick rows of 128 or 64 cells");
+    static_assert(BZ == 128 || BZ == 64 || BZ == 32, "brick rows of 128, 64 or 32 cells");
     static constexpr int kRPW = 128 / BZ;       // brick rows per wave
     static constexpr int kLPR = BZ / 2;         // lanes (z pairs) per row
     static constexpr int kTYB = kTY * kRPW;     // brick rows (y) per workgroup
@@ -507,7 +507,9 @@ struct ZGeom {
     {
         return ((PAR + DZ) & 1) * kHalfB + ((PAR + 2 + DZ) >> 1);
     }
-    __device__ static int row() { return threadIdx.y * kRPW + (int)threadIdx.x / kLPR; }
+    // the rows of a wave are kTY apart: one y parity, so the active member of their z pairs
+    // is the same and a colour pass takes one branch per wave
+    __device__ static int row() { return threadIdx.y + kTY * ((int)threadIdx.x / kLPR); }
     __device__ static int pair() { return (int)threadIdx.x % kLPR; }
 };
 
@@ -932,6 +934,28 @@ struct ResSums {
     double hsum = 0.0, hmax = 0.0, msum = 0.0, mmax2 = 0.0;
 };
 
+// Eq. Ham at a cell from the unscaled Laplacian sum lu of u, psi, the matter r5 and r1, A2 and
+// the forcing f: H and its derivative c.
+__device__ __forceinline__ void ham_point(const Geo &g, const ResArgs &a, double K2, double lu, double psi, double r5,
+                                          double r1, double A2, double f, double &H, double &c)
+{
+    const double psi2 = psi * psi, psi4 = psi2 * psi2, psi5 = psi4 * psi;
+    const double ipsi = 1.0 / psi, ipsi2 = ipsi * ipsi, ipsi4 = ipsi2 * ipsi2;
+    const double ipsi7 = ipsi4 * ipsi2 * ipsi, ipsi8 = ipsi4 * ipsi4;
+    double matter, dmatter;
+    if (a.conformal) {
+        const double rbar = r5 + r1;
+        matter = 2.0 * kPi * rbar * (ipsi4 * psi);
+        dmatter = -6.0 * kPi * rbar * ipsi4;
+    } else {
+        matter = 2.0 * kPi * r5 * psi5 + 2.0 * kPi * r1 * psi;
+        dmatter = 10.0 * kPi * r5 * psi4 + 2.0 * kPi * r1;
+    }
+    H = lu * g.inv12h2 + matter - (K2 / 12.0) * psi5 + 0.125 * A2 * ipsi7;
+    if (a.f) H += f;
+    c = dmatter - (5.0 * K2 / 12.0) * psi4 - 0.875 * A2 * ipsi8;
+}
+
 // BG: the background fields (psi0f, A2bg) may be set; the marched columns of the
 // periodic coupled solve are compiled without them (the host does not route a
 // context with a background to them).
@@ -1010,27 +1034,13 @@ __device__ __forceinline__ void residual_cell(const Geo &g, const ResArgs &a, in
 #pragma unroll
         for (int s2 = 0; s2 < 3; s2++) Mv[s2] -= 8.0 * kPi * w6 * elt(a.S + (size_t)s2 * m, q) - a.meanS[s2];
     }
-    const double psi2 = psi * psi, psi4 = psi2 * psi2, psi5 = psi4 * psi;
-    const double ipsi = 1.0 / psi, ipsi2 = ipsi * ipsi, ipsi4 = ipsi2 * ipsi2;
-    const double ipsi7 = ipsi4 * ipsi2 * ipsi, ipsi8 = ipsi4 * ipsi4;
-    const double r5 = elt(a.rho5, q), r1 = elt(a.rho1, q);
-    double matter, dmatter;
-    if (a.conformal) {
-        const double rbar = r5 + r1;
-        matter = 2.0 * kPi * rbar * (ipsi4 * psi);
-        dmatter = -6.0 * kPi * rbar * ipsi4;
-    } else {
-        matter = 2.0 * kPi * r5 * psi5 + 2.0 * kPi * r1 * psi;
-        dmatter = 10.0 * kPi * r5 * psi4 + 2.0 * kPi * r1;
-    }
     double lu;
     if constexpr (BC == kBcPeriodic)
         lu = lap_periodic(a.u, n, x, y, z, uc);
     else
         lu = lap_sum<double>(Acc<BC, double>{a.u, g}, x, y, z, uc);
-    double H = lu * g.inv12h2 + matter - (K2 / 12.0) * psi5 + 0.125 * A2 * ipsi7;
-    if (a.f) H += elt(a.f, q);
-    const double cc = dmatter - (5.0 * K2 / 12.0) * psi4 - 0.875 * A2 * ipsi8;
+    double H, cc;
+    ham_point(g, a, K2, lu, psi, elt(a.rho5, q), elt(a.rho1, q), A2, a.f ? elt(a.f, q) : 0.0, H, cc);
     if (a.H) elt(a.H, q) = H;
     if (a.c) elt(a.c, q) = cc;
     const T rT = pinned((T)(-H)), rcT = pinned((T)cc);
@@ -1041,6 +1051,8 @@ __device__ __forceinline__ void residual_cell(const Geo &g, const ResArgs &a, in
         ap.d1W = nullptr;
         first_pass_fine<BC, T>(g, ap, q, x, y, z, rT, rcT, nullptr);
     }
+    acc.hsum += H * H;
+    acc.hmax = fmax(acc.hmax, fabs(H));
     if (a.want_M) {
         if (a.M) {
 #pragma unroll
@@ -1060,8 +1072,6 @@ __device__ __forceinline__ void residual_cell(const Geo &g, const ResArgs &a, in
         acc.msum += m2;
         acc.mmax2 = fmax(acc.mmax2, m2);
     }
-    acc.hsum += H * H;
-    acc.hmax = fmax(acc.hmax, fabs(H));
 }
 
 template <int BC, typename T, int TX, bool HAS_W>
