@@ -87,12 +87,17 @@ constexpr int kProbeMax = 4096;
 // LDS (depth 2 uses 152 KB).
 constexpr int kBrickPsi = 4;
 constexpr int kBrickW = 2;
-// marched columns of 64-cell rows (levels whose side is a multiple of 64 but
-// not of 128): x planes per column of the W pass and of the W defect restriction
 // planes of a psi brick of the defect restriction
 constexpr int kBrickDefect = 4;
 // and of the residual without W (FP64 staging)
 constexpr int kBrickResidual = 2;
+// levels of at most this side take four lanes per z pair in the W kernels
+constexpr int kQuadMax = 32;
+// marched columns of 64-cell rows (levels whose side is a multiple of 64 but not of 128, in
+// single contexts: columns this short spread one 64^3 level over the chip, 7.4 us a pass,
+// while a batch group fills it with the longer columns of 32-cell rows: three 64^3 members,
+// other groups running beside them, 33 us against 48): x planes per column of the W pass and of
+// the W defect restriction
 constexpr int kMarch64Pass = 1;
 constexpr int kMarch64Defect = 2;
 constexpr int kBrickR = 2;
@@ -267,8 +272,11 @@ void carve(mg_ctx *c, Carver &cv)
     const int ls = spectral_level(c);
     c->specZ = ls >= 0 && c->n[ls] > kFourierN ? (float2 *)cv.take(3 * c->cells[ls] * sizeof(float2)) : nullptr;
     const int64_t nb = nblk(c->cells[0]);
-    // 4 partials per block of the finest level, and room for one block of the Anderson sums
-    c->part = (double *)cv.take((size_t)std::max<int64_t>(nb * 4, kMixState) * sizeof(double));
+    // 4 partials per block of the finest level (the ragged residual's overhanging columns may
+    // be more blocks), and room for one block of the Anderson sums
+    const TileMap rm = make_ragged_rmap(p.n);
+    c->part = (double *)cv.take(
+        (size_t)std::max<int64_t>({nb * 4, (int64_t)kMixState, 4 * (int64_t)rm.nx * rm.ny * rm.nz}) * sizeof(double));
     c->part_w = (p.flags & MG_FLAG_SAME_STATE) && c->momentum
                     ? (double *)cv.take((size_t)sum_blocks(c->cells[0]) * 3 * sizeof(double))
                     : nullptr;
@@ -436,10 +444,6 @@ void fill(hipStream_t s, T *a, int64_t count, T v, int gz = 1, long long zs = 0)
     if (count > 0) hipLaunchKernelGGL(k_fill<T>, dim3(nblk(count), 1, gz), dim3(kBlock), 0, s, a, count, v, zs);
 }
 
-// Defect+restriction form: one thread per fine cell on grids of at most 32^3
-// cells (latency-bound), one per coarse cell above (register reuse).
-bool fine_threads(int n_fine) { return n_fine <= 32; }
-
 // ---- coarsest level -----------------------------------------------------------------
 
 void factor(hipStream_t s, double *A, double *aug, double *inv, int m, double *flag)
@@ -517,6 +521,9 @@ void coarse_W(mg_ctx *c, const T *r, T *x)
 }
 
 // ---- psi V-cycle ----------------------------------------------------------------------
+
+// The finest residual with W marches ragged columns (periodic; 32-bit byte offsets per field).
+bool ragged_residual(int n) { return n % 2 == 0 && n >= 18 && (double)n * n * n * sizeof(double) < 4294967296.0; }
 
 // psi kernels on bricks (mg_brick.hpp) from this side on (the wrapped overhang of a brick stays
 // inside grids of at least 18 cells per axis); rows of 64 cells where they divide the side,
@@ -642,19 +649,21 @@ void defect_restrict_W(mg_ctx *c, int l, const T *d, const T *r, T *rc, T *d1 = 
     const int n = c->n[l];
     const T idiag = (T)(1.0 / (-100.0 * c->geo[l + 1].inv12h2));
     const TileMap tm = w_tileable(n) ? make_marchmap<8, 128>(n) : TileMap{0, 0, 0, 0};
-    const TileMap tm64 = w_tileable(n) ? make_marchmap<kMarch64Defect, 64>(n) : TileMap{0, 0, 0, 0};
+    const TileMap tm64 = w_tileable(n) && c->gz == 1 ? make_marchmap<kMarch64Defect, 64>(n) : TileMap{0, 0, 0, 0};
     if (tm.tx > 0)
         hipLaunchKernelGGL((k_defect_restrict_W_march<T, 8, 128>), dim3(ntiles(tm), 1, c->gz), dim3(kLanes, kTY), 0, c->s,
                            c->geo[l], tm, d, r, rc, d1, idiag);
     else if (tm64.tx > 0)
         hipLaunchKernelGGL((k_defect_restrict_W_march<T, kMarch64Defect, 64>), dim3(ntiles(tm64), 1, c->gz),
                            dim3(kLanes, kTY), 0, c->s, c->geo[l], tm64, d, r, rc, d1, idiag);
-    else if (fine_threads(n))
+    else if (n <= kQuadMax)
         hipLaunchKernelGGL(k_defect_restrict_W_quad<T>, dim3(nblk(32 * c->cells[l + 1]), 1, c->gz), dim3(kBlock), 0, c->s,
                            c->geo[l], d, r, rc, d1, idiag);
-    else
-        hipLaunchKernelGGL(k_defect_restrict_W<T>, dim3(nblk(c->cells[l + 1]), 1, c->gz), dim3(kBlock), 0, c->s, c->geo[l], d,
-                           r, rc, d1, idiag);
+    else {
+        const TileMap rm = make_ragged_map(n, c->gz);
+        hipLaunchKernelGGL((k_defect_restrict_W_march<T, 0, 32>), dim3(ntiles(rm), 1, c->gz), dim3(kLanes, kTY), 0, c->s,
+                           c->geo[l], rm, d, r, rc, d1, idiag);
+    }
 }
 
 template <typename T>
@@ -839,17 +848,21 @@ void pass_W(mg_ctx *c, int l, const T *in, T *out, const T *r, int colour)
     Probe pr(c, MG_PROBE_PASS_W, l, true);
     const TileMap &tm = c->tileW[l];
     const TileMap tm64 =
-        tm.tx == 0 && w_tileable(c->n[l]) ? make_marchmap<kMarch64Pass, 64>(c->n[l]) : TileMap{0, 0, 0, 0};
+        tm.tx == 0 && w_tileable(c->n[l]) && c->gz == 1 ? make_marchmap<kMarch64Pass, 64>(c->n[l])
+                                                        : TileMap{0, 0, 0, 0};
     if (tm.tx > 0)
         launch_W_tiled<T>(pr, c->s, c->geo[l], tm, in, out, r, colour);
     else if (tm64.tx > 0)
         probe_launch(pr, k_pass_W_march<T, kMarch64Pass, 64>, dim3(ntiles(tm64), 1, c->gz), dim3(kLanes, kTY), c->s,
                      c->geo[l], tm64, in, out, r, colour);
-    else if (c->n[l] % 2 == 0 && c->n[l] <= 32)
+    else if (c->n[l] <= kQuadMax) // smoothed levels are even
         probe_launch(pr, k_pass_W_quad<T>, dim3(nblk(2 * c->cells[l]), 1, c->gz), dim3(kBlock), c->s, c->geo[l], in, out, r,
                      colour);
-    else
-        probe_launch(pr, k_pass_W<T>, dim3(nblk(c->cells[l]), 1, c->gz), dim3(kBlock), c->s, c->geo[l], in, out, r, colour);
+    else {
+        const TileMap rm = make_ragged_map(c->n[l], c->gz);
+        probe_launch(pr, k_pass_W_march<T, 0, 32>, dim3(ntiles(rm), 1, c->gz), dim3(kLanes, kTY), c->s, c->geo[l], rm, in,
+                     out, r, colour);
+    }
 }
 
 template <typename T>
@@ -1017,6 +1030,11 @@ void residual(mg_ctx *c, const double *u, const double *W, bool want_M, double *
                                        dim3(kLanes, kTY), 0, c->s, c->geo[0], bm, a);
                 });
             });
+        } else if (tm.tx == 0 && W && c->p.bc == MG_BC_PERIODIC && ragged_residual(n) && !c->bg_psi0 && !c->bg_A2) {
+            const TileMap rm = make_ragged_rmap(n);
+            nb = ntiles(rm);
+            hipLaunchKernelGGL((k_residual_march<T, 0, true, 32>), dim3(nb, 1, c->gz), dim3(kLanes, kTY), 0, c->s,
+                               c->geo[0], rm, a);
         } else if (tm.tx > 0) {
             nb = ntiles(tm);
             if (c->p.bc == MG_BC_PERIODIC)

@@ -390,28 +390,6 @@ __device__ __forceinline__ void deltaL_apply(const Geo &g, const T *d, int64_t m
     deltaL_at<T>(g, d, (unsigned)m, WrapOff(g.n, i, j, k), out);
 }
 
-// One colour pass of the W smoother at cell q (periodic, double-buffered).
-template <typename T>
-__device__ __forceinline__ void W_pass_cell(const Geo &g, const T *__restrict__ in, T *__restrict__ out,
-                                            const T *__restrict__ r, int colour, int64_t q,
-                                            int i, int j, int k)
-{
-    const int n = g.n;
-    const int64_t m = (int64_t)n * n * n;
-    if (((i + j + k) & 1) != colour) {
-        out[q] = in[q];
-        out[m + q] = in[m + q];
-        out[2 * m + q] = in[2 * m + q];
-        return;
-    }
-    T Ad[3];
-    deltaL_apply<T>(g, in, m, i, j, k, q, Ad);
-    // diagonal of Delta_L,h: (-90 - 30/3) / (12 h^2) = -25 / (3 h^2)
-    const T diag = (T)(-100.0 * g.inv12h2);
-#pragma unroll
-    for (int s = 0; s < 3; s++) out[s * m + q] = in[s * m + q] + (r[s * m + q] - Ad[s]) / diag;
-}
-
 // Colour passes on levels without bricks (periodic): thread p owns the z pair
 // (2 kp, 2 kp + 1) of row (i, j), updates the member of the active colour and
 // copies the other (no idle lanes on the checkerboard).
@@ -600,20 +578,6 @@ __global__ void __launch_bounds__(kBlock) k_pass_psi_pairs(Geo g, const T *__res
     }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_pass_W(Geo g, const T *__restrict__ in,
-                                                   T *__restrict__ out, const T *__restrict__ r,
-                                                   int colour)
-{
-    in = zsh(in, g.zs);
-    out = zsh(out, g.zs);
-    r = zsh(r, g.zs);
-    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int i, j, k;
-    if (!cell_of(tid, g.n, i, j, k)) return;
-    W_pass_cell<T>(g, in, out, r, colour, tid, i, j, k);
-}
-
 // ---------------------------------------------------------------------------------------
 // Defect + restriction: coarse(I) = average over the 8 children of r - A d;
 // optionally the coefficient c is restricted the same way.
@@ -713,73 +677,6 @@ __global__ void __launch_bounds__(kBlock) k_defect_restrict_psi_fine(Geo g, cons
     d1_out = zsh(d1_out, g.zs);
     defect_restrict_psi_child<BC, T>(g, d, r, c, rc_out, cc_out, (int64_t)blockIdx.x * kBlock + threadIdx.x, d1_out,
                                      &gc);
-}
-
-template <typename T>
-__device__ __forceinline__ void defect_restrict_W_coarse(const Geo &g, const T *__restrict__ d, const T *__restrict__ r,
-                                                         T *__restrict__ rc_out,
-                                                         int64_t qc, int I, int J, int K)
-{
-    const int nc = g.n / 2;
-    const int64_t mf = (int64_t)g.n * g.n * g.n, mc = (int64_t)nc * nc * nc;
-    T s[3] = {T(0), T(0), T(0)};
-#pragma unroll
-    for (int di = 0; di < 2; di++)
-#pragma unroll
-        for (int dj = 0; dj < 2; dj++)
-#pragma unroll
-            for (int dk = 0; dk < 2; dk++) {
-                const int i = 2 * I + di, j = 2 * J + dj, k = 2 * K + dk;
-                const int64_t q = lidx(g.n, i, j, k);
-                T Ad[3];
-                deltaL_apply<T>(g, d, mf, i, j, k, q, Ad);
-#pragma unroll
-                for (int a = 0; a < 3; a++) s[a] += r[a * mf + q] - Ad[a];
-            }
-#pragma unroll
-    for (int a = 0; a < 3; a++) rc_out[a * mc + qc] = s[a] * T(0.125);
-}
-
-// Grid kernel with the body written out (not through defect_restrict_W_coarse):
-// at the 256-register limit the inlined form is scheduled with far fewer
-// loads in flight (mean outstanding loads per wait 4 instead of 21; 1.45x the
-// time at 128^3).
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_defect_restrict_W(Geo g, const T *__restrict__ d,
-                                                              const T *__restrict__ r,
-                                                              T *__restrict__ rc_out, T *__restrict__ d1_out,
-                                                              T idiag_c)
-{
-    d = zsh(d, g.zs);
-    r = zsh(r, g.zs);
-    rc_out = zsh(rc_out, g.zs);
-    d1_out = zsh(d1_out, g.zs);
-    const int nc = g.n / 2;
-    const int64_t mf = (int64_t)g.n * g.n * g.n, mc = (int64_t)nc * nc * nc;
-    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int I, J, K;
-    if (!cell_of(tid, nc, I, J, K)) return;
-    T s[3] = {T(0), T(0), T(0)};
-#pragma unroll
-    for (int di = 0; di < 2; di++)
-#pragma unroll
-        for (int dj = 0; dj < 2; dj++)
-#pragma unroll
-            for (int dk = 0; dk < 2; dk++) {
-                const int i = 2 * I + di, j = 2 * J + dj, k = 2 * K + dk;
-                const int64_t q = lidx(g.n, i, j, k);
-                T Ad[3];
-                deltaL_apply<T>(g, d, mf, i, j, k, q, Ad);
-#pragma unroll
-                for (int a = 0; a < 3; a++) s[a] += r[a * mf + q] - Ad[a];
-            }
-    const bool first = ((I + J + K) & 1) == 0;
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        const T v = s[a] * T(0.125);
-        rc_out[a * mc + tid] = v;
-        if (d1_out) d1_out[a * mc + tid] = first ? v * idiag_c : T(0);
-    }
 }
 
 template <typename T>

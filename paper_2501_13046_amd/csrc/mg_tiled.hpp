@@ -487,6 +487,13 @@ __global__ void __launch_bounds__(kTY *kLanes) k_pass_W_tiled(Geo g, TileMap tm,
 // written into the slot that plane x - 3 vacated, so global loads, LDS
 // traffic and arithmetic overlap for the whole column and each staged plane
 // is loaded once per column (x halo amortised over LX).
+//
+// LX = 0 serves grids of any even side from 18 cells on (rows of 32 cells, four per wave,
+// 16 per workgroup): the column length comes from the map, columns overhang the grid in y and
+// z (wrapped loads of the overhang, no stores) and the last column in x may be shorter.
+// Such levels had one thread per cell with 135 loads through the caches and half its lanes
+// idle: 160^3 FP32 pass 106 -> 43 us (147 MB, 3.4 TB/s), 80^3 16.4 -> 11.7, defect restriction
+// at 160^3 311 -> 66 us, residual 342 -> 179 us.
 // ---------------------------------------------------------------------------------------
 constexpr int kRing = 6;
 
@@ -639,17 +646,21 @@ __global__ void __launch_bounds__(kTY *kLanes) k_pass_W_march(Geo g, TileMap tm,
 
     // staged plane j (0 .. LX + 3) is x = x0 - 2 + j, in slot j % kRing; the
     // first six planes are all in flight at once
+    const int lx = LX > 0 ? LX : min(tm.tx, n - x0);
+    const bool live = LX > 0 || (y < n && z0 + 2 * p < n);
     PlaneRegs<T, BZ> st;
-    march_prologue<T, BZ>(lds, st, in, m, n, x0, y0, z0, LX > 1);
+    march_prologue<T, BZ>(lds, st, in, m, n, x0, y0, z0, lx > 1);
     auto row_of = [&](int x) { return (unsigned)(x * n + y) * (unsigned)n + (unsigned)(z0 + 2 * p); };
     auto par_of = [&](int x) { return (unsigned)((colour + x + y + z0) & 1); };
-    T rv[3];
+    T rv[3] = {T(0), T(0), T(0)};
+    if (live) {
 #pragma unroll
-    for (int f = 0; f < 3; f++) rv[f] = elt(rf[f], row_of(x0) + par_of(x0));
+        for (int f = 0; f < 3; f++) rv[f] = elt(rf[f], row_of(x0) + par_of(x0));
+    }
     __syncthreads();
 
 #pragma unroll 1
-    for (int k = 0; k < LX; k++) {
+    for (int k = 0; k < lx; k++) {
         const int x = x0 + k;
         const unsigned pa = par_of(x);
         const unsigned qa = row_of(x) + pa, qb = row_of(x) + (pa ^ 1u);
@@ -657,23 +668,25 @@ __global__ void __launch_bounds__(kTY *kLanes) k_pass_W_march(Geo g, TileMap tm,
 #pragma unroll
         for (int d = 0; d < 5; d++) pb[d] = &lds[(k + d) % kRing][ty][p];
         T rn[3] = {T(0), T(0), T(0)};
-        if (k + 1 < LX) { // r of the next plane's active cells
+        if (live && k + 1 < lx) { // r of the next plane's active cells
             const unsigned qn = row_of(x + 1) + (pa ^ 1u);
 #pragma unroll
             for (int f = 0; f < 3; f++) rn[f] = elt(rf[f], qn);
         }
-        WPart<T> P;
-        if (pa) W_march_cell<T, 1, BZ>(pb, of, qb, h2, P);
-        else W_march_cell<T, 0, BZ>(pb, of, qb, h2, P);
+        if (live) {
+            WPart<T> P;
+            if (pa) W_march_cell<T, 1, BZ>(pb, of, qb, h2, P);
+            else W_march_cell<T, 0, BZ>(pb, of, qb, h2, P);
 #pragma unroll
-        for (int f = 0; f < 3; f++) {
-            const T Ad = P.lap[f] + (P.dd[f] + P.mix[f] * m2) * third;
-            elt(of[f], qa) = P.c[f] + (rv[f] - Ad) * inv_diag;
-            rv[f] = rn[f];
+            for (int f = 0; f < 3; f++) {
+                const T Ad = P.lap[f] + (P.dd[f] + P.mix[f] * m2) * third;
+                elt(of[f], qa) = P.c[f] + (rv[f] - Ad) * inv_diag;
+                rv[f] = rn[f];
+            }
         }
-        if (k + 5 <= LX + 3) { // plane x + 3 into the slot plane x - 3 left
+        if (k + 5 <= lx + 3) { // plane x + 3 into the slot plane x - 3 left
             st.store(lds[(k + 5) % kRing]);
-            if (k + 6 <= LX + 3) st.fetch(in, m, n, x + 4, y0, z0);
+            if (k + 6 <= lx + 3) st.fetch(in, m, n, x + 4, y0, z0);
         }
         __syncthreads();
     }
@@ -708,7 +721,7 @@ __global__ void __launch_bounds__(kTY *kLanes) k_defect_restrict_W_march(Geo g, 
     rc_out = zsh(rc_out, g.zs);
     d1_out = zsh(d1_out, g.zs);
     using G = ZGeom<BZ>;
-    static_assert(LX % 2 == 0 && G::kTYB % 2 == 0, "whole coarse cells per column");
+    static_assert(LX % 2 == 0 && G::kTYB % 2 == 0, "whole coarse cells per column"); // LX = 0: an even map
     using V2 = typename Vec2<T>::type;
     __shared__ T lds[kRing][G::kNR][G::kPZB];
     __shared__ T red[3][G::kTYB / 2][G::kLPR];
@@ -722,40 +735,47 @@ __global__ void __launch_bounds__(kTY *kLanes) k_defect_restrict_W_march(Geo g, 
     const T h2 = (T)g.inv12h2, m2 = (T)g.inv144h2;
     const T third = T(1) / T(3);
 
+    const int lx = LX > 0 ? LX : min(tm.tx, n - x0); // even: the map's length and n are
+    const bool live = LX > 0 || (y < n && z0 + 2 * p < n);
     PlaneRegs<T, BZ> st;
     march_prologue<T, BZ>(lds, st, d, m, n, x0, y0, z0);
     auto pair_at = [&](int x) { return (unsigned)(x * n + y) * (unsigned)n + (unsigned)(z0 + 2 * p); };
     V2 rv[3];
 #pragma unroll
-    for (int f = 0; f < 3; f++) rv[f] = elt(reinterpret_cast<const V2 *>(rf[f]), pair_at(x0) >> 1);
+    for (int f = 0; f < 3; f++) {
+        rv[f].x = rv[f].y = T(0);
+        if (live) rv[f] = elt(reinterpret_cast<const V2 *>(rf[f]), pair_at(x0) >> 1);
+    }
     __syncthreads();
 
     T acc[3] = {T(0), T(0), T(0)};
 #pragma unroll 1
-    for (int k = 0; k < LX; k++) {
+    for (int k = 0; k < lx; k++) {
         const int x = x0 + k;
         const T *pb[5];
 #pragma unroll
         for (int dd = 0; dd < 5; dd++) pb[dd] = &lds[(k + dd) % kRing][ty][p];
         V2 rn[3];
-        if (k + 1 < LX) {
+        if (live && k + 1 < lx) {
 #pragma unroll
             for (int f = 0; f < 3; f++) rn[f] = elt(reinterpret_cast<const V2 *>(rf[f]), pair_at(x + 1) >> 1);
         }
-        const T ra[3] = {rv[0].x, rv[1].x, rv[2].x}, rb[3] = {rv[0].y, rv[1].y, rv[2].y};
-        W_defect_cell<T, 0, BZ>(pb, ra, h2, m2, third, acc);
-        W_defect_cell<T, 1, BZ>(pb, rb, h2, m2, third, acc);
+        if (live) {
+            const T ra[3] = {rv[0].x, rv[1].x, rv[2].x}, rb[3] = {rv[0].y, rv[1].y, rv[2].y};
+            W_defect_cell<T, 0, BZ>(pb, ra, h2, m2, third, acc);
+            W_defect_cell<T, 1, BZ>(pb, rb, h2, m2, third, acc);
+        }
         if ((k & 1) && (ty & 1)) {
 #pragma unroll
             for (int f = 0; f < 3; f++) red[f][ty >> 1][p] = acc[f];
         }
-        if (k + 5 <= LX + 3) {
+        if (k + 5 <= lx + 3) {
             st.store(lds[(k + 5) % kRing]);
-            if (k + 6 <= LX + 3) st.fetch(d, m, n, x + 4, y0, z0);
+            if (k + 6 <= lx + 3) st.fetch(d, m, n, x + 4, y0, z0);
         }
         __syncthreads();
         if (k & 1) {
-            if (!(ty & 1)) {
+            if (live && !(ty & 1)) {
                 const unsigned qc = ((unsigned)(x >> 1) * (unsigned)nc + (unsigned)(y >> 1)) * (unsigned)nc +
                                     (unsigned)((z0 >> 1) + p);
                 const bool first = (((x >> 1) + (y >> 1) + (z0 >> 1) + p) & 1) == 0;
@@ -769,11 +789,27 @@ __global__ void __launch_bounds__(kTY *kLanes) k_defect_restrict_W_march(Geo g, 
 #pragma unroll
             for (int f = 0; f < 3; f++) acc[f] = T(0);
         }
-        if (k + 1 < LX) {
+        if (live && k + 1 < lx) {
 #pragma unroll
             for (int f = 0; f < 3; f++) rv[f] = rn[f];
         }
     }
+}
+
+// Column map of the LX = 0 form of the marched W kernels: the longest columns (at most 8 planes,
+// which cuts the x halo's re-reads to 1.5x) that still give kRaggedFill workgroups, down to two
+// planes; three workgroups share a CU's LDS (52 KB each in FP32), so fewer leave CUs idle.
+constexpr unsigned kRaggedFill = 384;
+inline TileMap make_ragged_map(int n, int gz)
+{
+    using G = ZGeom<32>;
+    TileMap t;
+    t.ny = (n + G::kTYB - 1) / G::kTYB;
+    t.nz = (n + 31) / 32;
+    t.tx = 8;
+    while (t.tx > 2 && (unsigned)((n + t.tx - 1) / t.tx * t.ny * t.nz * gz) < kRaggedFill) t.tx /= 2;
+    t.nx = (n + t.tx - 1) / t.tx;
+    return t;
 }
 
 // Column map of the marched kernels (tx == 0: the level does not fit).
@@ -1120,96 +1156,114 @@ __global__ void __launch_bounds__(kTY *kLanes) k_residual_tiled(Geo g, TileMap t
 // vacated.  Each staged plane is loaded once per column, so the x halo costs
 // 4 / LX instead of 4 / TX of the bricks.  Same per-cell arithmetic.
 // ---------------------------------------------------------------------------------------
-constexpr int kRPlaneF = kPY * kRPZ; // one field of a staged plane
-constexpr int kRSlot = 3 * kRPlaneF; // one ring slot
+// Rows of RZ cells: 64 (one per wave, four per workgroup), or 32 (two per wave, eight per
+// workgroup), the form that serves grids of any even side from 18 cells on (columns overhang
+// the grid in y and z as in the marched W pass).
+template <int RZ>
+struct RGeom {
+    static constexpr int kRPW = kLanes / RZ, kTYR = kTY * kRPW, kPYR = kTYR + 4, kPZR = RZ + 4;
+    static constexpr int kPlaneF = kPYR * kPZR, kSlot = 3 * kPlaneF; // one field, one ring slot
+    __device__ static int row() { return threadIdx.y * kRPW + (int)threadIdx.x / RZ; }
+    __device__ static int col() { return (int)threadIdx.x % RZ; }
+};
 
-// One staged x plane of the three W fields: 3 kPY rows of kRPZ words; load i
-// of a thread moves word `lane` of row w + kTY i, threads tid < 4 * 3 kPY the
-// four remaining words of row tid / 4.
+// One staged x plane of the three W fields: 3 kPYR rows of kPZR words; load i of a thread
+// moves word col of row row + kTYR i, threads tid < 4 * 3 kPYR the four remaining words of row
+// tid / 4.
+template <int RZ>
 struct RPlaneRegs {
-    static constexpr int NROW = 3 * kPY;
-    static constexpr int RPW = NROW / kTY;
-    static_assert(NROW % kTY == 0 && 4 * NROW <= kTY * kLanes, "rows of a plane over the block");
+    using G = RGeom<RZ>;
+    static constexpr int NROW = 3 * G::kPYR;
+    static constexpr int RPW = (NROW + G::kTYR - 1) / G::kTYR;
+    static_assert(4 * NROW <= kTY * kLanes, "rows of a plane over the block");
     double v[RPW];
     double e;
     __device__ __forceinline__ void fetch(const double *__restrict__ W, unsigned m, int n, int x, int y0, int z0)
     {
-        const int w = threadIdx.y, lane = threadIdx.x, tid = w * kLanes + lane;
+        const int w = G::row(), lane = G::col(), tid = threadIdx.y * kLanes + threadIdx.x;
         const unsigned un = (unsigned)n, xo = (unsigned)wrap(x, n) * un;
         const unsigned zw = (unsigned)wrap(z0 - 2 + lane, n);
 #pragma unroll
         for (int i = 0; i < RPW; i++) {
-            const int row = w + kTY * i, f = row / kPY, yr = row - f * kPY;
-            v[i] = elt(W + (size_t)f * m, (xo + (unsigned)wrap(y0 + yr - 2, n)) * un + zw);
+            const int row = w + G::kTYR * i, f = row / G::kPYR, yr = row - f * G::kPYR;
+            if (NROW % G::kTYR == 0 || row < NROW)
+                v[i] = elt(W + (size_t)f * m, (xo + (unsigned)wrap(y0 + yr - 2, n)) * un + zw);
         }
         e = 0.0;
         if (tid < 4 * NROW) {
-            const int row = tid >> 2, f = row / kPY, yr = row - f * kPY;
-            e = elt(W + (size_t)f * m, (xo + (unsigned)wrap(y0 + yr - 2, n)) * un + (unsigned)wrap(z0 + kRZ - 2 + (tid & 3), n));
+            const int row = tid >> 2, f = row / G::kPYR, yr = row - f * G::kPYR;
+            e = elt(W + (size_t)f * m, (xo + (unsigned)wrap(y0 + yr - 2, n)) * un + (unsigned)wrap(z0 + RZ - 2 + (tid & 3), n));
         }
     }
     __device__ __forceinline__ void store(double *slot) const
     {
-        const int w = threadIdx.y, lane = threadIdx.x, tid = w * kLanes + lane;
+        const int w = G::row(), lane = G::col(), tid = threadIdx.y * kLanes + threadIdx.x;
 #pragma unroll
-        for (int i = 0; i < RPW; i++) slot[(w + kTY * i) * kRPZ + lane] = v[i];
-        if (tid < 4 * NROW) slot[(tid >> 2) * kRPZ + kRZ + (tid & 3)] = e;
+        for (int i = 0; i < RPW; i++)
+            if (NROW % G::kTYR == 0 || w + G::kTYR * i < NROW) slot[(w + G::kTYR * i) * G::kPZR + lane] = v[i];
+        if (tid < 4 * NROW) slot[(tid >> 2) * G::kPZR + RZ + (tid & 3)] = e;
     }
 };
 
 // Taps of field F around the thread's cell: pb[DX + 2] is the word of the
 // stencil corner row (y - 2, z - 2) in the slot of plane x + DX.
-template <int F>
+template <int F, int RZ>
 struct RRing {
+    using G = RGeom<RZ>;
     static constexpr bool kOrdered = true;
     const double *const *pb;
     template <int DX, int DY, int DZ>
     __device__ __forceinline__ double at() const
     {
-        return pb[DX + 2][F * kRPlaneF + (DY + 2) * kRPZ + DZ + 2];
+        return pb[DX + 2][F * G::kPlaneF + (DY + 2) * G::kPZR + DZ + 2];
     }
 };
 
-template <typename T, int LX, bool HAS_W>
+// LX = 0: the column length comes from the map (rows of 32 cells, any even side).
+template <typename T, int LX, bool HAS_W, int RZ = kRZ>
 __global__ void __launch_bounds__(kTY *kLanes) k_residual_march(Geo g, TileMap tm, ResArgs a)
 {
+    using G = RGeom<RZ>;
     a = res_shift(a, g.zs);
-    __shared__ double ring[HAS_W ? kRing : 1][HAS_W ? kRSlot : 1];
+    __shared__ double ring[HAS_W ? kRing : 1][HAS_W ? G::kSlot : 1];
     const int total = tm.nx * tm.ny * tm.nz;
     int logical = blockIdx.x;
     if (total % kXCD == 0) logical = (blockIdx.x % kXCD) * (total / kXCD) + blockIdx.x / kXCD;
     const int bz = logical % tm.nz, rest = logical / tm.nz;
-    const int x0 = (rest / tm.ny) * LX, y0 = (rest % tm.ny) * kTY, z0 = bz * kRZ;
+    const int x0 = (rest / tm.ny) * (LX > 0 ? LX : tm.tx), y0 = (rest % tm.ny) * G::kTYR, z0 = bz * RZ;
     const int n = g.n;
     const unsigned m = (unsigned)n * n * n;
-    const int ty = threadIdx.y, lane = threadIdx.x;
+    const int ty = G::row(), lane = G::col();
     const int y = y0 + ty, z = z0 + lane;
-    RPlaneRegs st;
+    const int lx = LX > 0 ? LX : min(tm.tx, n - x0);
+    const bool live = LX > 0 || (y < n && z < n);
+    RPlaneRegs<RZ> st;
     if constexpr (HAS_W) {
-        // staged plane j (0 .. LX + 3) is x = x0 - 2 + j, in slot j % kRing; the
+        // staged plane j (0 .. lx + 3) is x = x0 - 2 + j, in slot j % kRing; the
         // first six planes are all in flight at once
-        RPlaneRegs w5[5];
+        RPlaneRegs<RZ> w5[5];
 #pragma unroll
         for (int j = 0; j < 5; j++) w5[j].fetch(a.W, m, n, x0 - 2 + j, y0, z0);
-        if (LX > 1) st.fetch(a.W, m, n, x0 + 3, y0, z0);
+        if (lx > 1) st.fetch(a.W, m, n, x0 + 3, y0, z0);
 #pragma unroll
         for (int j = 0; j < 5; j++) w5[j].store(ring[j]);
         __syncthreads();
     }
     ResSums acc;
 #pragma unroll 1
-    for (int k = 0; k < LX; k++) {
+    for (int k = 0; k < lx; k++) {
         const double *pb[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
         if constexpr (HAS_W) {
 #pragma unroll
-            for (int d = 0; d < 5; d++) pb[d] = &ring[(k + d) % kRing][ty * kRPZ + lane];
+            for (int d = 0; d < 5; d++) pb[d] = &ring[(k + d) % kRing][ty * G::kPZR + lane];
         }
-        residual_cell<kBcPeriodic, T, HAS_W, false>(
-            g, a, x0 + k, y, z, [&](auto fc) { return RRing<decltype(fc)::value>{pb}; }, acc);
+        if (live)
+            residual_cell<kBcPeriodic, T, HAS_W, false>(
+                g, a, x0 + k, y, z, [&](auto fc) { return RRing<decltype(fc)::value, RZ>{pb}; }, acc);
         if constexpr (HAS_W) {
-            if (k + 5 <= LX + 3) { // plane x + 3 into the slot plane x - 3 left
+            if (k + 5 <= lx + 3) { // plane x + 3 into the slot plane x - 3 left
                 st.store(ring[(k + 5) % kRing]);
-                if (k + 6 <= LX + 3) st.fetch(a.W, m, n, x0 + k + 4, y0, z0);
+                if (k + 6 <= lx + 3) st.fetch(a.W, m, n, x0 + k + 4, y0, z0);
             }
             __syncthreads();
         }
@@ -1219,6 +1273,20 @@ __global__ void __launch_bounds__(kTY *kLanes) k_residual_march(Geo g, TileMap t
         // 256 threads per block, as block_reduce_store assumes
         block_reduce_store<4>(v, 0xAu, a.partials + 4 * (int64_t)blockIdx.x);
     }
+}
+
+// Column map of the LX = 0 form (rows of 32 cells): the longest columns of at most 16 planes
+// that still give one workgroup per CU of a 256-CU device.
+inline TileMap make_ragged_rmap(int n)
+{
+    using G = RGeom<32>;
+    TileMap t;
+    t.ny = (n + G::kTYR - 1) / G::kTYR;
+    t.nz = (n + 31) / 32;
+    t.tx = 16;
+    while (t.tx > 1 && (n + t.tx - 1) / t.tx * t.ny * t.nz < 256) t.tx /= 2;
+    t.nx = (n + t.tx - 1) / t.tx;
+    return t;
 }
 
 // Column map of the marched residual (tx == 0: the level does not fit).

@@ -1,9 +1,10 @@
-"""psi kernels on LDS bricks (any even side and boundary rule), and the pair kernels below
-them, against the oracle: sides that are a multiple of the brick, that overhang it in y and
+"""psi kernels on LDS bricks (any even side and boundary rule), the pair kernels below
+them and the marched W kernels of any even side, against the oracle: sides that are a multiple of the brick, that overhang it in y and
 z, and that leave a half brick in x.
 
 FP32 tolerances: a 13-term sum of weights that add up to 180 against a diagonal of 90 keeps
-13 * 2 * 2^-24 = 1.6e-6 of the largest value; a restricted defect is such a sum itself.
+13 * 2 * 2^-24 = 1.6e-6 of the largest value; a restricted defect is such a sum itself (W: 135
+taps whose weights add up to 300 against a diagonal of 100).
 """
 import numpy as np
 import pytest
@@ -87,3 +88,36 @@ def test_cubic_prolongation_of_any_side(nc, bc, ncomp):
     s.kernel_op(g.OP_PROLONG_ADD, 0, ncomp, T(C), out)
     ref = np.stack([F[a] + oracle.interp_cubic(poc, np.ascontiguousarray(C[a])) for a in range(ncomp)])
     assert rel_err(N(out), ref) < 1e-13
+
+
+@pytest.mark.parametrize("n,levels", [(40, 4), (48, 4), (56, 4), (80, 5), (112, 5)])
+@pytest.mark.parametrize("precision", [g.PREC_FP32_IR, g.PREC_FP64])
+def test_ragged_w_columns(n, levels, precision):
+    """The marched W pass, defect restriction and residual on sides that are no multiple of
+    their rows: columns that overhang the grid, and a last column of fewer planes."""
+    f32 = precision == g.PREC_FP32_IR
+    vt = torch.float32 if f32 else torch.float64
+    K = 1.7
+    p = g.params(n, levels, K=K, precision=precision, solve_momentum=True)
+    po = oracle.params(n, levels, K=K, solve_momentum=True)
+    rho5, rho1 = field(40, n, 0, 1, False), field(41, n, 0, 1, False)
+    S = synth.uniform_random(42, (3, n, n, n))
+    s = g.Solver(p, T(rho5), T(rho1), T(S))
+    d, r = synth.uniform_random(43, (3, n, n, n)), synth.uniform_random(44, (3, n, n, n), -500, 500)
+    if f32:
+        d, r = (a.astype(np.float32).astype(np.float64) for a in (d, r))
+    for colour in (0, 1):
+        out = torch.full((3, n, n, n), np.nan, dtype=vt, device=dev())
+        s.kernel_op(g.OP_PASS_W, 0, colour, T(d, vt), out, T(r, vt))
+        assert rel_err(N(out), oracle.pass_W(po, d, r, colour)) < (4e-6 if f32 else 1e-12), colour
+    out = torch.full((3,) + (n // 2,) * 3, np.nan, dtype=vt, device=dev())
+    s.kernel_op(g.OP_DEFECT_RESTRICT_W, 0, 0, T(d, vt), out, T(r, vt))
+    defect = r - oracle.apply_deltaL(po, d)
+    ref = np.stack([oracle.restrict(np.ascontiguousarray(defect[a])) for a in range(3)])
+    assert rel_err(N(out), ref) < (1e-5 if f32 else 1e-12)
+    u = field(45, n, -0.05, 0.05, False)
+    W = synth.uniform_random(46, (3, n, n, n), -0.02, 0.02)
+    H, M, c = s.residual_fields(T(u), T(W))
+    Ho, Mo, co = oracle.residuals(po, u, W, rho5, rho1, S)
+    assert rel_err(N(H), Ho) < 1e-12 and rel_err(N(M), Mo) < 1e-12 and rel_err(N(c), co) < 1e-13
+    np.testing.assert_allclose(s.residual_norm(T(u), T(W)), oracle.norms(Ho, Mo), rtol=1e-11)
