@@ -463,7 +463,9 @@ mg_status mg_fmg_start(mg_ctx *cc, mg_ctx *cf, double *d_uc, double *d_Wc, doubl
  * level from which the cells of all levels down to the coarsest sum to at
  * most 4680 (psi, FP32, periodic) or 1971 (psi otherwise; W), spanning at
  * most 4 levels (e.g. 16^3 for psi and 8^3 for W, FP32 periodic), or from any
- * level below it down to the one above the coarsest.  Their `level` is the tail's
+ * level below it down to the one above the coarsest.  For psi, 0 means the
+ * library's own start of that kernel: the first level of at most 16^3 cells (one
+ * launch is quicker there than a launch per step).  Their `level` is the tail's
  * first level: mg_autotune times one whole V-cycle with the tail off and starting
  * at each such level and reports the fastest start (chosen 1) or the fastest
  * start tried (chosen 0, the tail off); mg_set_tile(family, level, 1) starts the

@@ -22,6 +22,7 @@
 #include "mg_kernels.hpp"
 #include "mg_tiled.hpp"
 #include "mg_brick.hpp"
+#include "mg_bottom.hpp"
 #include "mg_cttk.hpp"
 #include "mg_refine.hpp"
 #include "mg_fourier.hpp"
@@ -80,6 +81,16 @@ void with_bc(int bc, F &&f)
     }
 }
 
+// f(std::integral_constant<int, kBc...>{}) with the context's boundary rule.
+template <typename F>
+void with_rule(int bc, F &&f)
+{
+    if (bc == MG_BC_PERIODIC)
+        f(std::integral_constant<int, kBcPeriodic>{});
+    else
+        with_bc(bc, f);
+}
+
 constexpr int kProbeMax = 4096;
 // Brick depths along x of the tiled kernels: defaults and the candidates the
 // autotuner times (per-cell arithmetic does not depend on the depth, so every
@@ -131,6 +142,7 @@ struct mg_ctx {
     TileMap tile[kMaxLevels];  // brick map of the psi smoother per level (tx == 0: not tiled)
     TileMap tileW[kMaxLevels]; // brick map of the W smoother per level
     TileMap tileR;             // brick map of the finest-level residual
+    int bottom_psi;            // level from which the psi V-cycle runs in one workgroup (-1: none)
     int tail_psi, tail_W;      // first level of the workgroup-resident V-cycle tail (-1: not possible)
     int tail_psi_min, tail_W_min; // the highest level a tail can start from (its arrays fit in LDS)
     bool tail_psi_on, tail_W_on; // tail in use (chosen by mg_autotune / mg_set_tile; off by default)
@@ -144,7 +156,6 @@ struct mg_ctx {
     double *part_w; // the W step's partial sums while it runs beside the psi step
     double *scal;
     int m_psi, m_W;
-    double *A_psi, *aug_psi, *inv_psi;
     double *A_W, *aug_W, *inv_W;
     double *hpin;
     const double *rho5, *rho1, *S, *f;
@@ -301,10 +312,6 @@ void carve(mg_ctx *c, Carver &cv)
     }
     c->scal = (double *)cv.take(S_COUNT * sizeof(double));
     c->m_psi = (int)c->cells[c->L - 1];
-    const size_t mp = (size_t)c->m_psi;
-    c->A_psi = (double *)cv.take(mp * mp * sizeof(double));
-    c->aug_psi = (double *)cv.take(2 * mp * mp * sizeof(double));
-    c->inv_psi = (double *)cv.take(mp * mp * sizeof(double));
     if (c->momentum) {
         c->m_W = 3 * c->m_psi;
         const size_t mw = (size_t)c->m_W;
@@ -317,8 +324,10 @@ void carve(mg_ctx *c, Carver &cv)
     }
 }
 
-// Coarsest sizes solved by the register-resident Gauss-Jordan kernel (one block).
+// Coarsest psi systems below which a psi tail may be chosen.
 bool wave_solvable(int m) { return m == 8 || m == 27 || m == 64; }
+static_assert(kMaxCoarsePsi <= kKrylovMax && kMaxCoarsePsi <= 12 * 12 * 12 && kPaddedCoarse >= 16 * 16 * 16,
+              "every coarsest psi system has a solver");
 
 TileMap tilemap_rt(int n, int tx)
 {
@@ -367,15 +376,17 @@ void init_geo(mg_ctx *c)
         else if (r8.tx > 0 && ntiles(r8) >= 512)
             c->tileR = r8;
     }
-    // V-cycle tails: from the first level whose levels down to the coarsest fit
-    // the tail's LDS arrays; at least one level above the coarsest, at most
-    // kMaxTail levels, coarsest psi system solvable in registers.
+    // the psi V-cycle's coarse levels in one workgroup: from the first level that fits
+    c->bottom_psi = -1;
+    for (int l = 0; l + 1 < c->L && c->bottom_psi < 0; l++)
+        if (c->f32 ? bottom_fits<float>(c->n + l, c->L - l) : bottom_fits<double>(c->n + l, c->L - l)) c->bottom_psi = l;
+    // V-cycle tails that may be chosen: from the first level whose cells down to the coarsest
+    // are within these bounds; at least one level above the coarsest, at most kMaxTail levels,
+    // coarsest psi system of at most 64 cells.
     c->tail_psi = c->tail_W = -1;
     c->tail_psi_on = c->tail_W_on = false;
-    const int cap_psi = c->p.bc != MG_BC_PERIODIC ? TailCap<float>::kPsiRobin
-                        : c->f32                   ? TailCap<float>::kPsi
-                                                   : TailCap<double>::kPsi;
-    const int cap_W = c->f32 ? TailCap<float>::kW : TailCap<double>::kW;
+    const int cap_psi = c->p.bc == MG_BC_PERIODIC && c->f32 ? 4680 : 1971;
+    const int cap_W = kTailW;
     auto cells_from = [&](int l) {
         int64_t s = 0;
         for (int q = l; q < c->L; q++) s += c->cells[q];
@@ -453,62 +464,16 @@ void factor(hipStream_t s, double *A, double *aug, double *inv, int m, double *f
 }
 
 
-template <int BC, typename T>
-void launch_coarse_wave(mg_ctx *c, int l, const T *r, T *x)
-{
-    const Geo &g = c->geo[l];
-    const T *cf = (const T *)c->pc[l];
-    double *flag = c->scal + S_FLAG_PSI;
-    switch (c->m_psi) {
-    case 8: hipLaunchKernelGGL((k_coarse_psi_block<BC, T, 8>), dim3(1, 1, c->gz), dim3(kGjWaves * kWave), 0, c->s, g, cf, r, x, flag); break;
-    case 27: hipLaunchKernelGGL((k_coarse_psi_block<BC, T, 27>), dim3(1, 1, c->gz), dim3(kGjWaves * kWave), 0, c->s, g, cf, r, x, flag); break;
-    default: hipLaunchKernelGGL((k_coarse_psi_block<BC, T, 64>), dim3(1, 1, c->gz), dim3(kGjWaves * kWave), 0, c->s, g, cf, r, x, flag); break;
-    }
-}
-
 template <typename T>
 void coarse_psi(mg_ctx *c, const T *r, T *x)
 {
     const int l = c->L - 1;
     Probe pr(c, MG_PROBE_COARSE, l);
-    const int m = c->m_psi;
-    if (wave_solvable(m)) {
-        if (c->p.bc == MG_BC_PERIODIC)
-            launch_coarse_wave<kBcPeriodic, T>(c, l, r, x);
-        else
-            with_bc(c->p.bc, [&](auto bcx) {
-                constexpr int BCX = decltype(bcx)::value;
-                launch_coarse_wave<BCX, T>(c, l, r, x);
-            });
-        return;
-    }
-    if (m <= kKrylovMax) {
-        // conjugate gradients (periodic) or BiCGSTAB (Robin) on one block; a system it
-        // does not solve to 1e-12 raises the singular flag
-        if (c->p.bc == MG_BC_PERIODIC)
-            hipLaunchKernelGGL((k_coarse_psi_krylov<kBcPeriodic, T>), dim3(1, 1, c->gz), dim3(kGjWaves * kWave), 0, c->s,
-                               c->geo[l], m, (const T *)c->pc[l], r, x, c->scal + S_FLAG_PSI);
-        else
-            with_bc(c->p.bc, [&](auto bcx) {
-                constexpr int BCX = decltype(bcx)::value;
-                hipLaunchKernelGGL((k_coarse_psi_krylov<BCX, T>), dim3(1, 1, c->gz), dim3(kGjWaves * kWave), 0, c->s,
-                                   c->geo[l], m, (const T *)c->pc[l], r, x, c->scal + S_FLAG_PSI);
-            });
-        return;
-    }
-    fill<double>(c->s, c->A_psi, (int64_t)m * m, 0.0);
-    if (c->p.bc == MG_BC_PERIODIC)
-        hipLaunchKernelGGL((k_assemble_psi<kBcPeriodic, T>), dim3(nblk(m)), dim3(kBlock), 0, c->s,
-                           c->geo[l], (const T *)c->pc[l], c->A_psi);
-    else
-        with_bc(c->p.bc, [&](auto bcx) {
-            constexpr int BCX = decltype(bcx)::value;
-            hipLaunchKernelGGL((k_assemble_psi<BCX, T>), dim3(nblk(m)), dim3(kBlock), 0, c->s,
-                               c->geo[l], (const T *)c->pc[l], c->A_psi);
-        });
-    factor(c->s, c->A_psi, c->aug_psi, c->inv_psi, m, c->scal + S_FLAG_PSI);
-    hipLaunchKernelGGL(k_coarse_apply<T>, dim3((m + kApplyRows - 1) / kApplyRows, 1, c->gz), dim3(kBlock),
-                       m * sizeof(double), c->s, (const double *)c->inv_psi, m, r, x, 0, c->zs);
+    with_rule(c->p.bc, [&](auto bcx) {
+        constexpr int BCX = decltype(bcx)::value;
+        hipLaunchKernelGGL((k_coarse_psi<BCX, T>), dim3(1, 1, c->gz), dim3(kGjWaves * kWave), 0, c->s, c->geo[l],
+                           c->m_psi, (const T *)c->pc[l], r, x, c->scal + S_FLAG_PSI);
+    });
 }
 
 template <typename T>
@@ -542,16 +507,6 @@ void with_rows(int n, F &&f)
         f(std::integral_constant<int, 64>{});
     else
         f(std::integral_constant<int, 32>{});
-}
-
-// f(std::integral_constant<int, kBc...>{}) with the context's boundary rule.
-template <typename F>
-void with_rule(int bc, F &&f)
-{
-    if (bc == MG_BC_PERIODIC)
-        f(std::integral_constant<int, kBcPeriodic>{});
-    else
-        with_bc(bc, f);
 }
 
 template <typename T>
@@ -698,40 +653,6 @@ void prolong_add(mg_ctx *c, int lc, const T *coarse, T *fine, int ncomp)
         });
 }
 
-// After the residual wrote the finest c: restrict c level by level and, when
-// the coarsest system is too large for the register-resident solver, assemble and
-// invert it.  All on the context's stream: the V-cycle kernels that follow
-// stay on one queue of the graph.
-// Without a V-cycle tail and with the coarsest psi system solved in registers,
-// the coefficient c of each coarser level is restricted by the defect
-// restriction that produces that level's right-hand side (the level is not
-// smoothed before), so no separate sweep over the levels is needed.
-// A tail restricts c below its own first level.
-bool c_with_defect(const mg_ctx *c) { return wave_solvable(c->m_psi) || c->m_psi <= kKrylovMax; }
-
-template <typename T>
-void restrict_coefficients(mg_ctx *c)
-{
-    if (c_with_defect(c)) return; // each level's c comes with its defect restriction
-    for (int l = 0; l + 1 < c->L; l++)
-        hipLaunchKernelGGL(k_restrict<T>, dim3(nblk(c->cells[l + 1]), 1, c->gz), dim3(kBlock), 0, c->s, c->n[l],
-                           (const T *)c->pc[l], (T *)c->pc[l + 1], c->zs);
-    const int l = c->L - 1;
-    const int m = c->m_psi;
-    if (wave_solvable(m) || m <= kKrylovMax) return; // solved directly at the bottom of the V-cycle
-    fill<double>(c->s, c->A_psi, (int64_t)m * m, 0.0);
-    if (c->p.bc == MG_BC_PERIODIC)
-        hipLaunchKernelGGL((k_assemble_psi<kBcPeriodic, T>), dim3(nblk(m)), dim3(kBlock), 0, c->s, c->geo[l],
-                           (const T *)c->pc[l], c->A_psi);
-    else
-        with_bc(c->p.bc, [&](auto bcx) {
-            constexpr int BCX = decltype(bcx)::value;
-            hipLaunchKernelGGL((k_assemble_psi<BCX, T>), dim3(nblk(m)), dim3(kBlock), 0, c->s, c->geo[l],
-                               (const T *)c->pc[l], c->A_psi);
-        });
-    factor(c->s, c->A_psi, c->aug_psi, c->inv_psi, m, c->scal + S_FLAG_PSI);
-}
-
 // Sweeps of the W V-cycle: the parameters' own while its bottom is exact, else the psi
 // cycle's.
 int nu_pre_W(const mg_ctx *c)
@@ -744,7 +665,7 @@ int nu_post_W(const mg_ctx *c)
 }
 
 template <typename T>
-TailArgs<T> tail_args(mg_ctx *c, int l0, bool W)
+TailArgs<T> tail_args(mg_ctx *c, int l0)
 {
     TailArgs<T> a;
     std::memset(&a, 0, sizeof(a));
@@ -752,70 +673,59 @@ TailArgs<T> tail_args(mg_ctx *c, int l0, bool W)
     a.nu_pre = c->p.nu_pre; // a W tail runs only below a multigrid bottom
     a.nu_post = c->p.nu_post;
     for (int q = 0; q < a.nl; q++) a.geo[q] = c->geo[l0 + q];
-    a.r0 = (const T *)(W ? c->wr[l0] : c->pr[l0]);
-    a.c0 = W ? nullptr : (const T *)c->pc[l0];
-    a.d0 = (T *)(W ? c->wd0[l0] : c->pd0[l0]);
+    a.r0 = (const T *)c->wr[l0];
+    a.d0 = (T *)c->wd0[l0];
     a.inv = c->inv_W;
-    a.flag = c->scal + S_FLAG_PSI;
     return a;
 }
 
+// The level from which the psi V-cycle runs in one workgroup (mg_bottom.hpp); -1: none.
+int bottom_level(const mg_ctx *c) { return c->tail_psi_on ? c->tail_psi : c->bottom_psi; }
+
 template <typename T>
-void tail_psi(mg_ctx *c)
+void bottom_psi(mg_ctx *c, int l0)
 {
     Probe pr(c, MG_PROBE_COARSE, c->L - 1);
-    const TailArgs<T> a = tail_args<T>(c, c->tail_psi, false);
-    const dim3 g1(1, 1, c->gz), blk(kTailThreads);
-    if (c->p.bc == MG_BC_PERIODIC) {
-        switch (c->m_psi) {
-        case 8: hipLaunchKernelGGL((k_tail_psi<kBcPeriodic, T, 8>), g1, blk, 0, c->s, a); break;
-        case 27: hipLaunchKernelGGL((k_tail_psi<kBcPeriodic, T, 27>), g1, blk, 0, c->s, a); break;
-        default: hipLaunchKernelGGL((k_tail_psi<kBcPeriodic, T, 64>), g1, blk, 0, c->s, a); break;
-        }
-    } else {
-        with_bc(c->p.bc, [&](auto bcx) {
-            constexpr int BCX = decltype(bcx)::value;
-            switch (c->m_psi) {
-            case 8: hipLaunchKernelGGL((k_tail_psi<BCX, T, 8>), g1, blk, 0, c->s, a); break;
-            case 27: hipLaunchKernelGGL((k_tail_psi<BCX, T, 27>), g1, blk, 0, c->s, a); break;
-            default: hipLaunchKernelGGL((k_tail_psi<BCX, T, 64>), g1, blk, 0, c->s, a); break;
-            }
-        });
-    }
+    BottomArgs<T> a;
+    std::memset(&a, 0, sizeof(a));
+    a.nl = c->L - l0;
+    a.nu_pre = c->p.nu_pre;
+    a.nu_post = c->p.nu_post;
+    a.cubic = (c->p.flags & MG_FLAG_CUBIC_PROLONG) ? 1 : 0;
+    for (int q = 0; q < a.nl; q++) a.geo[q] = c->geo[l0 + q];
+    a.r0 = (const T *)c->pr[l0];
+    a.c0 = (const T *)c->pc[l0];
+    a.d0 = (T *)c->pd0[l0];
+    a.flag = c->scal + S_FLAG_PSI;
+    with_rule(c->p.bc, [&](auto bcx) {
+        constexpr int BCX = decltype(bcx)::value;
+        hipLaunchKernelGGL((k_bottom_psi<BCX, T>), dim3(1, 1, c->gz), dim3(kBottomThreads), 0, c->s, a);
+    });
 }
 
-// psi V-cycle on level l; the coefficients of levels > 0 and the coarsest
-// inverse come from restrict_coefficients (and the tail kernel below its first level).
-template <typename T>
+// psi V-cycle on level l; the coefficient of each coarser level comes with the defect
+// restriction that produces its right-hand side.
 // first_done: the producer of this level's right-hand side also wrote the
-// first colour pass from a zero correction into pd1 (coarser levels, when c
-// is restricted with the defect).
+// first colour pass from a zero correction into pd1.
+template <typename T>
 void vcycle_psi(mg_ctx *c, int l, bool first_done = false)
 {
-    if (c->tail_psi_on && l == c->tail_psi) {
-        tail_psi<T>(c);
+    const int lb = bottom_level(c);
+    if (l == lb) {
+        bottom_psi<T>(c, l);
         return;
     }
     if (l == c->L - 1) {
-        const int m = c->m_psi;
-        if (wave_solvable(m) || m <= kKrylovMax) {
-            coarse_psi<T>(c, (const T *)c->pr[l], (T *)c->pd0[l]);
-            return;
-        }
-        Probe pr(c, MG_PROBE_COARSE, l);
-        hipLaunchKernelGGL(k_coarse_apply<T>, dim3((m + kApplyRows - 1) / kApplyRows, 1, c->gz), dim3(kBlock),
-                           m * sizeof(double), c->s, (const double *)c->inv_psi, m, (const T *)c->pr[l],
-                           (T *)c->pd0[l], 0, c->zs);
+        coarse_psi<T>(c, (const T *)c->pr[l], (T *)c->pd0[l]);
         return;
     }
     if (!first_done) fill<T>(c->s, (T *)c->pd0[l], c->cells[l], T(0), c->gz, c->zs);
     smooth_psi<T>(c, l, c->p.nu_pre, first_done);
     // the next level's first pass comes with its defect when that level is
-    // smoothed by grid launches (a tail starts from zero in LDS)
-    const bool next_first = c_with_defect(c) && l + 2 < c->L && !(c->tail_psi_on && l + 1 == c->tail_psi);
+    // smoothed by grid launches
+    const bool next_first = l + 2 < c->L && l + 1 != lb;
     defect_restrict_psi<T>(c, l, (const T *)c->pd0[l], (const T *)c->pr[l], (const T *)c->pc[l],
-                           (T *)c->pr[l + 1], c_with_defect(c) ? (T *)c->pc[l + 1] : nullptr,
-                           next_first ? (T *)c->pd1[l + 1] : nullptr);
+                           (T *)c->pr[l + 1], (T *)c->pc[l + 1], next_first ? (T *)c->pd1[l + 1] : nullptr);
     vcycle_psi<T>(c, l + 1, next_first);
     prolong_add<T>(c, l + 1, (const T *)c->pd0[l + 1], (T *)c->pd0[l], 1);
     smooth_psi<T>(c, l, c->p.nu_post);
@@ -910,7 +820,7 @@ void vcycle_W(mg_ctx *c, int l, bool first_done = false)
     }
     if (c->tail_W_on && l == c->tail_W) {
         Probe pr(c, MG_PROBE_COARSE, c->L - 1);
-        hipLaunchKernelGGL(k_tail_W<T>, dim3(1, 1, c->gz), dim3(kTailThreads), 0, c->s, tail_args<T>(c, l, true));
+        hipLaunchKernelGGL(k_tail_W<T>, dim3(1, 1, c->gz), dim3(kTailThreads), 0, c->s, tail_args<T>(c, l));
         return;
     }
     if (l == c->L - 1) {
@@ -1128,7 +1038,6 @@ void step_psi(mg_ctx *c, double *u, const double *W, bool residual_done)
 {
     if (!residual_done)
         residual<T>(c, u, W, false, nullptr, nullptr, nullptr, c->pr[0], c->pc[0], nullptr, false, true);
-    restrict_coefficients<T>(c);
     // the residual (this step's or the evaluation's) wrote the first pass into pd1
     vcycle_psi<T>(c, 0, true);
     const int64_t m = c->cells[0];
@@ -1633,7 +1542,6 @@ mg_status autotune(mg_ctx *c, const double *u, const double *W, int reps, mg_tun
     if (c->cttk) cttk_update<T>(c, u, W);
     source_mean(c, u);
     residual<T>(c, u, W, false, nullptr, nullptr, nullptr, c->pr[0], c->pc[0], nullptr, false);
-    restrict_coefficients<T>(c);
     for (int l = 0; l < c->L; l++) {
         fill<T>(c->s, (T *)c->pd0[l], c->cells[l], T(0));
         if (l > 0) fill<T>(c->s, (T *)c->pr[l], c->cells[l], T(0));
@@ -1683,12 +1591,10 @@ mg_status autotune(mg_ctx *c, const double *u, const double *W, int reps, mg_tun
             on = cq != 0;
             if (q > 0) start = first + (q - 1);
             auto cycle = [&]() {
-                if (family == MG_TUNE_TAIL_PSI) {
-                    restrict_coefficients<T>(c);
+                if (family == MG_TUNE_TAIL_PSI)
                     vcycle_psi<T>(c, 0);
-                } else {
+                else
                     vcycle_W<T>(c, 0);
-                }
             };
             cycle();
             float ms = 0.0f;
@@ -1935,14 +1841,6 @@ bool same_group(const mg_params &a, const mg_params &b)
     return std::memcmp(&x, &y, offsetof(mg_params, mix_depth) + sizeof(x.mix_depth)) == 0;
 }
 
-// A group runs as one launch per kernel only if every kernel of its path takes the
-// member stride: the coarsest psi system must be solved by the Krylov kernels.
-bool groupable(const mg_params &p)
-{
-    const int nc = p.n >> (p.levels - 1);
-    return nc * nc * nc <= kKrylovMax;
-}
-
 struct BatchPlan {
     int ngroups;
     std::vector<int> gfirst, order, gof;
@@ -1969,7 +1867,6 @@ BatchPlan batch_plan(const mg_params *p, int count)
         pl.gfirst.push_back((int)pl.order.size());
         pl.gof[i] = g;
         pl.order.push_back(i);
-        if (!groupable(p[i])) continue;
         for (int j = i + 1; j < count; j++)
             if (pl.gof[j] < 0 && same_group(p[i], p[j])) {
                 pl.gof[j] = g;

@@ -910,27 +910,6 @@ __global__ void __launch_bounds__(kBlock) k_prolong_cubic_add_staged(Geo gc, con
 // pivoting, FP64, one workgroup), and x = A^-1 r as a column-major mat-vec.
 // ---------------------------------------------------------------------------------------
 
-// Row `row` of (L_h + c): A[row][col] accumulated over the 13 taps, boundary
-// rule included.  A is zeroed by the caller.
-template <int BC, typename T>
-__global__ void __launch_bounds__(kBlock) k_assemble_psi(Geo g, const T *c, double *A)
-{
-    const int n = g.n;
-    const int64_t m = (int64_t)n * n * n;
-    const int64_t row = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int i, j, k;
-    if (!cell_of(row, n, i, j, k)) return;
-    const double w[5] = {-1.0, 16.0, -30.0, 16.0, -1.0};
-    for (int ax = 0; ax < 3; ax++)
-        for (int d = -2; d <= 2; d++) {
-            int bi, bj, bk;
-            const double fac =
-                ghost_source<BC>(g, i + (ax == 0 ? d : 0), j + (ax == 1 ? d : 0), k + (ax == 2 ? d : 0), bi, bj, bk);
-            A[row * m + lidx(n, bi, bj, bk)] += w[d + 2] * g.inv12h2 * fac;
-        }
-    A[row * m + row] += (double)c[row];
-}
-
 // Rows of Delta_L,h on a periodic grid (3 n^3 unknowns) plus -(1/(n^3 h^2))
 // on every same-component entry, which fixes each component's mean to zero.
 __global__ void __launch_bounds__(kBlock) k_assemble_W(Geo g, double *A)
@@ -1119,31 +1098,10 @@ __global__ void __launch_bounds__(kBlock) k_coarse_apply(const double *Ainv, int
     }
 }
 
-// coarse = average of the 8 children of fine (coefficient restriction alone);
-// same summation order as the fused defect-restriction kernels.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_restrict(int nf, const T *__restrict__ fine, T *__restrict__ coarse, long long zs)
-{
-    fine = zsh(fine, zs);
-    coarse = zsh(coarse, zs);
-    const int nc = nf / 2;
-    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int I, J, K;
-    if (!cell_of(tid, nc, I, J, K)) return;
-    T s = T(0);
-#pragma unroll
-    for (int di = 0; di < 2; di++)
-#pragma unroll
-        for (int dj = 0; dj < 2; dj++)
-#pragma unroll
-            for (int dk = 0; dk < 2; dk++) s += fine[lidx(nf, 2 * I + di, 2 * J + dj, 2 * K + dk)];
-    coarse[tid] = s * T(0.125);
-}
-
 // ---------------------------------------------------------------------------------------
-// Coarsest psi solve (m = M unknowns, M <= 64, a compile-time constant that
-// fixes the number of columns each wave holds in registers): Gauss-Jordan with
-// partial pivoting on [A | r], A assembled from the level's stencil and c.
+// Coarsest psi solve of m <= 64 unknowns by elimination, where the Krylov solve below is not
+// accepted: Gauss-Jordan with partial pivoting on [A | r], A assembled from the level's
+// stencil and c (identity rows beyond m).
 // Pivot: the largest |a_ik| over unused rows, found with one wave max of a
 // packed key (float bits of |a_ik|, low 6 bits replaced by 63 - row so ties go
 // to the lowest row).  *flag = 1 if no non-zero pivot exists (published as
@@ -1196,9 +1154,65 @@ __device__ __forceinline__ double readlane_f64(double x, int l)
 // the true residual |r - A x| is below 1e-12 |r| afterwards; the caller otherwise
 // solves by elimination.
 //
+// ---------------------------------------------------------------------------------------
+// Padded arrays of (n + 4)^3 values in LDS: a level with the two ghost layers the boundary rule
+// gives, so that every tap is a fixed offset from its cell.  padded_store writes v to the cell
+// at word a and to its ghosts along the axes; gv: the ghost values of a cell on a face under the
+// Robin rule (padded_ghosts), first and second layer of each axis.
+template <int BC, typename T>
+__device__ __forceinline__ void padded_store(T *D, int a, int n, int i, int j, int k, T v, const T (&gv)[3][2])
+{
+    D[a] = v;
+    if constexpr (BC == kBcZero) return;
+    const int P = n + 4, pos[3] = {i, j, k}, st[3] = {P * P, P, 1};
+#pragma unroll
+    for (int ax = 0; ax < 3; ax++) {
+        const int p = pos[ax], s = st[ax];
+        if constexpr (BC == kBcPeriodic) {
+            if (p < 2) D[a + n * s] = v;
+            if (p >= n - 2) D[a - n * s] = v;
+        } else if constexpr (BC == kBcReflect) {
+            if (p < 2) D[a - (2 * p + 1) * s] = v;
+            if (p >= n - 2) D[a + (2 * (n - p) - 1) * s] = v;
+        } else {
+            if (p == 0 || p == n - 1) {
+                const int o = p == 0 ? -s : s;
+                D[a + o] = BC == kBcRobin ? gv[ax][0] : v;
+                D[a + 2 * o] = BC == kBcRobin ? gv[ax][1] : v;
+            }
+        }
+    }
+}
+
+// Ghost values of a cell with value v (Robin); gw: the level's weights.
+template <int BC, typename T>
+__device__ __forceinline__ void padded_ghosts(int n, const double *gw, int i, int j, int k, T v, T (&gv)[3][2])
+{
+    if constexpr (BC == kBcRobin) {
+        const int pos[3] = {i, j, k}, A[3] = {j, i, i}, B[3] = {k, k, j};
+        const int nn = n * n;
+#pragma unroll
+        for (int ax = 0; ax < 3; ax++)
+            if (pos[ax] == 0 || pos[ax] == n - 1) {
+                const double *w = gw + (2 * ax + (pos[ax] ? 1 : 0)) * 2 * nn + A[ax] * n + B[ax];
+                gv[ax][0] = (T)((double)v * w[0]);
+                gv[ax][1] = (T)((double)v * w[nn]);
+            }
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ T padded_lap(const T *D, int a, int P, T v)
+{
+    const int PP = P * P;
+    const T x = T(16) * (D[a - PP] + D[a + PP]) - (D[a - 2 * PP] + D[a + 2 * PP]) - T(30) * v;
+    const T y = T(16) * (D[a - P] + D[a + P]) - (D[a - 2 * P] + D[a + 2 * P]) - T(30) * v;
+    const T z = T(16) * (D[a - 1] + D[a + 1]) - (D[a - 2] + D[a + 2]) - T(30) * v;
+    return x + y + z;
+}
+
 // The 12 off-centre taps of L_h at a cell, as (source cell, weight) pairs with the
 // boundary rule folded in (ghost_source).  A tap may name the cell itself.
-// ---------------------------------------------------------------------------------------
 template <int BC>
 __device__ __forceinline__ void coarse_taps(const Geo &g, int q, int src[12], double w[12])
 {
@@ -1218,6 +1232,72 @@ __device__ __forceinline__ void coarse_taps(const Geo &g, int q, int src[12], do
             w[t] = wt[e] * g.inv12h2 * fac;
         }
 }
+
+// 1 / x to an ulp or two: the hardware estimate and two Newton steps (the coefficients of a
+// Krylov step, whose result is judged by its residual).
+__device__ __forceinline__ double quick_rcp(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+
+// The operator L_h + c of the cells first, first + stride, ... that a thread owns (E of them) on
+// a padded vector in LDS.
+template <int BC, int E>
+struct CoarseOp {
+    int i[E], j[E], k[E], a[E], n, m, first, stride;
+    double dg[E], w[E][BC == kBcRobin ? 3 : 1][2], inv12h2;
+    __device__ __forceinline__ bool own(int e) const { return first + stride * e < m; }
+    template <typename T>
+    __device__ __forceinline__ void init(const Geo &g, int m_, const T *c, int first_, int stride_)
+    {
+        n = g.n;
+        m = m_;
+        first = first_;
+        stride = stride_;
+        inv12h2 = g.inv12h2;
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            const int q = own(e) ? first + stride * e : 0;
+            k[e] = q % n;
+            j[e] = (q / n) % n;
+            i[e] = q / (n * n);
+            a[e] = ((i[e] + 2) * (n + 4) + j[e] + 2) * (n + 4) + k[e] + 2;
+            dg[e] = own(e) ? (double)c[q] : 0.0;
+            if constexpr (BC == kBcRobin) {
+                const int pos[3] = {i[e], j[e], k[e]}, A[3] = {j[e], i[e], i[e]}, B[3] = {k[e], k[e], j[e]};
+#pragma unroll
+                for (int ax = 0; ax < 3; ax++) {
+                    const double *t = g.gw + (2 * ax + (pos[ax] ? 1 : 0)) * 2 * n * n + A[ax] * n + B[ax];
+                    w[e][ax][0] = t[0];
+                    w[e][ax][1] = t[n * n];
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void put(double *vec, const double (&v)[E]) const
+    {
+#pragma unroll
+        for (int e = 0; e < E; e++)
+            if (own(e)) {
+                double gv[3][2];
+                if constexpr (BC == kBcRobin) {
+#pragma unroll
+                    for (int ax = 0; ax < 3; ax++) {
+                        gv[ax][0] = v[e] * w[e][ax][0];
+                        gv[ax][1] = v[e] * w[e][ax][1];
+                    }
+                }
+                padded_store<BC>(vec, a[e], n, i[e], j[e], k[e], v[e], gv);
+            }
+    }
+    __device__ __forceinline__ void get(const double *vec, const double (&v)[E], double (&y)[E]) const
+    {
+#pragma unroll
+        for (int e = 0; e < E; e++) y[e] = own(e) ? padded_lap(vec, a[e], n + 4, v[e]) * inv12h2 + dg[e] * v[e] : 0.0;
+    }
+};
 
 // One 64-bit DPP lane move (both halves with the same control).
 template <int CTRL>
@@ -1240,104 +1320,157 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
     return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
-// One wave, one cell per lane (M <= 64 cells); lanes >= M carry zeros.  Needs no
-// barrier: the taps come from the owning lanes by cross-lane permutes.  Writes x and
-// returns true when accepted.
-template <int BC, typename T, int M>
-__device__ __forceinline__ bool coarse_psi_krylov_wave(const Geo &g, const T *c, const T *r, T *x)
+// One wave, E cells per lane (m <= 64 E; cell lane + 64 e).  Needs no block barrier: the vector
+// being multiplied passes through LDS (vec, m values), whose accesses a wave makes in order.
+// A step is a chain of latencies (LDS round, sums, reduction, division), so the reductions are
+// merged: conjugate gradients in the single-reduction form of Chronopoulos and Gear, whose
+// <r, r> hides behind the operator, and BiCGSTAB with three reduction points a step.  Writes x
+// and returns true when accepted.
+template <int BC, typename T, int E>
+__device__ __forceinline__ bool coarse_psi_krylov_wave(const Geo &g, int m, const T *c, const T *r, T *x, double *vec)
 {
-    static_assert(M <= kWave, "one cell per lane");
     const int lane = threadIdx.x & (kWave - 1);
-    const bool own = lane < M;
-    int src[12];
-    double w[12];
-    if (own) {
-        coarse_taps<BC>(g, lane, src, w);
-    } else {
+    int src[E][12];
+    double w[E][12], dg[E], b[E];
 #pragma unroll
-        for (int t = 0; t < 12; t++) {
-            src[t] = lane;
-            w[t] = 0.0;
-        }
+    for (int e = 0; e < E; e++) {
+        const int q = lane + kWave * e < m ? lane + kWave * e : 0;
+        const bool own = lane + kWave * e < m;
+        coarse_taps<BC>(g, q, src[e], w[e]);
+        dg[e] = own ? -90.0 * g.inv12h2 + (double)c[q] : 0.0;
+        b[e] = own ? (double)r[q] : 0.0;
     }
-    const double cq = own ? (double)c[lane] : 0.0;
-    const double dg = own ? -90.0 * g.inv12h2 + cq : 0.0;
-    auto apply = [&](double v) {
-        double y = dg * v;
+    auto apply = [&](const double (&v)[E], double (&y)[E]) {
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int t = 0; t < 12; t++) y += w[t] * __shfl(v, src[t], kWave);
-        return y;
+        for (int e = 0; e < E; e++)
+            if (lane + kWave * e < m) vec[lane + kWave * e] = v[e];
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            double t[12], s[3];
+#pragma unroll
+            for (int k = 0; k < 12; k++) t[k] = vec[src[e][k]];
+#pragma unroll
+            for (int ax = 0; ax < 3; ax++) {
+                if constexpr (BC == kBcPeriodic)
+                    s[ax] = 16.0 * (t[4 * ax + 1] + t[4 * ax + 2]) - (t[4 * ax] + t[4 * ax + 3]);
+                else
+                    s[ax] = (w[e][4 * ax + 1] * t[4 * ax + 1] + w[e][4 * ax + 2] * t[4 * ax + 2]) +
+                            (w[e][4 * ax] * t[4 * ax] + w[e][4 * ax + 3] * t[4 * ax + 3]);
+            }
+            const double o = s[0] + s[1] + s[2];
+            y[e] = lane + kWave * e < m ? (BC == kBcPeriodic ? o * g.inv12h2 : o) + dg[e] * v[e] : 0.0;
+        }
+        asm volatile("" ::: "memory");
     };
-    const double b = own ? (double)r[lane] : 0.0;
-    const double bb = wave_sum_dpp(b * b);
+    auto part = [&](const double (&u)[E], const double (&v)[E]) {
+        double s = u[0] * v[0];
+#pragma unroll
+        for (int e = 1; e < E; e++) s += u[e] * v[e];
+        return s;
+    };
+    auto dot = [&](const double (&u)[E], const double (&v)[E]) { return wave_sum_dpp(part(u, v)); };
+    auto write = [&](const double (&v)[E]) {
+#pragma unroll
+        for (int e = 0; e < E; e++)
+            if (lane + kWave * e < m) x[lane + kWave * e] = (T)v[e];
+    };
+    const double bb = dot(b, b);
+    double xv[E], rr[E], p[E], y[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        xv[e] = 0.0;
+        rr[e] = b[e];
+    }
     if (!(bb > 0.0)) {
-        if (own) x[lane] = T(0);
+        write(xv);
         return bb == 0.0;
     }
     const double tol2 = 1e-28 * bb;
-    double xv = 0.0;
     bool ok = false;
     if constexpr (BC == kBcPeriodic) {
-        // conjugate gradients end within M steps in exact arithmetic; a system that needs
-        // many more is ill-conditioned or indefinite, and elimination is then quicker
-        double rr = b, p = b, rz = bb;
+        // conjugate gradients end within m steps in exact arithmetic; where elimination can
+        // follow (m <= 64), it is quicker than many more steps
+        const int most = m <= kWave ? m + 16 : 2 * m + 32;
+        double s[E], gamma = bb, beta = 0.0, corr = 0.0; // corr = beta gamma / alpha of the step before
+#pragma unroll
+        for (int e = 0; e < E; e++) p[e] = s[e] = 0.0;
 #pragma unroll 1
-        for (int it = 0; it < M + 16; it++) {
-            const double ap = apply(p);
-            const double pap = wave_sum_dpp(p * ap);
-            if (!(pap != 0.0)) break;
-            const double alpha = rz / pap;
-            xv += alpha * p;
-            rr -= alpha * ap;
-            const double rz1 = wave_sum_dpp(rr * rr);
-            if (rz1 <= tol2) {
+        for (int it = 0; it < most; it++) {
+            apply(rr, y);
+            const double den = dot(rr, y) - corr;
+            if (!(den != 0.0)) break;
+            const double alpha = gamma * quick_rcp(den);
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                p[e] = rr[e] + beta * p[e];
+                s[e] = y[e] + beta * s[e];
+                xv[e] += alpha * p[e];
+                rr[e] -= alpha * s[e];
+            }
+            const double g1 = dot(rr, rr);
+            if (g1 <= tol2) {
                 ok = true;
                 break;
             }
-            p = rr + (rz1 / rz) * p;
-            rz = rz1;
+            beta = g1 * quick_rcp(gamma);
+            corr = beta * g1 * quick_rcp(alpha);
+            gamma = g1;
         }
     } else {
-        double rr = b, rh = b, p = 0.0, v = 0.0, rho = 1.0, alpha = 1.0, omega = 1.0;
+        double v[E], sv[E], rho = 1.0, alpha = 1.0, omega = 1.0, rho1 = bb;
+#pragma unroll
+        for (int e = 0; e < E; e++) p[e] = v[e] = 0.0;
 #pragma unroll 1
-        for (int it = 0; it < 4 * M + 32; it++) {
-            const double rho1 = wave_sum_dpp(rh * rr);
+        for (int it = 0; it < 4 * m + 32; it++) {
             if (!(rho1 != 0.0)) break;
-            p = rr + (rho1 / rho) * (alpha / omega) * (p - omega * v);
-            v = apply(p);
-            const double rv = wave_sum_dpp(rh * v);
+            const double beta = (rho1 * quick_rcp(rho)) * (alpha * quick_rcp(omega));
+#pragma unroll
+            for (int e = 0; e < E; e++) p[e] = rr[e] + beta * (p[e] - omega * v[e]);
+            apply(p, v);
+            const double rv = dot(b, v);
             if (!(rv != 0.0)) break;
-            alpha = rho1 / rv;
-            const double sv = rr - alpha * v;
-            if (wave_sum_dpp(sv * sv) <= tol2) {
-                xv += alpha * p;
+            alpha = rho1 * quick_rcp(rv);
+#pragma unroll
+            for (int e = 0; e < E; e++) sv[e] = rr[e] - alpha * v[e];
+            const double ss = dot(sv, sv);
+            apply(sv, y);
+            const double ts = dot(y, sv), tt = dot(y, y);
+            if (ss <= tol2) {
+#pragma unroll
+                for (int e = 0; e < E; e++) xv[e] += alpha * p[e];
                 ok = true;
                 break;
             }
-            const double t = apply(sv);
-            const double ts = wave_sum_dpp(t * sv), tt = wave_sum_dpp(t * t);
             if (!(tt > 0.0)) break;
-            omega = ts / tt;
-            xv += alpha * p + omega * sv;
-            rr = sv - omega * t;
+            omega = ts * quick_rcp(tt);
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                xv[e] += alpha * p[e] + omega * sv[e];
+                rr[e] = sv[e] - omega * y[e];
+            }
             rho = rho1;
-            if (wave_sum_dpp(rr * rr) <= tol2) {
+            const double rr2 = dot(rr, rr);
+            rho1 = dot(b, rr);
+            if (rr2 <= tol2) {
                 ok = true;
                 break;
             }
             if (!(omega != 0.0)) break;
         }
     }
-    const double tr = b - apply(xv);
-    const double trr = wave_sum_dpp(tr * tr);
-    ok = ok && trr <= 1e-24 * bb;
-    if (ok && own) x[lane] = (T)xv;
+    apply(xv, y);
+#pragma unroll
+    for (int e = 0; e < E; e++) y[e] = b[e] - y[e];
+    ok = ok && dot(y, y) <= 1e-24 * bb;
+    if (ok) write(xv);
     return ok;
 }
 
 // The same for up to kGjWaves * kWave * CPT cells on a block of kGjWaves waves: every
 // thread owns CPT cells (q = tid + kGjWaves * kWave * e), the vector being multiplied
-// is staged in LDS, and inner products are block reductions.  Writes x and returns
+// is staged in LDS (padded), and inner products are block reductions.  Writes x and returns
 // true (in every thread) when accepted; called by every thread of the block.
 constexpr int kKrylovCpt = 2;
 constexpr int kKrylovMax = kGjWaves * kWave * kKrylovCpt;
@@ -1364,46 +1497,23 @@ __device__ __forceinline__ void block_sums(double v[NV], double (*part)[kGjWaves
 }
 
 template <int BC, typename T>
-__device__ __forceinline__ bool coarse_psi_krylov_block(const Geo &g, int m, const T *c, const T *r, T *x)
+__device__ __forceinline__ bool coarse_psi_krylov_block(const Geo &g, int m, const T *c, const T *r, T *x, double *vec,
+                                                        double (*part)[kGjWaves])
 {
     constexpr int E = kKrylovCpt;
     constexpr int NT = kGjWaves * kWave;
-    __shared__ double vec[kKrylovMax];
-    __shared__ double part[3][kGjWaves];
-    int src[E][12];
-    double w[E][12], dg[E], b[E];
+    CoarseOp<BC, E> op;
+    op.init(g, m, c, threadIdx.x, NT);
+    for (int t = threadIdx.x; t < (g.n + 4) * (g.n + 4) * (g.n + 4); t += NT) vec[t] = 0.0;
+    double b[E];
 #pragma unroll
-    for (int e = 0; e < E; e++) {
-        const int q = threadIdx.x + NT * e;
-        if (q < m) {
-            coarse_taps<BC>(g, q, src[e], w[e]);
-            dg[e] = -90.0 * g.inv12h2 + (double)c[q];
-            b[e] = (double)r[q];
-        } else {
-#pragma unroll
-            for (int t = 0; t < 12; t++) {
-                src[e][t] = 0;
-                w[e][t] = 0.0;
-            }
-            dg[e] = 0.0;
-            b[e] = 0.0;
-        }
-    }
-    // y = A v for the owned cells (v staged in LDS by every thread first)
-    auto apply = [&](const double v[E], double y[E]) {
-#pragma unroll
-        for (int e = 0; e < E; e++) {
-            const int q = threadIdx.x + NT * e;
-            if (q < m) vec[q] = v[e];
-        }
+    for (int e = 0; e < E; e++) b[e] = op.own(e) ? (double)r[threadIdx.x + NT * e] : 0.0;
+    __syncthreads();
+    // y = A v for the owned cells
+    auto apply = [&](const double (&v)[E], double (&y)[E]) {
+        op.put(vec, v);
         __syncthreads();
-#pragma unroll
-        for (int e = 0; e < E; e++) {
-            double s = dg[e] * v[e];
-#pragma unroll
-            for (int t = 0; t < 12; t++) s += w[e][t] * vec[src[e][t]];
-            y[e] = s;
-        }
+        op.get(vec, v, y);
         __syncthreads();
     };
     double t3[3];
@@ -1540,45 +1650,43 @@ __device__ __forceinline__ bool coarse_psi_krylov_block(const Geo &g, int m, con
     return ok;
 }
 
-// Coarsest psi levels of more than 64 cells: the block Krylov solve; a system it
-// does not solve raises the singular flag.
-template <int BC, typename T>
-__global__ void __launch_bounds__(kGjWaves *kWave) k_coarse_psi_krylov(Geo g, int m, const T *c, const T *r, T *x,
-                                                                      double *flag)
-{
-    c = zsh(c, g.zs);
-    r = zsh(r, g.zs);
-    x = zsh(x, g.zs);
-    flag = zsh(flag, g.zs);
-    const bool ok = coarse_psi_krylov_block<BC, T>(g, m, c, r, x);
-    if (!ok && threadIdx.x == 0) *flag = 1.0;
-}
+constexpr int kPaddedCoarse = 16 * 16 * 16; // coarsest psi levels hold at most 12^3 cells
+// LDS of the coarsest solve.
+struct CoarseScratch {
+    union {
+        struct {
+            double vec[kPaddedCoarse], part[3][kGjWaves];
+        } kr;
+        struct {
+            double A[kWave][kWave + 2], fac[2][kWave], pdiag[kWave];
+            int piv[2], perm[kWave];
+        } gj;
+    };
+    int ok;
+};
 
-// Called by every thread of a block of kGjWaves waves.
-template <int BC, typename T, int M>
-__device__ __forceinline__ void coarse_psi_block_solve(const Geo &g, const T *c, const T *r, T *x, double *flag)
+// Elimination of a system of m <= 64 unknowns; called by every thread of a block of kGjWaves
+// waves.
+template <int BC, typename T>
+__device__ __forceinline__ void coarse_psi_eliminate(const Geo &g, int m, const T *c, const T *r, T *x, double *flag,
+                                                     CoarseScratch &cs)
 {
-    constexpr int NC = M + 1;
+    constexpr int M = kWave, NC = M + 1;
     constexpr int S = (NC + kGjWaves - 1) / kGjWaves;
-    __shared__ double A[M][NC + 1];
-    __shared__ double fac[2][kWave];
-    __shared__ int piv[2];
-    __shared__ int perm[M];
-    __shared__ double pdiag[M];
-    __shared__ int krylov_ok;
+    auto &A = cs.gj.A;
+    auto &fac = cs.gj.fac;
+    auto &pdiag = cs.gj.pdiag;
+    auto &piv = cs.gj.piv;
+    auto &perm = cs.gj.perm;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int n = g.n;
-    // first the Krylov solve on wave 0 alone; elimination only if it is not accepted
-    if (wave == 0) {
-        const bool ok = coarse_psi_krylov_wave<BC, T, M>(g, c, r, x);
-        if (lane == 0) krylov_ok = ok ? 1 : 0;
-    }
-    __syncthreads();
-    if (krylov_ok) return;
     if (threadIdx.x < M) {
         const int row = threadIdx.x;
-        for (int j = 0; j < NC; j++) A[row][j] = 0.0;
+        for (int j = 0; j < NC; j++) A[row][j] = row >= m && j == row ? 1.0 : 0.0;
+    }
+    if ((int)threadIdx.x < m) {
+        const int row = threadIdx.x;
         const int k = row % n, j = (row / n) % n, i = row / (n * n);
         const double wt[5] = {-1.0, 16.0, -30.0, 16.0, -1.0};
         for (int ax = 0; ax < 3; ax++)
@@ -1657,219 +1765,66 @@ __device__ __forceinline__ void coarse_psi_block_solve(const Geo &g, const T *c,
     for (int q = 0; q < S; q++)
         if (wave + kGjWaves * q == M && lane < M) A[lane][M] = v[q];
     __syncthreads();
-    if (threadIdx.x < M) x[threadIdx.x] = (T)(A[perm[threadIdx.x]][M] / pdiag[threadIdx.x]);
+    if ((int)threadIdx.x < m) x[threadIdx.x] = (T)(A[perm[threadIdx.x]][M] / pdiag[threadIdx.x]);
 }
 
-template <int BC, typename T, int M>
-__global__ void __launch_bounds__(kGjWaves * kWave) k_coarse_psi_block(Geo g, const T *c, const T *r, T *x,
-                                                                      double *flag)
+// (L_h + c) x = r on the coarsest level (m <= kKrylovMax cells): up to 128 cells on one wave,
+// which needs no barrier between its steps (125 cells: 58 us as a block of 16 waves); a system
+// the Krylov solve does not accept is eliminated (m <= 64) or raises the flag.  x keeps its
+// values when the flag is raised.  Called by every thread of a block of kGjWaves waves.
+template <int BC, typename T>
+__device__ __forceinline__ void coarse_psi_solve(const Geo &g, int m, const T *c, const T *r, T *x, double *flag,
+                                                 CoarseScratch &cs)
 {
+    if (m <= 2 * kWave) {
+        if (threadIdx.x < kWave) {
+            const bool ok = m <= kWave ? coarse_psi_krylov_wave<BC, T, 1>(g, m, c, r, x, cs.kr.vec)
+                                       : coarse_psi_krylov_wave<BC, T, 2>(g, m, c, r, x, cs.kr.vec);
+            if (threadIdx.x == 0) cs.ok = ok ? 1 : 0;
+        }
+        __syncthreads();
+        if (cs.ok) return;
+        if (m <= kWave) {
+            coarse_psi_eliminate<BC, T>(g, m, c, r, x, flag, cs);
+            return;
+        }
+    }
+    if (!coarse_psi_krylov_block<BC, T>(g, m, c, r, x, cs.kr.vec, cs.kr.part) && threadIdx.x == 0) *flag = 1.0;
+}
+
+template <int BC, typename T>
+__global__ void __launch_bounds__(kGjWaves *kWave) k_coarse_psi(Geo g, int m, const T *c, const T *r, T *x, double *flag)
+{
+    __shared__ CoarseScratch cs;
     c = zsh(c, g.zs);
     r = zsh(r, g.zs);
     x = zsh(x, g.zs);
     flag = zsh(flag, g.zs);
-    coarse_psi_block_solve<BC, T, M>(g, c, r, x, flag);
+    coarse_psi_solve<BC, T>(g, m, c, r, x, flag, cs);
 }
 
 // ---------------------------------------------------------------------------------------
-// V-cycle tails: the coarse levels of one V-cycle (from level ls down to the
-// coarsest and back) run in one workgroup of kGjWaves waves, phase by phase
-// with block barriers, on arrays resident in LDS (these levels are too small
-// to fill the GPU: as separate launches every phase would cost a launch).
-// The tail reads its first level's right-hand side (and psi coefficient) from
-// global memory, keeps every level's corrections, right-hand sides and
-// coefficients in LDS, and writes its first level's correction back.  Each
-// phase calls the same per-cell functions as the grid kernels.
+// W V-cycle tail: the coarse levels of one V-cycle (from its first level down to the coarsest
+// and back) in one workgroup of kGjWaves waves, phase by phase with block barriers, on arrays
+// resident in LDS.  It reads its first level's right-hand side from global memory and writes
+// that level's correction back.  A W colour pass of more than 12^3 cells takes longer on one CU
+// than as a grid launch, so a tail's levels hold at most kTailW cells.
 // ---------------------------------------------------------------------------------------
 constexpr int kTailThreads = kGjWaves * kWave;
 constexpr int kMaxTail = 4;
-
-// Cells of a tail summed over its levels: psi keeps d, r and c of every level
-// in LDS, W d and r of three components (the passes update in place).  One
-// workgroup runs a whole level per phase, so a tail pays off only while its
-// first level is small: a W colour pass over 16^3 cells takes longer on one
-// CU than as a grid launch, a psi pass (13 taps) does not.
-template <typename T>
-struct TailCap {
-    static constexpr int kPsi = sizeof(T) == 4 ? 4680 : 1971; // 16^3 + 8^3 + 4^3 + 2^3 ; 12^3 + 6^3 + 3^3
-    static constexpr int kPsiRobin = 1971;
-    static constexpr int kW = 1971;
-};
+constexpr int kTailW = 1971; // 12^3 + 6^3 + 3^3
 
 template <typename T>
 struct TailArgs {
-    int nl;      // levels in the tail (the last one is the coarsest)
+    int nl; // levels in the tail (the last one is the coarsest)
     int nu_pre, nu_post;
     Geo geo[kMaxTail];
-    const T *r0, *c0; // first level: right-hand side (3 components for W), psi coefficient
-    T *d0;            // first level: the correction (output)
-    const double *inv; // W: coarsest inverse (column-major m x m), m = 3 cells
-    double *flag;      // psi: set when the coarsest matrix is singular
+    const T *r0;       // first level: right-hand side (3 components)
+    T *d0;             // first level: the correction (output)
+    const double *inv; // coarsest inverse (column-major m x m), m = 3 cells
 };
 
 __device__ __forceinline__ int tail_cells(const Geo &g) { return g.n * g.n * g.n; }
-
-// New value of an active cell of a psi colour pass (the arithmetic of the
-// grid pass kernels: k_pass_psi_pairs when periodic, psi_pass_cell otherwise).
-template <int BC, typename T>
-__device__ __forceinline__ T psi_new_value(const Geo &g, const T *in, const T *r, const T *c, unsigned q, int i,
-                                           int j, int k)
-{
-    if constexpr (BC == kBcPeriodic) {
-        const WrapOff o(g.n, i, j, k);
-        RegTaps<T, false> D;
-        D.get_lap(WrapTaps<T>{in, o});
-        const T v = D.c(), cv = c[q];
-        const T Ad = (D.dxx(v) + D.dyy(v) + D.dzz(v)) * (T)g.inv12h2 + cv * v;
-        const T diag = pinned((T)(-90.0 * g.inv12h2)) + cv;
-        return v + (r[q] - Ad) / diag;
-    } else {
-        Acc<BC, T> D{in, g};
-        const T x = in[q], cv = c[q];
-        const T Ad = lap_sum<T>(D, i, j, k, x) * (T)g.inv12h2 + cv * x;
-        const T diag = pinned((T)(lap_diag_sum<BC>(g, i, j, k) * g.inv12h2)) + cv;
-        return x + (r[q] - Ad) / diag;
-    }
-}
-
-// Active cells of a psi tail pass per thread: half the cells of a first level
-// of at most 16^3 (periodic) or 12^3 (Robin: its ghost-cell taps need the
-// registers of a second item).
-template <int BC>
-constexpr int tail_psi_items()
-{
-    return BC == kBcPeriodic ? 2 : 1;
-}
-
-// One colour pass of the psi smoother on an LDS-resident level, in place: the
-// active cells' new values are formed from d into registers, the block waits,
-// then they are written (the double-buffered pass's values).
-template <int BC, typename T>
-__device__ __forceinline__ void tail_psi_pass(const Geo &g, T *d, const T *r, const T *c, int colour)
-{
-    const int n = g.n, np = n >> 1, half = (n * n * n) >> 1;
-    constexpr int NI = tail_psi_items<BC>();
-    T val[NI];
-    unsigned dst[NI];
-#pragma unroll
-    for (int s = 0; s < NI; s++) {
-        const int it = (int)threadIdx.x + s * kTailThreads;
-        dst[s] = ~0u;
-        val[s] = T(0);
-        if (it < half) {
-            const int row = it / np, kp = it - row * np, i = row / n, j = row - i * n;
-            const int k = 2 * kp + ((i + j + colour) & 1);
-            const unsigned q = (unsigned)((i * n + j) * n + k);
-            val[s] = psi_new_value<BC, T>(g, d, r, c, q, i, j, k);
-            dst[s] = q;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < NI; s++)
-        if (dst[s] != ~0u) d[dst[s]] = val[s];
-    __syncthreads();
-}
-
-// psi tail: restricts c below its first level, then the V-cycle from the
-// tail's first level.  LDS: per level d | r | c, levels consecutive.
-template <int BC, typename T, int M>
-__global__ void __launch_bounds__(kTailThreads) k_tail_psi(TailArgs<T> a)
-{
-    {
-        const long long zs = a.geo[0].zs;
-        a.r0 = zsh(a.r0, zs);
-        a.c0 = zsh(a.c0, zs);
-        a.d0 = zsh(a.d0, zs);
-        a.inv = zsh(a.inv, zs);
-        a.flag = zsh(a.flag, zs);
-    }
-    __shared__ T buf[3 * TailCap<T>::kPsi];
-    const int L = a.nl;
-    int off[kMaxTail] = {0, 0, 0, 0};
-    {
-        int o = 0;
-        for (int l = 0; l < L && l < kMaxTail; l++) {
-            off[l] = o;
-            o += 3 * tail_cells(a.geo[l]);
-        }
-        if (L < 2 || L > kMaxTail || o > 3 * TailCap<T>::kPsi ||
-            tail_cells(a.geo[0]) / 2 > tail_psi_items<BC>() * kTailThreads)
-            return; // the host picks tails that fit
-    }
-    auto D = [&](int l) { return buf + off[l]; };
-    auto R = [&](int l) { return buf + off[l] + tail_cells(a.geo[l]); };
-    auto C = [&](int l) { return buf + off[l] + 2 * tail_cells(a.geo[l]); };
-    {
-        const int m0 = tail_cells(a.geo[0]);
-        T *r0 = R(0), *c0 = C(0);
-        for (int q = threadIdx.x; q < m0; q += kTailThreads) {
-            r0[q] = a.r0[q];
-            c0[q] = a.c0[q];
-        }
-    }
-    __syncthreads();
-    for (int l = 0; l + 1 < L; l++) {
-        const int nf = a.geo[l].n, nc = a.geo[l + 1].n, mc = tail_cells(a.geo[l + 1]);
-        const T *cf = C(l);
-        T *cc = C(l + 1);
-        for (int q = threadIdx.x; q < mc; q += kTailThreads) {
-            int I, J, K;
-            cell_of(q, nc, I, J, K);
-            T s = T(0);
-#pragma unroll
-            for (int di = 0; di < 2; di++)
-#pragma unroll
-                for (int dj = 0; dj < 2; dj++)
-#pragma unroll
-                    for (int dk = 0; dk < 2; dk++) s += cf[lidx(nf, 2 * I + di, 2 * J + dj, 2 * K + dk)];
-            cc[q] = s * T(0.125);
-        }
-        __syncthreads();
-    }
-    for (int l = 0; l + 1 < L; l++) {
-        const Geo &g = a.geo[l];
-        const int mf = tail_cells(g);
-        T *d = D(l);
-        for (int q = threadIdx.x; q < mf; q += kTailThreads) d[q] = T(0);
-        __syncthreads();
-        for (int s = 0; s < a.nu_pre; s++) {
-            tail_psi_pass<BC, T>(g, D(l), R(l), C(l), 0);
-            tail_psi_pass<BC, T>(g, D(l), R(l), C(l), 1);
-        }
-        for (int q = threadIdx.x; q < mf + (kTailThreads - 1); q += kTailThreads) {
-            if (q - (int)threadIdx.x >= mf) break; // the whole block leaves together
-            defect_restrict_psi_child<BC, T>(g, D(l), R(l), C(l), R(l + 1), (T *)nullptr, q);
-        }
-        __syncthreads();
-    }
-    {
-        const int mc = tail_cells(a.geo[L - 1]);
-        T *x = D(L - 1);
-        for (int q = threadIdx.x; q < mc; q += kTailThreads) x[q] = T(0); // stays 0 if singular
-        __syncthreads();
-        coarse_psi_block_solve<BC, T, M>(a.geo[L - 1], C(L - 1), R(L - 1), x, a.flag);
-        __syncthreads();
-    }
-    for (int l = L - 2; l >= 0; l--) {
-        const int nf = a.geo[l].n, mf = tail_cells(a.geo[l]);
-        for (int q = threadIdx.x; q < mf; q += kTailThreads) {
-            int i, j, k;
-            cell_of(q, nf, i, j, k);
-            prolong_cell<BC, T>(a.geo[l + 1], D(l + 1), D(l), 1, q, i, j, k);
-        }
-        __syncthreads();
-        for (int s = 0; s < a.nu_post; s++) {
-            tail_psi_pass<BC, T>(a.geo[l], D(l), R(l), C(l), 0);
-            tail_psi_pass<BC, T>(a.geo[l], D(l), R(l), C(l), 1);
-        }
-    }
-    {
-        const int m0 = tail_cells(a.geo[0]);
-        const T *d0 = D(0);
-        for (int q = threadIdx.x; q < m0; q += kTailThreads) a.d0[q] = d0[q];
-    }
-}
 
 // (Delta_L d)_A at a cell from wrapped offsets, component A alone: the terms
 // W_field_parts forms for that component, in the same order.  centre: d_A at
@@ -1906,7 +1861,7 @@ __device__ __forceinline__ T deltaL_comp(const T *d, unsigned m, const WrapOff &
 }
 
 // Work items of a W tail pass: three components of half the cells of a first
-// level of at most TailCap<T>::kW cells in all (12^3).
+// level of at most kTailW cells in all (12^3).
 constexpr int kTailWStage = 3 * 1728 / 2;
 
 // One colour pass of the W smoother on an LDS-resident level, in place: the
@@ -1965,12 +1920,10 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_W(TailArgs<T> a)
     {
         const long long zs = a.geo[0].zs;
         a.r0 = zsh(a.r0, zs);
-        a.c0 = zsh(a.c0, zs);
         a.d0 = zsh(a.d0, zs);
         a.inv = zsh(a.inv, zs);
-        a.flag = zsh(a.flag, zs);
     }
-    __shared__ T buf[6 * TailCap<T>::kW];
+    __shared__ T buf[6 * kTailW];
     __shared__ T stage[kTailWStage];
     __shared__ double rs[1536];
     __shared__ double red[kTailThreads / kWave][kWave];
@@ -1983,7 +1936,7 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_W(TailArgs<T> a)
             off[l] = o;
             o += 6 * tail_cells(a.geo[l]);
         }
-        if (L < 2 || L > kMaxTail || o > 6 * TailCap<T>::kW || 3 * tail_cells(a.geo[0]) / 2 > kTailWStage ||
+        if (L < 2 || L > kMaxTail || o > 6 * kTailW || 3 * tail_cells(a.geo[0]) / 2 > kTailWStage ||
             3 * tail_cells(a.geo[L - 1]) > 1536)
             return; // the host picks tails that fit
     }
