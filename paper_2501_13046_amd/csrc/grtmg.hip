@@ -2813,9 +2813,11 @@ mg_status refine_check_all(int L, const mg_params *const *p, const int32_t *b0)
 }
 
 // Workspace: per level its residual field, the old values (all but the finest) and
-// the FAS forcing of intermediate levels, then the norm partials and result.
+// the FAS forcing of intermediate levels, then a box's interface ghosts, the norm partials
+// and the result.
 struct RefineWork {
     double *H[kMaxRefineLevels], *old[kMaxRefineLevels], *tau[kMaxRefineLevels];
+    double *ghosts; // of the box being forced (two layers of six faces)
     double *part, *res;
     size_t bytes;
 };
@@ -2831,31 +2833,51 @@ RefineWork refine_layout(int L, const mg_params *const *p, char *base)
         if (k + 1 < L) w.old[k] = (double *)cv.take(bytes);
         if (k > 0 && k + 1 < L) w.tau[k] = (double *)cv.take(bytes);
     }
+    size_t face = 0;
+    for (int k = 1; k < L; k++) face = std::max(face, (size_t)p[k]->n * p[k]->n);
+    w.ghosts = (double *)cv.take(12 * face * sizeof(double));
     w.part = (double *)cv.take(2 * (size_t)L * kSrcBlocks * sizeof(double));
     w.res = (double *)cv.take(2 * sizeof(double));
     w.bytes = align_up(cv.off, 256);
     return w;
 }
 
-// One Newton-multigrid step of eq. Ham on a context, on its own stream (ordered
-// after and before the caller's stream).
+// One Newton-multigrid step of eq. Ham on a context.
 void psi_step(mg_ctx *c, double *u)
 {
-    enter(c);
     if (c->f32)
         step_psi<float>(c, u, nullptr, false);
     else
         step_psi<double>(c, u, nullptr, false);
-    leave(c);
 }
 
 // H_h of a context at u (its forcing included) into H.
 void residual_field(mg_ctx *c, const double *u, double *H)
 {
-    enter(c);
     residual<double>(c, u, nullptr, false, H, nullptr, nullptr, nullptr, nullptr, nullptr, false);
-    leave(c);
 }
+
+// The contexts of a composite solve on the base context's stream, ordered after the work on
+// the caller's stream; given back, and the caller's stream ordered after it, on every way out.
+// (With each step on its own context's stream every step waited for two stream events.)
+struct OneStream {
+    int L;
+    mg_ctx *const *c;
+    hipStream_t own[kMaxRefineLevels];
+    OneStream(int levels, mg_ctx *const *ctx) : L(levels), c(ctx)
+    {
+        enter(c[0]);
+        for (int k = 0; k < L; k++) {
+            own[k] = c[k]->s;
+            c[k]->s = c[0]->s;
+        }
+    }
+    ~OneStream()
+    {
+        leave(c[0]);
+        for (int k = 0; k < L; k++) c[k]->s = own[k];
+    }
+};
 
 mg_status refine_solve(int L, mg_ctx *const *c, const int32_t *b0, double *const *u, void *d_work, size_t work_bytes,
                        double tol, int max_outer, int nu_box, int nu_base, mg_report *rep)
@@ -2877,7 +2899,8 @@ mg_status refine_solve(int L, mg_ctx *const *c, const int32_t *b0, double *const
     const RefineWork w = refine_layout(L, p, (char *)d_work);
     if (!d_work || work_bytes < w.bytes || ((uintptr_t)d_work % 256) != 0) return MG_ERR_WORKSPACE;
     auto t0 = std::chrono::steady_clock::now();
-    const hipStream_t s = c[0]->user_s;
+    const OneStream one(L, c);
+    const hipStream_t s = c[0]->s;
     BoxGeo bx[kMaxRefineLevels]; // bx[k]: level k as the box of level k - 1
     int64_t cells[kMaxRefineLevels];
     double *f[kMaxRefineLevels], vol[kMaxRefineLevels];
@@ -2899,11 +2922,14 @@ mg_status refine_solve(int L, mg_ctx *const *c, const int32_t *b0, double *const
     // the forcing of level k: interface ghosts from its parent (+ its FAS forcing);
     // the base level: its FAS forcing or zero
     auto forcing = [&](int k, const double *tau) {
-        if (k > 0)
+        if (k > 0) {
+            hipLaunchKernelGGL(k_box_ghosts, dim3(nblk((int64_t)p[k]->n * p[k]->n), 6), dim3(kBlock), 0, s, bx[k],
+                               (const double *)u[k - 1], w.ghosts);
             hipLaunchKernelGGL(k_box_ghost_forcing, dim3(nblk(cells[k])), dim3(kBlock), 0, s, bx[k],
-                               c[k]->geo[0].inv12h2, (const double *)u[k - 1], tau, f[k]);
-        else
+                               c[k]->geo[0].inv12h2, (const double *)w.ghosts, tau, f[k]);
+        } else {
             fill<double>(s, f[0], cells[0], 0.0);
+        }
     };
     const unsigned nbn = kSrcBlocks;
     mg_status st = MG_ERR_NOT_CONVERGED;
@@ -2912,17 +2938,18 @@ mg_status refine_solve(int L, mg_ctx *const *c, const int32_t *b0, double *const
     for (;; it++) {
         // composite norm of the synchronised state
         for (int k = L - 1; k > 0; k--) to_parent(k);
+        int64_t parts = 0;
         for (int k = 0; k < L; k++) {
             forcing(k, nullptr);
             residual_field(c[k], u[k], w.H[k]);
             const BoxGeo child = k + 1 < L ? bx[k + 1] : BoxGeo{0, 0, 0};
             const unsigned nb = std::min<unsigned>(nblk(cells[k]), nbn);
-            fill<double>(s, w.part + 2 * (size_t)k * nbn, 2 * (int64_t)nbn, 0.0);
             hipLaunchKernelGGL(k_level_norm, dim3(nb), dim3(kBlock), 0, s, p[k]->n, child, vol[k],
-                               (const double *)w.H[k], w.part + 2 * (size_t)k * nbn);
+                               (const double *)w.H[k], w.part + 2 * parts);
+            parts += nb;
         }
         hipLaunchKernelGGL(k_reduce_final<2>, dim3(1), dim3(kBlock), 0, s, (const double *)w.part,
-                           (int64_t)L * nbn, 0x2u, 0.0, w.res, 0LL);
+                           parts, 0x2u, 0.0, w.res, 0LL);
         if (hipMemcpyAsync(c[0]->hpin, w.res, 2 * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             return MG_ERR_HIP;
@@ -2973,8 +3000,8 @@ mg_status refine_solve(int L, mg_ctx *const *c, const int32_t *b0, double *const
         for (int q = 0; q < nu_base; q++) psi_step(c[0], u[0]);
         // up the levels: every box adds the cubic interpolation of its parent's change
         for (int k = 1; k < L; k++)
-            hipLaunchKernelGGL(k_box_correct, dim3(nblk((int64_t)bx[k].m * bx[k].m * bx[k].m)), dim3(kBlock), 0, s,
-                               bx[k], (const double *)u[k - 1], (const double *)w.old[k - 1], u[k]);
+            hipLaunchKernelGGL(k_box_correct, dim3(CubicTile<8>::blocks(bx[k].m)), dim3(kBlock), 0, s, bx[k],
+                               (const double *)u[k - 1], (const double *)w.old[k - 1], u[k]);
         if (hip_status() != MG_OK) return MG_ERR_HIP;
     }
     // the parents' cells under every box end as their children's average

@@ -14,7 +14,7 @@
 // nc is the parent's cells per axis.
 #pragma once
 
-#include "mg_device.hpp"
+#include "mg_kernels.hpp"
 
 namespace grtmg {
 
@@ -35,39 +35,6 @@ __device__ __forceinline__ double cubic_w(int p, int e)
     return p ? w1[e] : w0[e];
 }
 
-// Value at box cell (fi, fj, fk) (indices may lie up to 2 cells outside the box) of the
-// cubic interpolation of the base field a (difference a - b when b is not null).
-__device__ __forceinline__ double box_cubic_at(const BoxGeo &bx, const double *a, const double *b, int fi, int fj,
-                                               int fk)
-{
-    const int f[3] = {fi, fj, fk};
-    int lo[3], par[3];
-#pragma unroll
-    for (int ax = 0; ax < 3; ax++) {
-        const int q = 2 * bx.b0 + f[ax]; // fine index on the base grid's refinement
-        const int I = q >> 1;            // q >= 0: the margin keeps the box inside
-        par[ax] = q & 1;
-        lo[ax] = I - 2 + par[ax];
-    }
-    double s = 0.0;
-#pragma unroll
-    for (int x = 0; x < 4; x++) {
-        double sy = 0.0;
-#pragma unroll
-        for (int y = 0; y < 4; y++) {
-            double sz = 0.0;
-#pragma unroll
-            for (int z = 0; z < 4; z++) {
-                const int64_t q = cidx(bx.nc, lo[0] + x, lo[1] + y, lo[2] + z);
-                sz += cubic_w(par[2], z) * (b ? a[q] - b[q] : a[q]);
-            }
-            sy += cubic_w(par[1], y) * sz;
-        }
-        s += cubic_w(par[0], x) * sy;
-    }
-    return s;
-}
-
 // Base cells under the box take the average of their 8 children: uc[b0 + I..] = R uf.
 __global__ void __launch_bounds__(kBlock) k_box_restrict(BoxGeo bx, const double *__restrict__ uf,
                                                          double *__restrict__ uc)
@@ -86,29 +53,67 @@ __global__ void __launch_bounds__(kBlock) k_box_restrict(BoxGeo bx, const double
     uc[cidx(bx.nc, bx.b0 + I, bx.b0 + J, bx.b0 + K)] = 0.125 * s;
 }
 
+// The box's ghosts across its faces, from the cubic of the base field: one thread per face and
+// line (blockIdx.y: face x-, x+, y-, y+, z-, z+; two in-face coordinates) forms both layers,
+// the two children of the base cell beside the face, from that cell's 5 nodes along the normal
+// and the 4 x 4 in-face nodes of the line.  gv: layer l of face f at (2 f + l) nf^2.  (Formed
+// per fine cell instead, every wave of a z line waited for its few boundary lanes' 64-node
+// sums: 24 us for a 64^3 box, 14 us with this and the forcing kernel below.)
+__global__ void __launch_bounds__(kBlock) k_box_ghosts(BoxGeo bx, const double *__restrict__ uc, double *__restrict__ gv)
+{
+    const int nf = 2 * bx.m, nc = bx.nc, t = (int)(blockIdx.x * kBlock + threadIdx.x);
+    if (t >= nf * nf) return;
+    const int face = (int)blockIdx.y, ax = face >> 1, hi = face & 1;
+    const int64_t st[3] = {(int64_t)nc * nc, nc, 1};
+    const int64_t sn = st[ax], sa = ax == 0 ? st[1] : st[0], sb = ax == 2 ? st[1] : st[2];
+    const int a = t / nf, b = t - a * nf;
+    // base cell beside the face, and the first in-face nodes
+    const int I = hi ? bx.b0 + bx.m : bx.b0 - 1, pa = a & 1, pb = b & 1;
+    const double *q = uc + (I - 2) * sn + (bx.b0 + (a >> 1) - 2 + pa) * sa + (bx.b0 + (b >> 1) - 2 + pb) * sb;
+    double v[5];
+#pragma unroll
+    for (int e = 0; e < 5; e++) {
+        double sy = 0.0;
+#pragma unroll
+        for (int x = 0; x < 4; x++) {
+            double sz = 0.0;
+#pragma unroll
+            for (int y = 0; y < 4; y++) sz += cubic_w(pb, y) * q[e * sn + x * sa + y * sb];
+            sy += cubic_w(pa, x) * sz;
+        }
+        v[e] = sy;
+    }
+#pragma unroll
+    for (int c = 0; c < 2; c++) { // child c of the cell: layer 0 is the one next to the face
+        double o = 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; e++) o += cubic_w(c, e) * v[e + c];
+        gv[(size_t)(2 * face + (hi ? c : 1 - c)) * nf * nf + t] = o;
+    }
+}
+
 // Forcing of the box under the zero rule: the taps of every fine cell that fall
-// outside the box, on the interpolated ghosts, times 1/(12 (h/2)^2), plus the box's
+// outside the box, on the interpolated ghosts gv, times 1/(12 (h/2)^2), plus the box's
 // own FAS forcing tau from a finer box inside it (null: none).
-__global__ void __launch_bounds__(kBlock) k_box_ghost_forcing(BoxGeo bx, double inv12h2, const double *__restrict__ uc,
+__global__ void __launch_bounds__(kBlock) k_box_ghost_forcing(BoxGeo bx, double inv12h2, const double *__restrict__ gv,
                                                               const double *__restrict__ tau, double *__restrict__ ff)
 {
     const int nf = 2 * bx.m;
     const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const unsigned un = (unsigned)nf;
     if (t >= (int64_t)nf * nf * nf) return;
-    const int k = (int)(t % nf), j = (int)((t / nf) % nf), i = (int)(t / ((int64_t)nf * nf));
-    const double wt[5] = {-1.0, 16.0, 0.0, 16.0, -1.0};
-    const int c[3] = {i, j, k};
+    const unsigned row = (unsigned)t / un;
+    const int k = (int)((unsigned)t - row * un), i = (int)(row / un), j = (int)(row - (unsigned)i * un);
+    const size_t nn = (size_t)nf * nf;
+    const int c[3] = {i, j, k}, A[3] = {j, i, i}, B[3] = {k, k, j};
     double f = 0.0;
 #pragma unroll
     for (int ax = 0; ax < 3; ax++) {
-        if (c[ax] >= 2 && c[ax] < nf - 2) continue; // every tap along this axis is inside
-#pragma unroll
-        for (int d = -2; d <= 2; d++) {
-            const int q = c[ax] + d;
-            if (d == 0 || (q >= 0 && q < nf)) continue;
-            const int gi = ax == 0 ? q : i, gj = ax == 1 ? q : j, gk = ax == 2 ? q : k;
-            f += wt[d + 2] * box_cubic_at(bx, uc, nullptr, gi, gj, gk);
-        }
+        const bool hi = c[ax] >= nf - 2;
+        const int d = hi ? nf - 1 - c[ax] : c[ax]; // distance from the face
+        if (d >= 2) continue;                      // every tap along this axis is inside
+        const double *g = gv + 2 * (2 * ax + (hi ? 1 : 0)) * nn + (unsigned)(A[ax] * nf + B[ax]);
+        f += d == 0 ? 16.0 * g[0] - g[nn] : -g[0];
     }
     ff[t] = f * inv12h2 + (tau ? tau[t] : 0.0);
 }
@@ -135,24 +140,31 @@ __global__ void __launch_bounds__(kBlock) k_box_tau(BoxGeo bx, const double *__r
     fc[t] = 0.125 * s - Hc[t];
 }
 
-// Box correction by the base grid's change: uf += cubic interpolation of uc - uc_old,
-// one thread per covered base cell writing its 8 children.
+// Box correction by the base grid's change: uf += cubic interpolation of uc - uc_old, one
+// thread per covered base cell writing its 8 children from the tile's staged differences (tiles
+// of k_prolong_cubic_add_staged; read through the caches, a thread took 1024 loads: 61 us for
+// 32^3 covered cells, 7 us staged).
 __global__ void __launch_bounds__(kBlock) k_box_correct(BoxGeo bx, const double *__restrict__ uc,
                                                         const double *__restrict__ uc_old, double *__restrict__ uf)
 {
-    const int m = bx.m, nf = 2 * m;
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= (int64_t)m * m * m) return;
-    const int K = (int)(t % m), J = (int)((t / m) % m), I = (int)(t / ((int64_t)m * m));
-#pragma unroll
-    for (int di = 0; di < 2; di++)
-#pragma unroll
-        for (int dj = 0; dj < 2; dj++)
-#pragma unroll
-            for (int dk = 0; dk < 2; dk++) {
-                const int fi = 2 * I + di, fj = 2 * J + dj, fk = 2 * K + dk;
-                uf[cidx(nf, fi, fj, fk)] += box_cubic_at(bx, uc, uc_old, fi, fj, fk);
-            }
+    using Q = CubicTile<8>;
+    __shared__ double S[Q::kSX][Q::kSY][Q::kSZP];
+    const int m = bx.m, nby = (m + Q::kY - 1) / Q::kY, nbz = (m + Q::kZ - 1) / Q::kZ;
+    const int bz = blockIdx.x % nbz, by = (blockIdx.x / nbz) % nby, bxx = blockIdx.x / (nbz * nby);
+    const int I0 = bxx * Q::kX, J0 = by * Q::kY, K0 = bz * Q::kZ;
+    const int t = threadIdx.x, kz = t % Q::kZ, jy = (t / Q::kZ) % Q::kY, ix = t / (Q::kZ * Q::kY);
+    for (int q = t; q < Q::kSX * Q::kSY * Q::kSZ; q += kBlock) {
+        const int a = q / (Q::kSY * Q::kSZ), rem = q % (Q::kSY * Q::kSZ), b = rem / Q::kSZ, e = rem % Q::kSZ;
+        const int I = I0 - 2 + a, J = J0 - 2 + b, K = K0 - 2 + e;
+        if (I < m + 2 && J < m + 2 && K < m + 2) { // the margin of 3 cells keeps these inside the base grid
+            const int64_t at = cidx(bx.nc, bx.b0 + I, bx.b0 + J, bx.b0 + K);
+            S[a][b][e] = uc[at] - uc_old[at];
+        }
+    }
+    __syncthreads();
+    if (I0 + ix < m && J0 + jy < m && K0 + kz < m)
+        cubic_children_add<double>([&](int a, int b, int e) { return S[ix + a][jy + b][kz + e]; }, uf, 2 * m, I0 + ix,
+                                   J0 + jy, K0 + kz);
 }
 
 // Composite norm partials of one level: sum of H^2 times the cell volume over the
