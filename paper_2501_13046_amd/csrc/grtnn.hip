@@ -24,6 +24,12 @@ namespace {
 
 constexpr int kMaxLayers = 15;      // 4 levels: 8 encoder + 6 decoder convolutions + head
 constexpr int kWgradBlocks = 512;   // target grid of the weight-gradient kernel
+// blocks that a large convolution is dealt to: what is resident at once (four per CU, two
+// with slices of 32 channels, by LDS), in one round
+constexpr int kConvBlocks = 1024, kConvBlocks32 = 512;
+// bricks x channel tiles from which the larger bricks keep up: at 32^3 with 48 channels
+// (384) 12.2 against 16.0 us; the 16^3 levels (48 to 64) would leave three CUs of four idle
+constexpr int kConvSmall = 256;
 constexpr int kMomentBlocks = 1024; // grid of the moments kernel
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -258,38 +264,28 @@ void carve(nn_ctx *c, Carver &cv)
 // ---- launchers ----------------------------------------------------------------------
 
 struct Out {
-    int channels = 0, mode = kEpStoreBf16;
+    int channels = 0, mode = kEpStoreF32;
     void *ptr = nullptr;
     const u16 *zref = nullptr;
     u16 *zout = nullptr; // kEpSiluBf16: pre-activations (first destination only)
 };
 
 
-
-// Brick kernel launch: one block per 4 x 4 x 16 brick (n a multiple of 16).  Grids
-// of fewer than 1024 blocks keep 7 K steps of weights in flight, larger ones 2.
-template <int NTB, int PD>
-void launch_conv_brick_pd(hipStream_t s, const ConvArgs &a, const dim3 &grid, int cs)
+// Bricks of BZ cells along z (16 where that divides n, else 8).
+template <int CS, int BZ>
+void launch_conv_slice(hipStream_t s, const ConvArgs &a)
 {
-    if (cs == 32)
-        hipLaunchKernelGGL((k_conv3_brick<NTB, 32, PD>), grid, dim3(kNBlock), 0, s, a);
-    else if (cs == 16)
-        hipLaunchKernelGGL((k_conv3_brick<NTB, 16, PD>), grid, dim3(kNBlock), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_conv3_brick<NTB, 8, PD>), grid, dim3(kNBlock), 0, s, a);
-}
-
-template <int NTB>
-void launch_conv_brick(hipStream_t s, const ConvArgs &a, int n, int cs, unsigned gy)
-{
-    const dim3 grid((unsigned)((int64_t)n * n * n / 256), gy);
-    if constexpr (NTB == 1) {
-        if ((int64_t)grid.x * gy < 1024) {
-            launch_conv_brick_pd<1, 7>(s, a, grid, cs);
-            return;
-        }
+    using B = Brick<BZ, 4, CS / 8>;
+    using S = Brick<BZ, 1, CS / 8>;
+    const int bricks = ceil_div(a.n, B::BX) * ceil_div(a.n, B::BY) * ceil_div(a.n, BZ);
+    if (bricks * a.ntile < kConvSmall) {
+        const int small = ceil_div(a.n, S::BX) * ceil_div(a.n, S::BY) * ceil_div(a.n, BZ);
+        hipLaunchKernelGGL((k_conv3_small<CS, BZ>), dim3((unsigned)small, (unsigned)a.ntile), dim3(kNBlock), 0, s, a);
+        return;
     }
-    launch_conv_brick_pd<NTB, 2>(s, a, grid, cs);
+    const int per = std::max(1, (int)((int64_t)bricks * a.ntile / (CS == 32 ? kConvBlocks32 : kConvBlocks)));
+    hipLaunchKernelGGL((k_conv3_stream<CS, BZ>), dim3((unsigned)ceil_div(bricks, per), (unsigned)a.ntile), dim3(kNBlock),
+                       0, s, a, bricks, per);
 }
 
 void launch_conv(hipStream_t s, const Layer &ly, bool transposed, int n, const u16 *in1, int c1, int act1,
@@ -318,41 +314,13 @@ void launch_conv(hipStream_t s, const Layer &ly, bool transposed, int n, const u
     a.zref1 = o1.zref;
     a.zref2 = o2.zref;
     a.zout1 = o1.zout;
-    // the brick kernel reads activations as stored (no SiLU on load)
-    const bool brick = brick_ok(n) && !act1 && !act2;
-    // output tiles per block: all of them (the staged halo and every A operand
-    // read once per block) unless the grid would then have fewer than ~4 blocks
-    // per CU (32^3 and 16^3 levels: 128 and 16 bricks)
-    int ntb = std::min(a.ntile, 4);
-    if (brick) {
-        const int64_t bricks = (int64_t)n * n * n / 256;
-        while (ntb > 1 && bricks * ceil_div(a.ntile, ntb) < 1024) ntb--;
-    }
-    const unsigned gy = (unsigned)ceil_div(a.ntile, ntb);
-    if (!brick) {
-        const int64_t V = (int64_t)n * n * n;
-        if (V <= 4096) {
-            // small grids (the coarsest levels): one M tile and one N tile per wave, so
-            // that the (cell, channel) tiles spread over many waves instead of 2 blocks
-            const dim3 grid((unsigned)ceil_div(V, (int64_t)(kNBlock / 64) * 16), (unsigned)a.ntile);
-            hipLaunchKernelGGL((k_conv3<1, 1>), grid, dim3(kNBlock), 0, s, a);
-            return;
-        }
-        const dim3 grid((unsigned)ceil_div(V, (int64_t)(kNBlock / 64) * 16 * kRows), gy);
-        switch (ntb) {
-        case 1: hipLaunchKernelGGL(k_conv3<1>, grid, dim3(kNBlock), 0, s, a); break;
-        case 2: hipLaunchKernelGGL(k_conv3<2>, grid, dim3(kNBlock), 0, s, a); break;
-        case 3: hipLaunchKernelGGL(k_conv3<3>, grid, dim3(kNBlock), 0, s, a); break;
-        default: hipLaunchKernelGGL(k_conv3<4>, grid, dim3(kNBlock), 0, s, a); break;
-        }
-        return;
-    }
-    switch (ntb) {
-    case 1: launch_conv_brick<1>(s, a, n, a.ko.cs, gy); break;
-    case 2: launch_conv_brick<2>(s, a, n, a.ko.cs, gy); break;
-    case 3: launch_conv_brick<3>(s, a, n, a.ko.cs, gy); break;
-    default: launch_conv_brick<4>(s, a, n, a.ko.cs, gy); break;
-    }
+    const bool z16 = n % 16 == 0;
+    if (a.ko.cs == 32)
+        z16 ? launch_conv_slice<32, 16>(s, a) : launch_conv_slice<32, 8>(s, a);
+    else if (a.ko.cs == 16)
+        z16 ? launch_conv_slice<16, 16>(s, a) : launch_conv_slice<16, 8>(s, a);
+    else
+        z16 ? launch_conv_slice<8, 16>(s, a) : launch_conv_slice<8, 8>(s, a);
 }
 
 // weight and bias gradients of layer ly (input [in1, in2], output gradient dy)

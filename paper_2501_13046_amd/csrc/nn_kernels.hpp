@@ -4,12 +4,13 @@
 // of a C-channel tensor is at v*C + c (C a multiple of 8, so one channel
 // octet is one aligned 16-byte load).  Convolutions are implicit GEMMs on
 // the BF16 matrix cores (v_mfma_f32_16x16x32_bf16, FP32 accumulate):
-//   M = cells (16 per tile), N = output channels (16 per tile), K = 27 taps x
+//   M = output channels (16 per tile), N = cells (16 per tile), K = 27 taps x
 //   input channels, enumerated as channel octets (see KOrder) and consumed
 //   4 octets (32 values) per step.
 // Lane l of a wave supplies row l%16 of A and column l%16 of B, each with
 // the 8 consecutive K values of octet l/16 of the step; it receives rows
-// 4*(l/16) .. 4*(l/16)+3 of column l%16 of the 16x16 result.
+// 4*(l/16) .. 4*(l/16)+3 of column l%16 of the 16x16 result, that is four
+// consecutive channels of one cell, stored as they are.
 #pragma once
 
 #include <utility>
@@ -19,7 +20,11 @@
 namespace grtnn {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4))); // rows of any alignment
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16;
 
@@ -35,7 +40,6 @@ __device__ __forceinline__ void static_for(Fn &&f)
 {
     static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
-constexpr int kRows = 4;     // 16-cell M tiles per wave in the convolution
 
 // ---- BF16 helpers -------------------------------------------------------------------
 
@@ -43,15 +47,12 @@ __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w <<
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 __device__ __forceinline__ float bf2f(u16 b) { return __uint_as_float((uint32_t)b << 16); }
 
-// float -> bf16 bits, round to nearest even (NaN kept quiet)
-__device__ __forceinline__ uint32_t f2bf(float f)
+// float -> bf16 bits, round to nearest even (NaN kept quiet): one v_cvt_pk_bf16_f32
+__device__ __forceinline__ uint32_t pack2(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) { return f2bf(lo) | (f2bf(hi) << 16); }
+__device__ __forceinline__ uint32_t f2bf(float f) { return pack2(f, 0.0f) & 0xffffu; }
 
 // logistic function with the hardware reciprocal (about 1 ulp; the results are
 // rounded to BF16)
@@ -121,12 +122,12 @@ struct KOrder {
 
 // ---- convolution (forward; backward data with mirrored transposed weights) ----------
 
-enum { kEpStoreBf16 = 0, kEpStoreF32 = 1, kEpAddF32 = 2, kEpDsiluBf16 = 3, kEpSiluBf16 = 4 };
+enum { kEpStoreF32, kEpDsiluBf16, kEpSiluBf16 };
 
 struct ConvArgs {
     const u16 *in1, *in2; // input = concatenation [in1, in2] along channels
     int c1, c2;           // channels (= strides) of in1 / in2 (c2 = 0: no in2)
-    int act1, act2;       // apply SiLU to values read from in1 / in2 (general kernel only)
+    int act1, act2;       // apply SiLU to values read from in1 / in2
     const u32x4 *w;       // packed weights [tile][chunk][64 lanes] of 8 BF16
     const float *bias;    // per output channel, or null
     int n;                // cells per axis
@@ -141,108 +142,35 @@ struct ConvArgs {
     u16 *zout1;           // kEpSiluBf16: pre-activations of destination 1 (may be null)
 };
 
-// Epilogue of one value: output channel co of cell v
-__device__ __forceinline__ void conv_store(const ConvArgs &a, int co, int64_t v, float acc)
+// Epilogue of output channels co0 .. co0+3 of cell v (acc with the bias added)
+__device__ __forceinline__ void conv_store4(const ConvArgs &a, int co0, int64_t v, f32x4 f)
 {
-    const float val = acc + (a.bias ? a.bias[co] : 0.0f);
-    const bool first = co < a.oc1;
-    const int cc = first ? co : co - a.oc1;
+    const bool first = co0 < a.oc1; // oc1 is a multiple of 8 where there is a second destination
+    const int cc = first ? co0 : co0 - a.oc1;
     const int oc = first ? a.oc1 : a.oc2;
     const int mode = first ? a.mode1 : a.mode2;
     void *out = first ? a.out1 : a.out2;
     const int64_t idx = v * oc + cc;
-    if (mode == kEpSiluBf16) {
-        ((u16 *)out)[idx] = (u16)f2bf(silu(val));
-        if (a.zout1) a.zout1[idx] = (u16)f2bf(val);
-    } else if (mode == kEpStoreBf16) {
-        ((u16 *)out)[idx] = (u16)f2bf(val);
-    } else if (mode == kEpStoreF32) {
-        ((float *)out)[idx] = val;
-    } else if (mode == kEpAddF32) {
-        ((float *)out)[idx] += val;
-    } else {
-        const u16 *zr = first ? a.zref1 : a.zref2;
-        ((u16 *)out)[idx] = (u16)f2bf(val * dsilu(bf2f(zr[idx])));
-    }
-}
-
-// General kernel (any n): every wave computes ROWS M tiles of 16 consecutive
-// cells and reads its A operands straight from global memory.
-template <int NTB, int ROWS = kRows>
-__global__ void __launch_bounds__(kNBlock) k_conv3(ConvArgs a)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane >> 4, r = lane & 15;
-    const int n = a.n;
-    const int64_t V = (int64_t)n * n * n;
-    const int64_t vb = ((int64_t)blockIdx.x * (kNBlock / 64) + wave) * (16 * ROWS);
-    if (vb >= V) return; // no block-level synchronisation in this kernel
-    const int t0 = blockIdx.y * NTB;
-    int px[ROWS], py[ROWS], pz[ROWS];
-#pragma unroll
-    for (int q = 0; q < ROWS; q++) {
-        int64_t v = vb + q * 16 + r;
-        if (v >= V) v = V - 1; // rows past the end are computed but not stored
-        const unsigned uv = (unsigned)v, un = (unsigned)n, t = uv / un; // n^3 < 2^32
-        pz[q] = (int)(uv - t * un);
-        py[q] = (int)(t % un);
-        px[q] = (int)(t / un);
-    }
-    f32x4 acc[ROWS][NTB];
-#pragma unroll
-    for (int q = 0; q < ROWS; q++)
-#pragma unroll
-        for (int t = 0; t < NTB; t++) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    for (int ch = 0; ch < a.nchunk; ch++) {
-        u32x4 b[NTB];
-#pragma unroll
-        for (int t = 0; t < NTB; t++)
-            b[t] = (t0 + t < a.ntile) ? a.w[((int64_t)(t0 + t) * a.nchunk + ch) * 64 + lane] : zero;
-        int tap, cg;
-        u32x4 av[ROWS];
-        if (a.ko.at(ch, g, tap, cg)) {
-            const int dx = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dz = tap % 3 - 1;
-            const bool one = cg < a.c1;
-            const u16 *src = one ? a.in1 : a.in2;
-            const int cs = one ? a.c1 : a.c2, c0 = one ? cg : cg - a.c1, act = one ? a.act1 : a.act2;
-#pragma unroll
-            for (int q = 0; q < ROWS; q++) {
-                const int x = wrapn(px[q] + dx, n), y = wrapn(py[q] + dy, n), z = wrapn(pz[q] + dz, n);
-                const int64_t v = ((int64_t)x * n + y) * n + z;
-                av[q] = *(const u32x4 *)(src + v * cs + c0);
-                if (act) av[q] = silu8(av[q]);
-            }
+    if (mode == kEpStoreF32) {
+        if (co0 + 4 <= a.cout) {
+            *(f32x4u *)((float *)out + idx) = f;
         } else {
 #pragma unroll
-            for (int q = 0; q < ROWS; q++) av[q] = zero;
+            for (int j = 0; j < 3; j++)
+                if (co0 + j < a.cout) ((float *)out)[idx + j] = f[j];
         }
-#pragma unroll
-        for (int q = 0; q < ROWS; q++)
-#pragma unroll
-            for (int t = 0; t < NTB; t++) acc[q][t] = mfma(av[q], b[t], acc[q][t]);
+        return;
     }
-#pragma unroll
-    for (int t = 0; t < NTB; t++) {
-        const int co = (t0 + t) * 16 + r;
-        if (co >= a.cout) continue;
-#pragma unroll
-        for (int q = 0; q < ROWS; q++)
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int64_t v = vb + q * 16 + 4 * g + i;
-                if (v < V) conv_store(a, co, v, acc[q][t][i]);
-            }
+    // BF16 destinations have a multiple of 8 channels
+    if (mode == kEpSiluBf16) {
+        *(u32x2 *)((u16 *)out + idx) = u32x2{pack2(silu(f[0]), silu(f[1])), pack2(silu(f[2]), silu(f[3]))};
+        if (a.zout1) *(u32x2 *)(a.zout1 + idx) = u32x2{pack2(f[0], f[1]), pack2(f[2], f[3])};
+    } else {
+        const u32x2 z = *(const u32x2 *)((first ? a.zref1 : a.zref2) + idx);
+        *(u32x2 *)((u16 *)out + idx) = u32x2{pack2(f[0] * dsilu(bf_lo(z[0])), f[1] * dsilu(bf_hi(z[0]))),
+                                             pack2(f[2] * dsilu(bf_lo(z[1])), f[3] * dsilu(bf_hi(z[1])))};
     }
 }
-
-// Brick kernel (n a multiple of 16): a block computes a brick of 4 x 4 x 16
-// cells (wave w: x0 + w; M tile q: y0 + q; row r: z0 + r).  For every channel
-// slice the block stages the brick's halo (6 x 6 x 18 cells x CS channels,
-// wrapped periodically) in LDS; every A operand is then one 16-byte LDS read,
-// and the 16 rows x 4 octets of a step are contiguous (conflict-free).
-constexpr int kHX = 6, kHY = 6, kHZ = 18;
-constexpr int kHalo = kHX * kHY * kHZ;
 
 __device__ __forceinline__ int brick_block(int nblocks)
 {
@@ -251,202 +179,322 @@ __device__ __forceinline__ int brick_block(int nblocks)
     return (nblocks % 8 == 0) ? (b % 8) * (nblocks / 8) + b / 8 : b;
 }
 
-// Epilogue of 8 consecutive output channels co0 .. co0+7 of cell v (values
-// without bias); vector stores where the octet is whole.
-__device__ __forceinline__ void conv_store8(const ConvArgs &a, int co0, int64_t v, const float (&acc)[8])
+// x / D for 0 <= x < 4096 and D <= 18, without a wide multiplication
+template <int D>
+__device__ __forceinline__ int div_small(int x)
 {
-    if (co0 >= a.cout) return;
-    const bool first = co0 < a.oc1;
-    const int cc = first ? co0 : co0 - a.oc1;
-    const int oc = first ? a.oc1 : a.oc2;
-    const int mode = first ? a.mode1 : a.mode2;
-    void *out = first ? a.out1 : a.out2;
-    const int nv = min(8, a.cout - co0);
-    float f[8];
-#pragma unroll
-    for (int j = 0; j < 8; j++) f[j] = acc[j] + ((a.bias && j < nv) ? a.bias[co0 + j] : 0.0f);
-    const int64_t idx = v * oc + cc;
-    if (nv == 8 && mode != kEpStoreF32 && mode != kEpAddF32) {
-        if (mode == kEpSiluBf16) {
-            float s8[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) s8[j] = silu(f[j]);
-            *(u32x4 *)((u16 *)out + idx) = pack8(s8);
-            if (a.zout1) *(u32x4 *)(a.zout1 + idx) = pack8(f);
-        } else if (mode == kEpStoreBf16) {
-            *(u32x4 *)((u16 *)out + idx) = pack8(f);
-        } else {
-            const u16 *zr = first ? a.zref1 : a.zref2;
-            float z[8];
-            unpack8(*(const u32x4 *)(zr + idx), z);
-#pragma unroll
-            for (int j = 0; j < 8; j++) f[j] *= dsilu(z[j]);
-            *(u32x4 *)((u16 *)out + idx) = pack8(f);
-        }
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; j++) {
-        if (j >= nv) break;
-        if (mode == kEpStoreF32)
-            ((float *)out)[idx + j] = f[j];
-        else if (mode == kEpAddF32)
-            ((float *)out)[idx + j] += f[j];
-        else if (mode == kEpStoreBf16)
-            ((u16 *)out)[idx + j] = (u16)f2bf(f[j]);
-        else if (mode == kEpSiluBf16) {
-            ((u16 *)out)[idx + j] = (u16)f2bf(silu(f[j]));
-            if (a.zout1) a.zout1[idx + j] = (u16)f2bf(f[j]);
-        } else {
-            const u16 *zr = first ? a.zref1 : a.zref2;
-            ((u16 *)out)[idx + j] = (u16)f2bf(f[j] * dsilu(bf2f(zr[idx + j])));
-        }
-    }
+    return __mul24(x, (65536 + D - 1) / D) >> 16;
 }
 
-// Halo element (16-byte units) of K octet o of a slice of P octets per tap,
-// relative to the lane's element ((wave kHY + q) kHZ + r) P; octets past the 27
-// taps point at element 0 (their operands are zeroed).
-template <int P>
-struct TapOffsets {
-    static constexpr int kSteps = (27 * P + 3) / 4;
-    int v[kSteps * 4];
-    constexpr TapOffsets() : v()
+// Brick of cells of one block of four waves, ROWS tiles of 16 cells per wave.  A
+// tile is 16 / BZ rows of BZ cells.  ROWS = 4: 4 x 4 x 16 or 4 x 8 x 8 cells, wave
+// w at x0 + w, tile q at row q of tiles.  ROWS = 1: 2 x 2 x 16 or 2 x 4 x 8 cells,
+// one tile per wave.  The halo is one cell on every side; in LDS the octets
+// of a cell are adjacent (P = 4: in pairs, the second pairs half a bank row off), which
+// leaves both the operand reads (16 cells, lane groups on different octets) and the
+// staging stores (16 / P cells, all octets) without bank conflicts.
+template <int BZ, int ROWS, int P>
+struct Brick {
+    static constexpr int MY = 16 / BZ; // y rows of a tile
+    static constexpr int BX = ROWS == 4 ? 4 : 2;
+    static constexpr int BY = (ROWS == 4 ? 4 : 2) * MY;
+    static constexpr int HX = BX + 2, HY = BY + 2, HZ = BZ + 2;
+    static constexpr int kHalo = HX * HY * HZ;
+    static constexpr int CW = P == 1 ? 1 : 2;                      // elements per cell and plane
+    static constexpr int kPlane = (kHalo * CW + 15) / 16 * 16 + 8; // from the first to the second octet pair
+    static constexpr int kTile = P == 4 ? kPlane + 2 * kHalo : kHalo * CW;
+    static constexpr int NE = (kHalo * P + kNBlock - 1) / kNBlock; // staging loads per thread
+    static constexpr int kSteps = (27 * P + 3) / 4;                // K steps of a slice
+
+    // element of octet o relative to the cell's octet 0
+    static __host__ __device__ constexpr int octet(int o) { return (o >> 1) * kPlane + (o & 1); }
+    // halo cell of staging load k of this thread (past the halo: its last cell)
+    static __device__ __forceinline__ int cell(int tid, int k) { return min((tid + k * kNBlock) / P, kHalo - 1); }
+    static __device__ __forceinline__ void split(int hv, int &hx, int &hy, int &hz)
     {
-        for (int o = 0; o < kSteps * 4; o++) {
-            const int oo = o < 27 * P ? o : 0;
-            const int tap = oo / P, o8 = oo % P;
-            v[o] = (((tap / 9) * kHY + (tap / 3) % 3) * kHZ + tap % 3) * P + o8;
+        const int row = div_small<HZ>(hv);
+        hz = hv - row * HZ;
+        hx = div_small<HY>(row);
+        hy = row - hx * HY;
+    }
+    static __device__ __forceinline__ void store(u32x4 *smem, const u32x4 (&stg)[NE])
+    {
+        const int tid = threadIdx.x;
+#pragma unroll
+        for (int k = 0; k < NE; k++)
+            if ((k + 1) * kNBlock <= kHalo * P || tid + k * kNBlock < kHalo * P)
+                smem[octet(tid % P) + (tid / P + k * (kNBlock / P)) * CW] = stg[k];
+    }
+    // cell of tile 0 of this lane, from the brick's first one
+    static __device__ __forceinline__ void lane_cell(int wave, int r, int &x, int &y, int &z)
+    {
+        x = ROWS == 4 ? wave : wave >> 1;
+        y = (ROWS == 4 ? 0 : (wave & 1) * MY) + r / BZ;
+        z = r % BZ;
+    }
+    // element of K octet o relative to octet 0 of tap 0 (past the 27 taps: that one;
+    // its operands are zeroed)
+    static __host__ __device__ constexpr int tap(int o)
+    {
+        if (o >= 27 * P) return 0;
+        const int t = o / P;
+        return (((t / 9) * HY + (t / 3) % 3) * HZ + t % 3) * CW + octet(o % P);
+    }
+    // The operands of K step ST are read at row(ST) + tap(4 ST) + tile offset: the
+    // second and third summand are constants, the first takes few values over the
+    // steps (one for P = 4, four for P = 2)
+    template <int ST>
+    static __device__ __forceinline__ int row(int g)
+    {
+        constexpr int t0 = tap(4 * ST), d1 = tap(4 * ST + 1) - t0, d2 = tap(4 * ST + 2) - t0, d3 = tap(4 * ST + 3) - t0;
+        if constexpr (P == 4)
+            return octet(g);
+        else if constexpr (P == 2 && 4 * ST + 3 < 27 * P)
+            return (g & 1) + ((g & 2) ? d2 : 0);
+        else
+            return g == 0 ? 0 : g == 1 ? d1 : g == 2 ? d2 : d3;
+    }
+    // cell operands of step ST for the ROWS tiles of the lane (base: its first element)
+    template <int ST>
+    static __device__ __forceinline__ void operands(const u32x4 *base, int g, u32x4 (&av)[ROWS])
+    {
+        const u32x4 *ap = base + row<ST>(g);
+#pragma unroll
+        for (int q = 0; q < ROWS; q++) av[q] = ap[tap(4 * ST) + q * MY * HZ * CW];
+        if constexpr (4 * ST + 3 >= 27 * P) {
+            const bool pad = 4 * ST + g >= 27 * P;
+#pragma unroll
+            for (int q = 0; q < ROWS; q++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) av[q][j] = pad ? 0u : av[q][j];
         }
     }
 };
 
-// Offset of K step ST for lane group g (octet 4 ST + g).
-template <int P, int ST>
-__device__ __forceinline__ int tap_offset(int g)
+// A cell past the grid's wrapped one only feeds cells past the grid, which are not stored.
+__device__ __forceinline__ int halo_at(int p, int n) { return wrapn(min(p, n), n); }
+
+// The channel slice sl of the layer input: source of its first channel, stride, SiLU
+struct SliceSrc {
+    const u16 *p;
+    int cs, act;
+    __device__ __forceinline__ SliceSrc(const ConvArgs &a, int cb)
+    {
+        const bool one = cb < a.c1;
+        p = one ? a.in1 + cb : a.in2 + (cb - a.c1);
+        cs = one ? a.c1 : a.c2;
+        act = one ? a.act1 : a.act2;
+    }
+};
+
+__device__ __forceinline__ f32x4 conv_bias(const ConvArgs &a, int co0)
 {
-    constexpr TapOffsets<P> T{};
-    if constexpr (P == 4)
-        return T.v[4 * ST] + g; // one tap per step, the lane group picks the octet
-    else if constexpr (P == 2)
-        return ((g & 2) ? T.v[4 * ST + 2] : T.v[4 * ST]) + (g & 1);
-    else
-        return g == 0 ? T.v[4 * ST] : g == 1 ? T.v[4 * ST + 1] : g == 2 ? T.v[4 * ST + 2] : T.v[4 * ST + 3];
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+    if (a.bias) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) b[j] = a.bias[min(co0 + j, a.cout - 1)];
+    }
+    return b;
 }
 
-// PD: weight prefetch depth in K steps (2 for grids that fill the chip, deeper
-// for the small levels whose few blocks wait on every weight fetch).
-template <int NTB, int CS, int PD>
-__global__ void __launch_bounds__(kNBlock) k_conv3_brick(ConvArgs a)
+template <class B, int ROWS>
+__device__ __forceinline__ void conv_write(const ConvArgs &a, int co0, int x, int y, int z, f32x4 (&acc)[ROWS],
+                                           f32x4 bias)
 {
-    constexpr int P = CS / 8;
-    constexpr int kTile = kHalo * P;                     // 16-byte halo elements
-    constexpr int kOutRow = 17;                          // floats per staged output cell (padded)
-    constexpr int kOut = (256 * kOutRow + 3) / 4;        // 16-byte elements of the output stage
-    constexpr int kSmem = kTile > kOut ? kTile : kOut;
-    constexpr int NE = (kTile + kNBlock - 1) / kNBlock;  // staging loads per thread
-    __shared__ u32x4 smem[kSmem];
+    const int n = a.n;
+#pragma unroll
+    for (int q = 0; q < ROWS; q++) {
+        const int yq = y + q * B::MY;
+        if (co0 < a.cout && max(x, max(yq, z)) < n)
+            conv_store4(a, co0, ((int64_t)x * n + yq) * n + z, acc[q] + bias);
+        acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+}
+
+// Convolution on small grids (any n: cells past the grid are not stored): one brick of
+// ROWS = 1 and one tile of 16 output channels per block, so that the few cells spread
+// over many blocks.  Per channel slice the block stages the brick's halo (wrapped
+// periodically); a cell operand is then one 16-byte LDS read.  What bounds it is the
+// chain of latencies of one block, so a whole slice of weights is in registers and is
+// replaced step by step by the next slice's, whose halo is fetched meanwhile.
+// 48 -> 48 channels at 16^3 12.9 -> 5.8 us, 64 -> 64 at 8^3 22 -> 6.0 us against
+// two steps of weights in flight and operands from global memory at 8^3.
+template <int CS, int BZ>
+__global__ void __launch_bounds__(kNBlock, 2) k_conv3_small(ConvArgs a)
+{
+    using B = Brick<BZ, 1, CS / 8>;
+    constexpr int P = CS / 8, spp = B::kSteps;
+    __shared__ u32x4 smem[B::kTile];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, r = lane & 15;
-    const int n = a.n;
-    const int nbz = n / 16, nby = n / 4;
+    const int n = a.n, nbz = (n + BZ - 1) / BZ, nby = (n + B::BY - 1) / B::BY;
     int b = brick_block(gridDim.x);
     const int bz = b % nbz;
     b /= nbz;
     const int by = b % nby, bx = b / nby;
-    const int x0 = bx * 4, y0 = by * 4, z0 = bz * 16;
-    const int t0 = blockIdx.y * NTB;
-    f32x4 acc[4][NTB];
+    const int x0 = bx * B::BX, y0 = by * B::BY, z0 = bz * BZ;
+    int cell[B::NE];
 #pragma unroll
-    for (int q = 0; q < 4; q++)
-#pragma unroll
-        for (int t = 0; t < NTB; t++) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    const int nslice = (a.c1 + a.c2) / CS;
-    constexpr int spp = TapOffsets<P>::kSteps; // K steps per slice (the packed order's spp)
-    static_assert(PD >= 2 && PD <= spp, "prefetch depth");
-    const int lbase = ((wave * kHY) * kHZ + r) * P;
-    // weights (L2-resident, the same for every block): a ring of PD K steps; step
-    // st + PD - 1 is fetched when step st starts
-    u32x4 bw[PD][NTB];
-    auto wload = [&](int ch, u32x4 (&w)[NTB]) {
-#pragma unroll
-        for (int t = 0; t < NTB; t++)
-            w[t] = (t0 + t < a.ntile) ? a.w[((int64_t)(t0 + t) * a.nchunk + ch) * 64 + lane] : zero;
-    };
-    // halo of one channel slice, fetched into registers (wrapped periodically)
-    u32x4 stg[NE];
+    for (int k = 0; k < B::NE; k++) {
+        int hx, hy, hz;
+        B::split(B::cell(threadIdx.x, k), hx, hy, hz);
+        cell[k] = (halo_at(x0 + hx - 1, n) * n + halo_at(y0 + hy - 1, n)) * n + halo_at(z0 + hz - 1, n);
+    }
+    u32x4 stg[B::NE];
     auto stage_load = [&](int sl) {
-        const int cb = sl * CS;
-        const bool one = cb < a.c1;
-        const u16 *src = one ? a.in1 : a.in2;
-        const int cs = one ? a.c1 : a.c2, c0 = one ? cb : cb - a.c1;
+        const SliceSrc s(a, sl * CS);
 #pragma unroll
-        for (int k = 0; k < NE; k++) {
-            const int e = threadIdx.x + k * kNBlock;
-            stg[k] = zero;
-            if (e < kTile) {
-                const int o = e % P, hv = e / P;
-                const int hz = hv % kHZ, hy = (hv / kHZ) % kHY, hx = hv / (kHZ * kHY);
-                const int gx = wrapn(x0 + hx - 1, n), gy = wrapn(y0 + hy - 1, n), gz = wrapn(z0 + hz - 1, n);
-                stg[k] = *(const u32x4 *)(src + (((int64_t)gx * n + gy) * n + gz) * cs + c0 + o * 8);
-            }
+        for (int k = 0; k < B::NE; k++)
+            stg[k] = *(const u32x4 *)(s.p + ((int64_t)cell[k] * s.cs + 8 * (threadIdx.x % P)));
+        if (s.act) {
+#pragma unroll
+            for (int k = 0; k < B::NE; k++) stg[k] = silu8(stg[k]);
         }
     };
-    for (int sl = 0; sl < nslice; sl++) {
-        // every staging load of the slice is issued before the first LDS store
-        stage_load(sl);
-        static_for<PD - 1>([&](auto k) { wload(sl * spp + decltype(k)::value, bw[decltype(k)::value]); });
-        __syncthreads(); // previous slice consumed
-#pragma unroll
-        for (int k = 0; k < NE; k++) {
-            const int e = threadIdx.x + k * kNBlock;
-            if (e < kTile) smem[e] = stg[k];
-        }
-        __syncthreads();
-        // K steps unrolled: the halo offsets of the taps are compile-time constants
-        // (one select by lane group per step)
+    const u32x4 *w = a.w + (int64_t)blockIdx.y * a.nchunk * 64;
+    auto wload = [&](int ch) { return *(const u32x4 *)((const char *)(w + ch * 64) + (uint32_t)(16 * lane)); };
+    u32x4 bw[spp];
+    stage_load(0);
+    static_for<spp>([&](auto k) { bw[decltype(k)::value] = wload(decltype(k)::value); });
+    const int co0 = blockIdx.y * 16 + 4 * g;
+    const f32x4 bias = conv_bias(a, co0);
+    f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
+    int cx, cy, cz;
+    B::lane_cell(wave, r, cx, cy, cz);
+    const u32x4 *base = smem + ((cx * B::HY + cy) * B::HZ + cz) * B::CW;
+    auto consume = [&](auto reload, int sl) {
         static_for<spp>([&](auto stc) {
             constexpr int st = decltype(stc)::value;
-            if constexpr (st + PD - 1 < spp) wload(sl * spp + st + PD - 1, bw[(st + PD - 1) % PD]);
-            const u32x4 *ap = smem + lbase + tap_offset<P, st>(g);
-            u32x4 av[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) av[q] = ap[q * kHZ * P];
-            if constexpr (4 * st + 3 >= 27 * P) { // last step: octets past the 27 taps
-                if (4 * st + g >= 27 * P) {
-#pragma unroll
-                    for (int q = 0; q < 4; q++) av[q] = zero;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-#pragma unroll
-                for (int t = 0; t < NTB; t++) acc[q][t] = mfma(av[q], bw[st % PD][t], acc[q][t]);
+            u32x4 av[1];
+            B::template operands<st>(base, g, av);
+            acc[0] = mfma(bw[st], av[0], acc[0]);
+            if constexpr (decltype(reload)::value) bw[st] = wload((sl + 1) * spp + st);
         });
-    }
-    // epilogue through LDS: every thread then writes whole channel octets
-    float *os = (float *)smem;
-#pragma unroll
-    for (int t = 0; t < NTB; t++) {
-        if ((t0 + t) * 16 >= a.cout) break;
+    };
+    const int nslice = (a.c1 + a.c2) / CS;
+    for (int sl = 0; sl < nslice; sl++) {
+        __syncthreads(); // the slice staged before is consumed
+        B::store(smem, stg);
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4; q++)
-#pragma unroll
-            for (int i = 0; i < 4; i++) os[(wave * 64 + q * 16 + 4 * g + i) * kOutRow + r] = acc[q][t][i];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 2; k++) {
-            const int e = threadIdx.x + k * kNBlock; // 256 cells x 2 octets
-            const int cell = e >> 1, o = e & 1;
-            const int vx = cell >> 6, vy = (cell >> 4) & 3, vz = cell & 15;
-            float f[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) f[j] = os[cell * kOutRow + o * 8 + j];
-            const int64_t v = ((int64_t)(x0 + vx) * n + (y0 + vy)) * n + (z0 + vz);
-            conv_store8(a, (t0 + t) * 16 + o * 8, v, f);
+        if (sl + 1 < nslice) {
+            stage_load(sl + 1);
+            consume(std::true_type{}, sl);
+        } else {
+            consume(std::false_type{}, sl);
         }
+    }
+    conv_write<B, 1>(a, co0, x0 + cx, y0 + cy, z0 + cz, acc, bias);
+}
+
+// Convolution on large grids (any n): a block takes a range of bricks of ROWS = 4 and
+// one tile of 16 output channels (blockIdx.y).  The slice's weights are in LDS, read
+// there once per four products: from L2 into every wave they cost more of the vector
+// cache's bandwidth than the halo (14 against 5 loads of 1 KB per wave and brick of 16
+// channels).  A range of bricks, so that the loads of the next are in flight: with
+// one brick per block the same arithmetic waited 70 % of its time.  The next halo (of the next slice or brick) and, where
+// the layer has several slices, the next weights are fetched into registers while
+// this one is consumed.  The four layers with 16 output channels at 128^3 (one of them
+// of three slices) 350 -> 291 us, 112 -> 48 channels at 32^3 32 -> 24 us.
+template <int CS, int BZ>
+__global__ void __launch_bounds__(kNBlock, CS == 32 ? 2 : 4) k_conv3_stream(ConvArgs a, int bricks, int per_block)
+{
+    using B = Brick<BZ, 4, CS / 8>;
+    constexpr int P = CS / 8, spp = B::kSteps;
+    constexpr int NW = (spp * 64 + kNBlock - 1) / kNBlock; // weight loads per thread
+    __shared__ u32x4 smem[B::kTile];
+    __shared__ u32x4 wsm[spp * 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 4, r = lane & 15;
+    const int n = a.n, nbz = (n + BZ - 1) / BZ, nby = (n + B::BY - 1) / B::BY;
+    const int first = brick_block(gridDim.x) * per_block, last = min(bricks, first + per_block);
+    if (first >= last) return;
+    int off[B::NE]; // cells from the halo's first one, inside the grid
+#pragma unroll
+    for (int k = 0; k < B::NE; k++) {
+        int hx, hy, hz;
+        B::split(B::cell(tid, k), hx, hy, hz);
+        off[k] = (hx * n + hy) * n + hz;
+    }
+    int x0, y0, z0; // first cell of the brick whose halo was fetched last
+    auto brick_at = [&](int bi) {
+        const int t = bi / nbz;
+        z0 = (bi - t * nbz) * BZ;
+        const int bx = t / nby;
+        y0 = (t - bx * nby) * B::BY;
+        x0 = bx * B::BX;
+    };
+    u32x4 stg[B::NE], wst[NW];
+    auto stage_load = [&](int sl) {
+        const SliceSrc s(a, sl * CS);
+        if (min(x0, min(y0, z0)) > 0 && max(x0 + B::BX, max(y0 + B::BY, z0 + BZ)) < n) {
+            const char *p = (const char *)(s.p + (((int64_t)(x0 - 1) * n + y0 - 1) * n + z0 - 1) * s.cs);
+#pragma unroll
+            for (int k = 0; k < B::NE; k++)
+                stg[k] = *(const u32x4 *)(p + (uint32_t)(__mul24(off[k], 2 * s.cs) + 16 * (tid % P)));
+        } else {
+            int t = tid; // the cells are worked out anew, not kept in registers over the loop
+            asm volatile("" : "+v"(t));
+#pragma unroll
+            for (int k = 0; k < B::NE; k++) {
+                int hx, hy, hz;
+                B::split(B::cell(t, k), hx, hy, hz);
+                const int c = (halo_at(x0 + hx - 1, n) * n + halo_at(y0 + hy - 1, n)) * n + halo_at(z0 + hz - 1, n);
+                stg[k] = *(const u32x4 *)(s.p + ((int64_t)c * s.cs + 8 * (tid % P)));
+            }
+        }
+        if (s.act) {
+#pragma unroll
+            for (int k = 0; k < B::NE; k++) stg[k] = silu8(stg[k]);
+        }
+    };
+    const u32x4 *w = a.w + (int64_t)blockIdx.y * a.nchunk * 64;
+    auto weight_load = [&](int sl) {
+#pragma unroll
+        for (int k = 0; k < NW; k++) wst[k] = w[sl * spp * 64 + min(tid + k * kNBlock, spp * 64 - 1)];
+    };
+    auto weight_store = [&]() {
+#pragma unroll
+        for (int k = 0; k < NW; k++)
+            if ((k + 1) * kNBlock <= spp * 64 || tid + k * kNBlock < spp * 64) wsm[tid + k * kNBlock] = wst[k];
+    };
+    const int nslice = (a.c1 + a.c2) / CS;
+    int bi = first, sl = 0;
+    brick_at(bi);
+    weight_load(0);
+    stage_load(0);
+    const int co0 = blockIdx.y * 16 + 4 * g;
+    const f32x4 bias = conv_bias(a, co0);
+    f32x4 acc[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int cx, cy, cz;
+    B::lane_cell(wave, r, cx, cy, cz);
+    const u32x4 *base = smem + ((cx * B::HY + cy) * B::HZ + cz) * B::CW;
+    weight_store();
+    for (;;) {
+        B::store(smem, stg);
+        if (nslice > 1) weight_store();
+        __syncthreads();
+        const int nsl = sl + 1 < nslice ? sl + 1 : 0, nbi = nsl ? bi : bi + 1;
+        const int px = x0 + cx, py = y0 + cy, pz = z0 + cz;
+        if (nbi < last) {
+            if (!nsl) brick_at(nbi);
+            if (nslice > 1) weight_load(nsl);
+            stage_load(nsl);
+        }
+        static_for<spp>([&](auto stc) {
+            constexpr int st = decltype(stc)::value;
+            const u32x4 wv = wsm[st * 64 + lane];
+            u32x4 av[4];
+            B::template operands<st>(base, g, av);
+#pragma unroll
+            for (int q = 0; q < 4; q++) acc[q] = mfma(wv, av[q], acc[q]);
+        });
+        if (!nsl) conv_write<B, 4>(a, co0, px, py, pz, acc, bias);
+        if (nbi >= last) break;
+        bi = nbi;
+        sl = nsl;
+        __syncthreads(); // the staged slice is consumed
     }
 }
 
@@ -572,6 +620,7 @@ __global__ void __launch_bounds__(kNBlock) k_conv3_wgrad(WgtArgs a)
 // B operand of the MFMA (8 consecutive z cells of one channel) is then one
 // aligned 16-byte LDS read.  Row strides are padded so that the 16 lanes of a
 // read hit distinct banks.  Blocks take contiguous ranges of bricks.
+constexpr int kHX = 6, kHY = 6, kHZ = 18;
 constexpr int kDyStride = 256 + 8;          // u16 per co row of dyT
 constexpr int kHtStride = kHX * kHY * 16 + 8; // u16 per ci plane of one hT copy
 

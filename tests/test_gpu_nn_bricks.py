@@ -1,0 +1,36 @@
+"""Network kernels at the edges of their bricks, against the FP64 oracle.
+
+Operands are BF16 values, so that a result differs from the oracle only by FP32
+accumulation: 1e-4 of the output's rms (27 cin products of unit-scale terms, 27 cin
+2^-24 < 2e-4 in the worst order, its square root in practice); with SiLU on load the
+activation is rounded to BF16 on both sides and may differ by one unit: 1e-2.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import nn_oracle as nn
+from paper_2501_13046_amd import grtnn as gn
+from test_gpu_nn import bf, cf, cl, silu_bf, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+# sides below, at and past bricks of 2 x 4 x 8, 2 x 2 x 16, 4 x 8 x 8 and 4 x 4 x 16 cells
+# (from 256 bricks and channel tiles on the larger ones), slices of 8, 16 and 32
+# channels, one and several of them, output channels that end inside a tile or a quad
+@pytest.mark.parametrize("n,cin,cout,act", [(1, 8, 5, False), (2, 32, 16, True), (9, 64, 7, False), (12, 16, 4, False),
+                                            (20, 24, 17, False), (16, 96, 20, False), (34, 16, 24, False),
+                                            (36, 64, 48, False), (44, 8, 20, True), (40, 32, 18, False),
+                                            (48, 32, 16, True), (48, 24, 3, False)])
+def test_convolution_on_any_side(n, cin, cout, act):
+    rng = np.random.default_rng(100 * n + cin + cout)
+    x = bf(rng.standard_normal((cin, n, n, n)))
+    W = bf(rng.standard_normal((cout, cin, 3, 3, 3)) * np.sqrt(2.0 / (27 * cin)))
+    b = rng.uniform(-0.1, 0.1, cout).astype(np.float32).astype(np.float64)
+    y = gn.conv3_forward(to_dev(cl(x), torch.bfloat16), to_dev(W.reshape(-1), torch.float32),
+                         to_dev(b, torch.float32), n, cin, cout, act)
+    ref = nn.conv3(torch.tensor(silu_bf(x) if act else x), torch.tensor(W), torch.tensor(b)).numpy()
+    err = np.abs(cf(y.cpu().numpy(), n) - ref).max() / np.sqrt(np.mean(ref ** 2))
+    print(f"n={n} {cin}->{cout} act={act}: max err / rms = {err:.2e}", flush=True)
+    assert err < (1e-2 if act else 1e-4)
