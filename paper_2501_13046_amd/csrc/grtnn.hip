@@ -22,8 +22,9 @@ using namespace grtnn;
 
 namespace {
 
-constexpr int kMaxLayers = 15;      // 4 levels: 8 encoder + 6 decoder convolutions + head
-constexpr int kWgradBlocks = 512;   // target grid of the weight-gradient kernel
+// target grid of the weight-gradient kernel: two blocks per CU (16 -> 16 channels at 64^3:
+// 13 us with two bricks each, 16.5 with one block per CU and four)
+constexpr int kWgradBlocks = 512;
 // blocks that a large convolution is dealt to: what is resident at once (four per CU, two
 // with slices of 32 channels, by LDS), in one round
 constexpr int kConvBlocks = 1024, kConvBlocks32 = 512;
@@ -58,6 +59,8 @@ struct Layer {
     int nchunk_t, ntile_t; // backward-data GEMM (0 tiles: not needed)
     u32x4 *wf, *wt;       // packed weights
     float *bias;          // FP32 copy of the biases
+    int level;            // level of the network
+    float *part;          // training: partial sums of the weight gradient
 };
 
 // Channel slice of the K order: the largest of 32, 16, 8 dividing both inputs.
@@ -101,32 +104,27 @@ void make_layer(Layer &ly, int cin, int cout, int c1, int c2, bool need_bwd_data
 
 size_t packed_bytes(int ntile, int nchunk) { return (size_t)ntile * nchunk * 64 * sizeof(u32x4); }
 
-// Split of the weight-gradient reduction over cells for one layer.
+// Split of the weight-gradient reduction over cells for one layer: ranges of bricks.
 struct WSplit {
-    int cot, cit, nsplit, steps, bricks;
+    int cot, cit, nsplit, bricks, per;
 };
 
-bool brick_ok(int n) { return n >= 16 && n % 16 == 0; }
+// cells of a brick along z: 16 where that divides n, else 8 (fewer cells past the grid)
+int brick_z(int n) { return n % 16 == 0 ? 16 : 8; }
 
-// Cells of one weight-gradient launch are split into nsplit ranges: 32-cell
-// steps (general kernel) or 4 x 4 x 16 bricks (brick kernel, brick = true).
-WSplit wsplit(int cin_pad, int cout, int n, bool brick)
+WSplit wsplit(int cin_pad, int cout, int n)
 {
     WSplit w;
-    const int64_t V = (int64_t)n * n * n;
     w.cot = ceil_div(cout, 16);
     w.cit = ceil_div(cin_pad, 16);
-    const int64_t units = brick ? V / 256 : (V + 31) / 32;
-    int ns = ceil_div(kWgradBlocks, (int64_t)w.cot * w.cit);
-    ns = std::max(1, std::min<int>(ns, brick ? (int)units : ceil_div(units, 4)));
-    const int per = ceil_div(units, ns);
-    w.nsplit = ceil_div(units, per);
-    w.steps = brick ? 0 : per;
-    w.bricks = brick ? per : 0;
+    w.bricks = ceil_div(n, 4) * (brick_z(n) == 16 ? ceil_div(n, 4) * ceil_div(n, 16) : ceil_div(n, 8) * ceil_div(n, 8));
+    const int ns = std::min(w.bricks, std::max(1, ceil_div(kWgradBlocks, (int64_t)w.cot * w.cit)));
+    w.per = ceil_div(w.bricks, ns);
+    w.nsplit = ceil_div(w.bricks, w.per);
     return w;
 }
 
-size_t wsplit_floats(const WSplit &w) { return (size_t)w.nsplit * w.cot * 16 * w.cit * 16 * 27; }
+size_t wsplit_bytes(const WSplit &w) { return (size_t)w.nsplit * w.cot * w.cit * kWgtTile * sizeof(float); }
 
 mg_status check_config(const nn_config *c)
 {
@@ -162,7 +160,6 @@ struct nn_ctx {
     float *out;
     u16 *dzH, *dzA, *dzB;
     float *skipg[4], *upg, *pg;
-    float *part, *partb;
     double *dpart;
     double *hpin;
     const u16 *last_in;
@@ -188,12 +185,15 @@ void plan(nn_ctx *c)
         const int cin = l == 0 ? g.c_in : g.ch[l - 1];
         make_layer(c->layer[k++], cin, g.ch[l], l == 0 ? 8 : cin, 0, l > 0, off);
         make_layer(c->layer[k++], g.ch[l], g.ch[l], g.ch[l], 0, true, off);
+        c->layer[k - 2].level = c->layer[k - 1].level = l;
     }
     for (int l = c->L - 2; l >= 0; l--) {
         make_layer(c->layer[k++], g.ch[l] + g.ch[l + 1], g.ch[l], g.ch[l], g.ch[l + 1], true, off);
         make_layer(c->layer[k++], g.ch[l], g.ch[l], g.ch[l], 0, true, off);
+        c->layer[k - 2].level = c->layer[k - 1].level = l;
     }
     make_layer(c->layer[k++], g.ch[0], g.c_out, g.ch[0], 0, true, off);
+    c->layer[k - 1].level = 0;
     c->nlayers = k;
     c->nparams = off;
 }
@@ -207,6 +207,7 @@ void carve(nn_ctx *c, Carver &cv)
         ly.wf = (u32x4 *)cv.take(packed_bytes(ly.ntile, ly.nchunk));
         ly.wt = ly.ntile_t ? (u32x4 *)cv.take(packed_bytes(ly.ntile_t, ly.nchunk_t)) : nullptr;
         ly.bias = (float *)cv.take((size_t)ly.cout * sizeof(float));
+        ly.part = c->training ? (float *)cv.take(wsplit_bytes(wsplit(ly.cin_pad, ly.cout, c->nl[ly.level]))) : nullptr;
     }
     for (int l = 0; l < L; l++) {
         const size_t bytes = (size_t)c->V[l] * g.ch[l] * 2;
@@ -228,7 +229,7 @@ void carve(nn_ctx *c, Carver &cv)
     c->dpart = (double *)cv.take(nd * sizeof(double));
     if (!c->training) {
         c->dzH = c->dzA = c->dzB = nullptr;
-        c->upg = c->pg = c->part = c->partb = nullptr;
+        c->upg = c->pg = nullptr;
         for (int l = 0; l < 4; l++) c->skipg[l] = nullptr;
         return;
     }
@@ -245,20 +246,6 @@ void carve(nn_ctx *c, Carver &cv)
         c->skipg[l] = (l <= L - 2) ? (float *)cv.take((size_t)c->V[l] * g.ch[l] * 4) : nullptr;
     c->upg = up ? (float *)cv.take(up * 4) : nullptr;
     c->pg = pg ? (float *)cv.take(pg * 4) : nullptr;
-    size_t pf = 0, pb = 0;
-    for (int l = 0; l < L; l++) {
-        // every layer of level l runs its weight gradient on V[l] cells
-        for (int k = 0; k < c->nlayers; k++) {
-            const Layer &ly = c->layer[k];
-            for (int br = 0; br < 2; br++) {
-                const WSplit w = wsplit(ly.cin_pad, ly.cout, c->nl[l], br == 1 && brick_ok(c->nl[l]));
-                pf = std::max(pf, wsplit_floats(w));
-                pb = std::max(pb, (size_t)w.nsplit * w.cot * 16);
-            }
-        }
-    }
-    c->part = (float *)cv.take(pf * 4);
-    c->partb = (float *)cv.take(pb * 4);
 }
 
 // ---- launchers ----------------------------------------------------------------------
@@ -314,7 +301,7 @@ void launch_conv(hipStream_t s, const Layer &ly, bool transposed, int n, const u
     a.zref1 = o1.zref;
     a.zref2 = o2.zref;
     a.zout1 = o1.zout;
-    const bool z16 = n % 16 == 0;
+    const bool z16 = brick_z(n) == 16;
     if (a.ko.cs == 32)
         z16 ? launch_conv_slice<32, 16>(s, a) : launch_conv_slice<32, 8>(s, a);
     else if (a.ko.cs == 16)
@@ -323,48 +310,39 @@ void launch_conv(hipStream_t s, const Layer &ly, bool transposed, int n, const u
         z16 ? launch_conv_slice<8, 16>(s, a) : launch_conv_slice<8, 8>(s, a);
 }
 
-// weight and bias gradients of layer ly (input [in1, in2], output gradient dy)
-void launch_wgrad_to(hipStream_t s, const Layer &ly, int n, const u16 *in1, int c1, int act1, const u16 *in2,
-                     int c2, int act2, const u16 *dy, int cy, float *part, float *partb, float *gw, float *gb,
-                     int accumulate)
+// partial weight and bias gradients of layer ly (input [in1, in2], output gradient dy)
+void launch_wgrad(hipStream_t s, const Layer &ly, int n, const u16 *in1, int c1, int act1, const u16 *in2, int c2,
+                  const u16 *dy, int cy)
 {
-    const bool brick = brick_ok(n) && !act1 && !act2;
-    const WSplit w = wsplit(ly.cin_pad, ly.cout, n, brick);
+    const WSplit w = wsplit(ly.cin_pad, ly.cout, n);
     WgtArgs a;
     a.in1 = in1;
     a.in2 = in2;
     a.c1 = c1;
     a.c2 = in2 ? c2 : 0;
     a.act1 = act1;
-    a.act2 = act2;
+    a.act2 = 0;
     a.dy = dy;
     a.cy = cy;
-    a.cout = ly.cout;
     a.n = n;
-    a.steps_per_split = w.steps;
+    a.bricks = w.bricks;
+    a.per_split = w.per;
     a.cot = w.cot;
     a.cit = w.cit;
-    a.part = part;
-    a.partb = partb;
-    if (brick) {
-        WgtBrick wb;
-        wb.a = a;
-        wb.a.cit = w.cit;
-        wb.bricks_per_split = w.bricks;
-        hipLaunchKernelGGL(k_conv3_wgrad_brick, dim3(w.cot, w.cit, w.nsplit), dim3(kNBlock), 0, s, wb);
-    } else {
-        hipLaunchKernelGGL(k_conv3_wgrad, dim3(w.cot, w.cit, w.nsplit), dim3(kNBlock), 0, s, a);
-    }
-    const int64_t nw = (int64_t)ly.cout * ly.cin * 27;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(ceil_div(nw + ly.cout, 16)), dim3(kNBlock), 0, s, (const float *)part,
-                       (const float *)partb, w.nsplit, w.cot, w.cit, ly.cout, ly.cin, gw, gb, accumulate);
+    a.part = ly.part;
+    const dim3 grid((unsigned)w.cot, (unsigned)w.cit, (unsigned)w.nsplit);
+    if (brick_z(n) == 16)
+        hipLaunchKernelGGL(k_conv3_wgrad<16>, grid, dim3(kNBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_conv3_wgrad<8>, grid, dim3(kNBlock), 0, s, a);
 }
 
-void launch_wgrad(hipStream_t s, const Layer &ly, int n, const u16 *in1, int c1, int act1, const u16 *in2, int c2,
-                  int act2, const u16 *dy, int cy, float *part, float *partb, float *grad, int accumulate)
+// sums of the partial gradients of `count` layers, added to or stored in gw, gb
+void add_sum(WgtSums &t, int &blocks, const Layer &ly, int n, float *gw, float *gb)
 {
-    launch_wgrad_to(s, ly, n, in1, c1, act1, in2, c2, act2, dy, cy, part, partb, grad + ly.w_off, grad + ly.b_off,
-                    accumulate);
+    const WSplit w = wsplit(ly.cin_pad, ly.cout, n);
+    t.l[t.count++] = WgtSum{ly.part, gw, gb, blocks, w.nsplit, w.cot, w.cit, ly.cin, ly.cout};
+    blocks += w.cot * w.cit * (kWgtTile / 64);
 }
 
 void pack_layer(hipStream_t s, const Layer &ly, const float *params)
@@ -535,7 +513,7 @@ void backward(nn_ctx *c, float *grad)
     const u16 *top_z = L >= 2 ? c->zdb[0] : c->zb[0];
     {
         const Layer &lh = c->layer[head_layer(c)];
-        launch_wgrad(s, lh, c->nl[0], top_a, g.ch[0], 0, nullptr, 0, 0, c->dzH, 8, c->part, c->partb, grad, 1);
+        launch_wgrad(s, lh, c->nl[0], top_a, g.ch[0], 0, nullptr, 0, c->dzH, 8);
         launch_conv(s, lh, true, c->nl[0], c->dzH, lh.cout8, 0, nullptr, 0, 0, nullptr,
                     dsilu_out(g.ch[0], c->dzB, top_z), none);
     }
@@ -543,11 +521,10 @@ void backward(nn_ctx *c, float *grad)
     for (int l = 0; l <= L - 2; l++) {
         const int n = c->nl[l];
         const Layer &da = c->layer[dec_layer(c, l, 0)], &db = c->layer[dec_layer(c, l, 1)];
-        launch_wgrad(s, db, n, c->ada[l], g.ch[l], 0, nullptr, 0, 0, c->dzB, g.ch[l], c->part, c->partb, grad, 1);
+        launch_wgrad(s, db, n, c->ada[l], g.ch[l], 0, nullptr, 0, c->dzB, g.ch[l]);
         launch_conv(s, db, true, n, c->dzB, g.ch[l], 0, nullptr, 0, 0, nullptr, dsilu_out(g.ch[l], c->dzA, c->zda[l]),
                     none);
-        launch_wgrad(s, da, n, c->ab[l], g.ch[l], 0, c->upb[l], g.ch[l + 1], 0, c->dzA, g.ch[l], c->part, c->partb,
-                     grad, 1);
+        launch_wgrad(s, da, n, c->ab[l], g.ch[l], 0, c->upb[l], g.ch[l + 1], c->dzA, g.ch[l]);
         launch_conv(s, da, true, n, c->dzA, g.ch[l], 0, nullptr, 0, 0, nullptr, f32_out(g.ch[l], c->skipg[l]),
                     f32_out(g.ch[l + 1], c->upg));
         const u16 *zref = (l + 1 == L - 1) ? c->zb[L - 1] : c->zdb[l + 1];
@@ -559,20 +536,28 @@ void backward(nn_ctx *c, float *grad)
     for (int l = L - 1; l >= 0; l--) {
         const int n = c->nl[l];
         const Layer &la = c->layer[enc_layer(l, 0)], &lb = c->layer[enc_layer(l, 1)];
-        launch_wgrad(s, lb, n, c->aa[l], g.ch[l], 0, nullptr, 0, 0, c->dzB, g.ch[l], c->part, c->partb, grad, 1);
+        launch_wgrad(s, lb, n, c->aa[l], g.ch[l], 0, nullptr, 0, c->dzB, g.ch[l]);
         launch_conv(s, lb, true, n, c->dzB, g.ch[l], 0, nullptr, 0, 0, nullptr, dsilu_out(g.ch[l], c->dzA, c->za[l]),
                     none);
         if (l == 0) {
-            launch_wgrad(s, la, n, c->last_in, 8, 0, nullptr, 0, 0, c->dzA, g.ch[0], c->part, c->partb, grad, 1);
+            launch_wgrad(s, la, n, c->last_in, 8, 0, nullptr, 0, c->dzA, g.ch[0]);
             break;
         }
-        launch_wgrad(s, la, n, c->pl[l], g.ch[l - 1], 0, nullptr, 0, 0, c->dzA, g.ch[l], c->part, c->partb, grad,
-                     1);
+        launch_wgrad(s, la, n, c->pl[l], g.ch[l - 1], 0, nullptr, 0, c->dzA, g.ch[l]);
         launch_conv(s, la, true, n, c->dzA, g.ch[l], 0, nullptr, 0, 0, nullptr, f32_out(g.ch[l - 1], c->pg), none);
         const int64_t e = c->V[l - 1] * g.ch[l - 1];
         hipLaunchKernelGGL(k_pool_adjoint_dsilu, dim3(nblk(e)), dim3(kNBlock), 0, s, (const float *)c->pg,
                            (const float *)c->skipg[l - 1], g.ch[l - 1], n, (const u16 *)c->zb[l - 1], c->dzB);
     }
+    WgtSums sums;
+    sums.count = 0;
+    sums.accumulate = 1;
+    int blocks = 0;
+    for (int k = 0; k < c->nlayers; k++) {
+        const Layer &ly = c->layer[k];
+        add_sum(sums, blocks, ly, c->nl[ly.level], grad + ly.w_off, grad + ly.b_off);
+    }
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)blocks), dim3(kNBlock), 0, s, sums);
 }
 
 mg_status sync_status(hipStream_t s)
@@ -822,24 +807,17 @@ Layer op_layer(int cin, int cout)
 }
 
 struct OpScratch {
-    size_t wf, wt, part, partb, total;
+    size_t wf, wt, part, total;
 };
 
 OpScratch op_scratch(int32_t cin, int32_t cout, int32_t n)
 {
     const Layer ly = op_layer(cin, cout);
-    size_t pf = 0, pb = 0;
-    for (int br = 0; br < 2; br++) {
-        const WSplit w = wsplit(ly.cin_pad, ly.cout, n, br == 1 && brick_ok(n));
-        pf = std::max(pf, wsplit_floats(w));
-        pb = std::max(pb, (size_t)w.nsplit * w.cot * 16);
-    }
     OpScratch o;
     o.wf = 0;
     o.wt = align_up(packed_bytes(ly.ntile, ly.nchunk), 256);
     o.part = o.wt + align_up(packed_bytes(ly.ntile_t, ly.nchunk_t), 256);
-    o.partb = o.part + align_up(pf * 4, 256);
-    o.total = o.partb + align_up(pb * 4, 256);
+    o.total = o.part + align_up(wsplit_bytes(wsplit(ly.cin_pad, ly.cout, n)), 256);
     return o;
 }
 
@@ -904,9 +882,15 @@ mg_status nn_conv3_backward_weight(int32_t n, int32_t cin, int32_t cout, const u
     if (scratch_bytes < o.total || ((uintptr_t)d_scratch % 256) != 0) return MG_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     Layer ly = op_layer(cin, cout);
-    float *part = (float *)((char *)d_scratch + o.part), *partb = (float *)((char *)d_scratch + o.partb);
-    // the reduction overwrites dW (cout*cin*27) and db (cout)
-    launch_wgrad_to(s, ly, n, d_x, cin, act, nullptr, 0, 0, d_dy, ly.cout8, part, partb, d_dw, d_db, 0);
+    ly.part = (float *)((char *)d_scratch + o.part);
+    launch_wgrad(s, ly, n, d_x, cin, act, nullptr, 0, d_dy, ly.cout8);
+    // the sums overwrite dW (cout*cin*27) and db (cout)
+    WgtSums sums;
+    sums.count = 0;
+    sums.accumulate = 0;
+    int blocks = 0;
+    add_sum(sums, blocks, ly, n, d_dw, d_db);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)blocks), dim3(kNBlock), 0, s, sums);
     return hip_ok();
 }
 

@@ -278,7 +278,8 @@ __device__ __forceinline__ int halo_at(int p, int n) { return wrapn(min(p, n), n
 struct SliceSrc {
     const u16 *p;
     int cs, act;
-    __device__ __forceinline__ SliceSrc(const ConvArgs &a, int cb)
+    template <class Args>
+    __device__ __forceinline__ SliceSrc(const Args &a, int cb)
     {
         const bool one = cb < a.c1;
         p = one ? a.in1 + cb : a.in2 + (cb - a.c1);
@@ -500,312 +501,175 @@ __global__ void __launch_bounds__(kNBlock, CS == 32 ? 2 : 4) k_conv3_stream(Conv
 
 // ---- weight gradient ------------------------------------------------------------------
 //
-// dW[co][ci][t] = sum_v dy[v][co] a[v + d_t][ci]: an MFMA with M = output
-// channels, N = input channels, K = cells (32 per step, 8 per lane group).
-// Block (co tile, ci tile, split) sums the cells of its split (waves take
-// every fourth step), the waves' partial tiles are added in LDS in a fixed
-// order and the block writes its partial [co][ci][27] (and the bias partial
-// sum_v dy[v][co] when it is the first ci tile) for a deterministic reduction.
+// dW[co][ci][t] = sum_v dy[v][co] a[v + d_t][ci]: an MFMA with M = input channels,
+// N = output channels, K = cells (32 per step).  Block (co tile, ci tile, split) sums
+// the cells of a range of bricks; its partial sums [tap][co][ci] are added over the
+// splits in a fixed order afterwards.  Tap 27 is the bias (the same product with ones).
+//
+// A brick's halo and output gradients are staged as they are, channels last, and read
+// with transposing LDS loads: lanes 16 g .. 16 g + 15 read the 16 channels of four
+// consecutive cells (128 contiguous bytes) and lane 16 g + i receives channel i of the
+// four.  The waves split the taps (seven each), not the cells: no sums between waves
+// are left, and every wave keeps 7 accumulators instead of 27.  Bound by LDS reads
+// (27 times the staged bytes) and their latency; 16 -> 16 channels at 64^3 49 -> 13 us,
+// 64 -> 64 at 8^3 102 -> 6.3 us, against operands turned around while staging (and
+// formed from single values in global memory at 8^3).
 
 struct WgtArgs {
     const u16 *in1, *in2;
     int c1, c2, act1, act2; // layer input as in ConvArgs
     const u16 *dy;          // output gradient, BF16, stride cy
-    int cy, cout;           // stride and real output channels
+    int cy;
     int n;
-    int steps_per_split;    // 32-cell steps per split
+    int bricks, per_split;
     int cot, cit;           // co / ci tiles of the layer
-    float *part;            // [split][cot*16][cit*16][27]
-    float *partb;           // [split][cot*16]
+    float *part;            // [split][co tile][ci tile][28][16 co][16 ci]
 };
 
-__global__ void __launch_bounds__(kNBlock) k_conv3_wgrad(WgtArgs a)
+constexpr int kWgtTile = 28 * 256; // partial sums of one pair of tiles
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// four cells (32 bytes apart) of one channel; see above
+__device__ __forceinline__ u32x2 read_turned(const char *p)
 {
-    __shared__ float red[16 * 16 * 27 + 16];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane >> 4, r = lane & 15;
-    const int n = a.n;
-    const int64_t V = (int64_t)n * n * n;
-    const int64_t nsteps = (V + 31) / 32;
-    const int cotile = blockIdx.x, citile = blockIdx.y, split = blockIdx.z;
-    const int co = cotile * 16 + r, ci = citile * 16 + r;
-    const int cin = a.c1 + a.c2;
-    const u16 *src = nullptr;
-    int cs = 0, c0 = 0, act = 0;
-    if (ci < a.c1) {
-        src = a.in1;
-        cs = a.c1;
-        c0 = ci;
-        act = a.act1;
-    } else if (ci < cin) {
-        src = a.in2;
-        cs = a.c2;
-        c0 = ci - a.c1;
-        act = a.act2;
-    }
-    f32x4 acc[27];
-#pragma unroll
-    for (int t = 0; t < 27; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float dbias = 0.0f;
-    const int64_t s0 = (int64_t)split * a.steps_per_split;
-    int64_t s1 = s0 + a.steps_per_split;
-    if (s1 > nsteps) s1 = nsteps;
-    for (int64_t s = s0 + wave; s < s1; s += kNBlock / 64) {
-        const int64_t v0 = s * 32 + 8 * g;
-        int px[8], py[8], pz[8];
-        bool ok[8];
-        float av[8];
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            int64_t v = v0 + j;
-            ok[j] = v < V;
-            if (!ok[j]) v = 0;
-            const unsigned uv = (unsigned)v, un = (unsigned)n, t = uv / un; // n^3 < 2^32
-            pz[j] = (int)(uv - t * un);
-            py[j] = (int)(t % un);
-            px[j] = (int)(t / un);
-            av[j] = (ok[j] && co < a.cout) ? bf2f(a.dy[v * a.cy + co]) : 0.0f;
-            dbias += av[j];
-        }
-        const u32x4 A = pack8(av); // exact: av are BF16 values
-#pragma unroll 1
-        for (int t = 0; t < 27; t++) {
-            const int dx = t / 9 - 1, dyy = (t / 3) % 3 - 1, dz = t % 3 - 1;
-            float bv[8];
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                float x = 0.0f;
-                if (src && ok[j]) {
-                    const int64_t v = ((int64_t)wrapn(px[j] + dx, n) * n + wrapn(py[j] + dyy, n)) * n +
-                                      wrapn(pz[j] + dz, n);
-                    x = bf2f(src[v * cs + c0]);
-                    if (act) x = bf2f((u16)f2bf(silu(x)));
-                }
-                bv[j] = x;
-            }
-            acc[t] = mfma(A, pack8(bv), acc[t]);
-        }
-    }
-    // bias: lanes with the same r hold the same co; sum the four lane groups
-    dbias += __shfl_xor(dbias, 16, 64);
-    dbias += __shfl_xor(dbias, 32, 64);
-    // add the waves' tiles in LDS in a fixed order
-    for (int w = 0; w < kNBlock / 64; w++) {
-        if (wave == w) {
-#pragma unroll
-            for (int t = 0; t < 27; t++)
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int idx = ((4 * g + i) * 16 + r) * 27 + t;
-                    red[idx] = (w == 0 ? 0.0f : red[idx]) + acc[t][i];
-                }
-            if (g == 0) red[16 * 16 * 27 + r] = (w == 0 ? 0.0f : red[16 * 16 * 27 + r]) + dbias;
-        }
-        __syncthreads();
-    }
-    const int64_t ldco = (int64_t)a.cit * 16 * 27;
-    float *dst = a.part + (int64_t)split * a.cot * 16 * ldco;
-    for (int e = threadIdx.x; e < 16 * 16 * 27; e += kNBlock) {
-        const int rco = e / (16 * 27), rem = e - rco * 16 * 27;
-        dst[(int64_t)(cotile * 16 + rco) * ldco + (int64_t)citile * 16 * 27 + rem] = red[e];
-    }
-    if (citile == 0 && threadIdx.x < 16)
-        a.partb[(int64_t)split * a.cot * 16 + cotile * 16 + threadIdx.x] = red[16 * 16 * 27 + threadIdx.x];
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)p));
 }
 
-// Brick version (n a multiple of 16), ci tiles of 16 channels.  Per brick of
-// 4 x 4 x 16 cells the block stages dy of its co tile transposed,
-// dyT[co][cell], and the input halo transposed as three copies shifted by the
-// z offset, hT[dz][ci][x][y][z'] = a(x, y, z' + dz) (z' = 0..15): every A and
-// B operand of the MFMA (8 consecutive z cells of one channel) is then one
-// aligned 16-byte LDS read.  Row strides are padded so that the 16 lanes of a
-// read hit distinct banks.  Blocks take contiguous ranges of bricks.
-constexpr int kHX = 6, kHY = 6, kHZ = 18;
-constexpr int kDyStride = 256 + 8;          // u16 per co row of dyT
-constexpr int kHtStride = kHX * kHY * 16 + 8; // u16 per ci plane of one hT copy
+template <int BZ>
+__global__ void __launch_bounds__(kNBlock, 2) k_conv3_wgrad(WgtArgs a)
+{
+    using B = Brick<BZ, 4, 2>;
+    constexpr int BY = B::BY, kCells = 256;
+    __shared__ u32x4 halo[B::kTile], dys[2 * kCells];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 4, i = lane & 15, o = tid & 1;
+    const int n = a.n, nbz = (n + BZ - 1) / BZ, nby = (n + BY - 1) / BY;
+    const int first = blockIdx.z * a.per_split, last = min(a.bricks, first + a.per_split);
+    // the octet this thread stages (absent ones are zero)
+    const bool have = (int)blockIdx.y * 16 + 8 * o < a.c1 + a.c2, haved = (int)blockIdx.x * 16 + 8 * o < a.cy;
+    const SliceSrc src(a, have ? blockIdx.y * 16 + 8 * o : 0);
+    const u16 *dsrc = a.dy + (haved ? blockIdx.x * 16 + 8 * o : 0);
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    u32x4 stg[B::NE], dst[2];
+    auto load = [&](int bi) {
+        const int t = bi / nbz, bx = t / nby;
+        const int x0 = bx * B::BX, y0 = (t - bx * nby) * BY, z0 = (bi - t * nbz) * BZ;
+#pragma unroll
+        for (int k = 0; k < B::NE; k++) {
+            int hx, hy, hz;
+            B::split(B::cell(tid, k), hx, hy, hz);
+            const int c = (halo_at(x0 + hx - 1, n) * n + halo_at(y0 + hy - 1, n)) * n + halo_at(z0 + hz - 1, n);
+            const u32x4 v = *(const u32x4 *)(src.p + (int64_t)c * src.cs);
+            stg[k] = have ? v : zero;
+        }
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const int c = (tid >> 1) + k * (kNBlock / 2);
+            const int x = x0 + (c >> 6), y = y0 + (c / BZ) % BY, z = z0 + c % BZ;
+            const bool in = haved && max(x, max(y, z)) < n; // cells past the grid add nothing
+            const u32x4 v = *(const u32x4 *)(dsrc + (in ? ((int64_t)x * n + y) * n + z : 0) * a.cy);
+            dst[k] = in ? v : zero;
+        }
+        if (src.act) {
+#pragma unroll
+            for (int k = 0; k < B::NE; k++) stg[k] = silu8(stg[k]);
+        }
+    };
+    // lane's piece of the 16 cells of a tile row: cell 4 g + i / 4 of them
+    const int q = 4 * g + (i >> 2);
+    const char *db = (const char *)dys + q * 32 + (i & 3) * 8;
+    const char *hb[7];
+#pragma unroll
+    for (int t = 0; t < 7; t++) {
+        const int tap = min(7 * wave + t, 26);
+        const int c = ((tap / 9) * B::HY + tap / 3 % 3 + q / BZ) * B::HZ + tap % 3 + q % BZ;
+        hb[t] = (const char *)halo + c * 32 + (i & 3) * 8;
+    }
+    constexpr uint32_t kOnes = 0x3f803f80u;
+    f32x4 acc[7];
+#pragma unroll
+    for (int t = 0; t < 7; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    load(first);
+    for (int bi = first; bi < last; bi++) {
+        B::store(halo, stg);
+        dys[tid] = dst[0];
+        dys[tid + kNBlock] = dst[1];
+        __syncthreads();
+        if (bi + 1 < last) load(bi + 1);
+        static_for<8>([&](auto sc) {
+            constexpr int r0 = 2 * decltype(sc)::value, r1 = r0 + 1; // tile rows: x = r / 4, tile r % 4 of y
+            constexpr int h0 = ((r0 / 4) * B::HY + (r0 % 4) * B::MY) * B::HZ * 32;
+            constexpr int h1 = ((r1 / 4) * B::HY + (r1 % 4) * B::MY) * B::HZ * 32;
+            const u32x2 d0 = read_turned(db + r0 * 512), d1 = read_turned(db + r1 * 512);
+            const u32x4 dv = {d0[0], d0[1], d1[0], d1[1]};
+#pragma unroll
+            for (int t = 0; t < 7; t++) {
+                const u32x2 v0 = read_turned(hb[t] + h0), v1 = read_turned(hb[t] + h1);
+                u32x4 av = {v0[0], v0[1], v1[0], v1[1]};
+                if (t == 6) {
+#pragma unroll
+                    for (int j = 0; j < 4; j++) av[j] = wave == 3 ? kOnes : av[j];
+                }
+                acc[t] = mfma(av, dv, acc[t]);
+            }
+        });
+        __syncthreads(); // the staged brick is consumed
+    }
+    float *out = a.part + (((int64_t)blockIdx.z * a.cot + blockIdx.x) * a.cit + blockIdx.y) * kWgtTile;
+#pragma unroll
+    for (int t = 0; t < 7; t++) *(f32x4 *)(out + (7 * wave + t) * 256 + i * 16 + 4 * g) = acc[t];
+}
 
-struct WgtBrick {
-    WgtArgs a;
-    int bricks_per_split;
+// gw[(co*cin + ci)*27 + t] (+)= sum_s part[s][co][ci][t], gb[co] (+)= tap 27, for all
+// layers of a backward pass in one launch (one per layer left most of the chip idle
+// and cost 4.7 us at least, 112 us of a training step at 64^3, now 41 us).  A block reduces 16
+// quads of one layer with 16 threads each (thread k sums splits k, k + 16, ...) in FP64; the
+// 16 sums are added in a fixed order.
+constexpr int kMaxLayers = 15; // 4 levels: 8 encoder + 6 decoder convolutions + head
+
+struct WgtSum {
+    const float *part;
+    float *gw, *gb;
+    int first; // first block
+    int nsplit, cot, cit, cin, cout;
+};
+struct WgtSums {
+    WgtSum l[kMaxLayers];
+    int count, accumulate;
 };
 
-__global__ void __launch_bounds__(kNBlock) k_conv3_wgrad_brick(WgtBrick wb)
+__global__ void __launch_bounds__(kNBlock) k_wgrad_reduce(WgtSums w)
 {
-    __shared__ __attribute__((aligned(16))) u16 dyT[16 * kDyStride];
-    __shared__ __attribute__((aligned(16))) u16 hT[3 * 16 * kHtStride];
-    const WgtArgs &a = wb.a;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane >> 4, r = lane & 15;
-    const int n = a.n;
-    const int nbz = n / 16, nby = n / 4;
-    const int nbricks = nbz * nby * (n / 4);
-    const int cotile = blockIdx.x, citile = blockIdx.y, split = blockIdx.z;
-    const int cin = a.c1 + a.c2;
-    // the ci tile's source: one input (tiles never straddle in1 / in2), octets present
-    const int cb = citile * 16;
-    const bool one = cb < a.c1;
-    const u16 *src = one ? a.in1 : a.in2;
-    const int cs = one ? a.c1 : a.c2, c0 = one ? cb : cb - a.c1;
-    const int nci8 = min(2, (min(cin, cb + 16) - cb) / 8); // 1 or 2 octets of real channels
-    const int nco8 = min(2, (a.cy - cotile * 16) / 8);
-    f32x4 acc[27];
-#pragma unroll
-    for (int t = 0; t < 27; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float dbias = 0.0f;
-    const int b0 = split * wb.bricks_per_split;
-    const int b1 = min(nbricks, b0 + wb.bricks_per_split);
-    for (int bi = b0; bi < b1; bi++) {
-        const int bz = bi % nbz, by = (bi / nbz) % nby, bx = bi / (nbz * nby);
-        const int x0 = bx * 4, y0 = by * 4, z0 = bz * 16;
-        // staging: threads 0..143 build the three shifted halo copies for one
-        // (x, y, z quad) from 6 consecutive halo cells; threads 144..207 the
-        // transposed dy of one (x, y, z quad); every LDS write is 8 bytes
-        // (4 consecutive z of one channel)
-        const int tid = threadIdx.x;
-        u32x4 ld[12];
-        int kind = 0, ix = 0, iy = 0, iq = 0;
-        if (tid < 144) {
-            kind = 1;
-            iq = tid & 3;
-            iy = (tid >> 2) % kHY;
-            ix = (tid >> 2) / kHY;
-            const int gx = wrapn(x0 + ix - 1, n), gy = wrapn(y0 + iy - 1, n);
-#pragma unroll
-            for (int k = 0; k < 6; k++) {
-                const int gz = wrapn(z0 + 4 * iq + k - 1, n);
-                const int64_t v = ((int64_t)gx * n + gy) * n + gz;
-#pragma unroll
-                for (int o = 0; o < 2; o++)
-                    ld[2 * k + o] = (o < nci8) ? *(const u32x4 *)(src + v * cs + c0 + o * 8) : u32x4{0u, 0u, 0u, 0u};
-            }
-        } else if (tid < 208) {
-            kind = 2;
-            const int t = tid - 144;
-            iq = t & 3;
-            iy = (t >> 2) & 3;
-            ix = t >> 4;
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const int64_t v = ((int64_t)(x0 + ix) * n + (y0 + iy)) * n + (z0 + 4 * iq + k);
-#pragma unroll
-                for (int o = 0; o < 2; o++)
-                    ld[2 * k + o] = (o < nco8) ? *(const u32x4 *)(a.dy + v * a.cy + cotile * 16 + o * 8)
-                                               : u32x4{0u, 0u, 0u, 0u};
-            }
-        }
-        __syncthreads(); // the previous brick's operands are consumed
-        if (kind == 1) {
-#pragma unroll
-            for (int c = 0; c < 16; c++) {
-                const int o = c >> 3, w = (c & 7) >> 1, hi = c & 1;
-                uint32_t h[6];
-#pragma unroll
-                for (int k = 0; k < 6; k++) h[k] = hi ? (ld[2 * k + o][w] >> 16) : (ld[2 * k + o][w] & 0xffffu);
-#pragma unroll
-                for (int d = 0; d < 3; d++) {
-                    // copy d holds z' = hz - d: z' = 4 iq + k' reads halo cell 4 iq + k' + d
-                    uint2 q;
-                    q.x = h[d] | (h[d + 1] << 16);
-                    q.y = h[d + 2] | (h[d + 3] << 16);
-                    *(uint2 *)&hT[(d * 16 + c) * kHtStride + (ix * kHY + iy) * 16 + 4 * iq] = q;
-                }
-            }
-        } else if (kind == 2) {
-#pragma unroll
-            for (int c = 0; c < 16; c++) {
-                const int o = c >> 3, w = (c & 7) >> 1, hi = c & 1;
-                const bool ok = cotile * 16 + c < a.cout;
-                uint32_t h[4];
-#pragma unroll
-                for (int k = 0; k < 4; k++)
-                    h[k] = ok ? (hi ? (ld[2 * k + o][w] >> 16) : (ld[2 * k + o][w] & 0xffffu)) : 0u;
-                uint2 q;
-                q.x = h[0] | (h[1] << 16);
-                q.y = h[2] | (h[3] << 16);
-                *(uint2 *)&dyT[c * kDyStride + (ix * 4 + iy) * 16 + 4 * iq] = q;
-            }
-        }
-        __syncthreads();
-        // wave: x row x0 + wave; K steps of 32 cells = rows (2s, 2s + 1) of y, all 16 z
-#pragma unroll
-        for (int s = 0; s < 2; s++) {
-            const int row = 2 * s + (g >> 1), zh = (g & 1) * 8;
-            const u32x4 A = *(const u32x4 *)&dyT[r * kDyStride + (wave * 4 + row) * 16 + zh];
-            if (citile == 0) {
-                float h[8];
-                unpack8(A, h);
-#pragma unroll
-                for (int j = 0; j < 8; j++) dbias += h[j];
-            }
-#pragma unroll
-            for (int t = 0; t < 27; t++) {
-                const int dx = t / 9, dy = (t / 3) % 3, dz = t % 3;
-                const u32x4 B =
-                    *(const u32x4 *)&hT[(dz * 16 + r) * kHtStride + ((wave + dx) * kHY + row + dy) * 16 + zh];
-                acc[t] = mfma(A, B, acc[t]);
-            }
-        }
-    }
-    // reduce the waves in LDS (reusing hT) in a fixed order and write the partial
-    float *red = (float *)hT; // 16*16*27 + 16 floats fit in hT
-    dbias += __shfl_xor(dbias, 16, 64);
-    dbias += __shfl_xor(dbias, 32, 64);
-    for (int w = 0; w < kNBlock / 64; w++) {
-        __syncthreads();
-        if (wave == w) {
-#pragma unroll
-            for (int t = 0; t < 27; t++)
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int idx = ((4 * g + i) * 16 + r) * 27 + t;
-                    red[idx] = (w == 0 ? 0.0f : red[idx]) + acc[t][i];
-                }
-            if (g == 0) red[16 * 16 * 27 + r] = (w == 0 ? 0.0f : red[16 * 16 * 27 + r]) + dbias;
-        }
-    }
-    __syncthreads();
-    const int64_t ldco = (int64_t)a.cit * 16 * 27;
-    float *dst = a.part + (int64_t)split * a.cot * 16 * ldco;
-    for (int e = threadIdx.x; e < 16 * 16 * 27; e += kNBlock) {
-        const int rco = e / (16 * 27), rem = e - rco * 16 * 27;
-        dst[(int64_t)(cotile * 16 + rco) * ldco + (int64_t)citile * 16 * 27 + rem] = red[e];
-    }
-    if (citile == 0 && threadIdx.x < 16)
-        a.partb[(int64_t)split * a.cot * 16 + cotile * 16 + threadIdx.x] = red[16 * 16 * 27 + threadIdx.x];
-}
-
-// grad[(co*cin + ci)*27 + t] (+)= sum_s part[s][co][ci][t]; gradb[co] (+)= sum_s partb[s][co].
-// A block reduces 16 values with 16 threads each (thread k sums splits
-// k, k + 16, ...); the 16 sums are added in a fixed order.
-__global__ void __launch_bounds__(kNBlock) k_wgrad_reduce(const float *part, const float *partb, int nsplit,
-                                                         int cot, int cit, int cout, int cin, float *grad,
-                                                         float *gradb, int accumulate)
-{
-    __shared__ float sh[16][17];
+    __shared__ double sh[16][64];
+    int li = 0;
+    while (li + 1 < w.count && (int)blockIdx.x >= w.l[li + 1].first) li++;
+    const WgtSum &l = w.l[li];
     const int el = threadIdx.x & 15, k = threadIdx.x >> 4;
-    const int64_t nw = (int64_t)cout * cin * 27;
-    const int64_t e = (int64_t)blockIdx.x * 16 + el;
-    const int64_t per = (int64_t)cot * 16 * cit * 16 * 27;
-    float s = 0.0f;
-    if (e < nw) {
-        const int co = (int)(e / ((int64_t)cin * 27));
-        const int rem = (int)(e - (int64_t)co * cin * 27);
-        const int ci = rem / 27, t = rem - ci * 27;
-        const int64_t off = ((int64_t)co * cit * 16 + ci) * 27 + t;
-        for (int q = k; q < nsplit; q += 16) s += part[q * per + off];
-    } else if (e < nw + cout) {
-        const int co = (int)(e - nw);
-        for (int q = k; q < nsplit; q += 16) s += partb[(int64_t)q * cot * 16 + co];
+    const int e = ((int)blockIdx.x - l.first) * 16 + el; // quad of [co tile][ci tile][28][16][4]
+    const int64_t per = (int64_t)l.cot * l.cit * kWgtTile;
+    double s[4] = {0., 0., 0., 0.};
+    for (int q = k; q < l.nsplit; q += 16) {
+        const f32x4 v = *(const f32x4 *)(l.part + q * per + 4 * e);
+#pragma unroll
+        for (int j = 0; j < 4; j++) s[j] += (double)v[j];
     }
-    sh[el][k] = s;
+#pragma unroll
+    for (int j = 0; j < 4; j++) sh[k][4 * el + j] = s[j];
     __syncthreads();
-    if (k == 0 && e < nw + cout) {
-        float t = 0.0f;
-        for (int q = 0; q < 16; q++) t += sh[el][q];
-        if (e < nw)
-            grad[e] = accumulate ? grad[e] + t : t;
-        else
-            gradb[e - nw] = accumulate ? gradb[e - nw] + t : t;
+    if (threadIdx.x >= 64) return;
+    double d = 0.0;
+    for (int q = 0; q < 16; q++) d += sh[q][threadIdx.x];
+    const float t = (float)d;
+    const int v = ((int)blockIdx.x - l.first) * 64 + threadIdx.x;
+    const int tile = v / kWgtTile, tap = v % kWgtTile >> 8;
+    const int co = tile / l.cit * 16 + (v >> 4 & 15), ci = tile % l.cit * 16 + (v & 15);
+    if (co >= l.cout) return;
+    if (tap == 27) {
+        if (ci == 0) l.gb[co] = w.accumulate ? l.gb[co] + t : t;
+    } else if (ci < l.cin) {
+        float *dst = l.gw + ((int64_t)co * l.cin + ci) * 27 + tap;
+        *dst = w.accumulate ? *dst + t : t;
     }
 }
 

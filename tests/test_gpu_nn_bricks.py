@@ -34,3 +34,22 @@ def test_convolution_on_any_side(n, cin, cout, act):
     err = np.abs(cf(y.cpu().numpy(), n) - ref).max() / np.sqrt(np.mean(ref ** 2))
     print(f"n={n} {cin}->{cout} act={act}: max err / rms = {err:.2e}", flush=True)
     assert err < (1e-2 if act else 1e-4)
+
+
+# cells past the grid in one or more directions, one and several bricks per block (from 257
+# bricks and tile pairs on), tiles of one octet, output channels that end inside a tile
+@pytest.mark.parametrize("n,cin,cout,act", [(1, 8, 5, False), (2, 16, 16, False), (7, 24, 8, True), (9, 16, 20, False),
+                                            (20, 40, 12, False), (16, 24, 33, False), (34, 16, 4, False),
+                                            (48, 8, 16, False), (40, 16, 24, True)])
+def test_weight_gradient_on_any_side(n, cin, cout, act):
+    rng = np.random.default_rng(10 * n + cin + cout)
+    x = bf(rng.standard_normal((cin, n, n, n)))
+    dy = np.zeros(((cout + 7) // 8 * 8, n, n, n))
+    dy[:cout] = bf(rng.standard_normal((cout, n, n, n)))
+    dW, db = gn.conv3_backward_weight(to_dev(cl(x), torch.bfloat16), to_dev(cl(dy), torch.bfloat16), n, cin,
+                                      cout, act)
+    _, rW, rb = nn.conv3_vjp(silu_bf(x) if act else x, np.zeros((cout, cin, 3, 3, 3)), np.zeros(cout), dy[:cout])
+    eW = np.abs(dW.cpu().numpy().reshape(rW.shape) - rW).max() / np.sqrt(np.mean(rW ** 2))
+    eb = np.abs(db.cpu().numpy() - rb).max() / np.sqrt(np.mean(rb ** 2))
+    print(f"n={n} {cin}->{cout} act={act}: dW {eW:.2e} db {eb:.2e}", flush=True)
+    assert eW < (1e-2 if act else 1e-4) and eb < 1e-4
