@@ -345,20 +345,20 @@ void add_sum(WgtSums &t, int &blocks, const Layer &ly, int n, float *gw, float *
     blocks += w.cot * w.cit * (kWgtTile / 64);
 }
 
-void pack_layer(hipStream_t s, const Layer &ly, const float *params)
+// Packs of a layer's weights: forward (which also copies the biases) and backward data.
+PackJob pack_forward(const Layer &ly, const float *W, const float *b)
 {
-    const float *W = params + ly.w_off;
-    const int64_t nf = (int64_t)ly.ntile * ly.nchunk * 64;
-    hipLaunchKernelGGL(k_pack_weights, dim3(nblk(nf)), dim3(kNBlock), 0, s, W, ly.cin, ly.cout, ly.ko, ly.nchunk,
-                       ly.ntile, 0, ly.wf);
-    if (ly.ntile_t) {
-        const int64_t nt = (int64_t)ly.ntile_t * ly.nchunk_t * 64;
-        hipLaunchKernelGGL(k_pack_weights, dim3(nblk(nt)), dim3(kNBlock), 0, s, W, ly.cin, ly.cout, ly.ko_t,
-                           ly.nchunk_t, ly.ntile_t, 1, ly.wt);
-    }
-    if (ly.bias)
-        (void)hipMemcpyAsync(ly.bias, params + ly.b_off, (size_t)ly.cout * sizeof(float), hipMemcpyDeviceToDevice,
-                             s);
+    return PackJob{W, ly.wf, b, ly.bias, ly.cin, ly.cout, ly.ko, ly.nchunk, ly.ntile, 0};
+}
+PackJob pack_transposed(const Layer &ly, const float *W)
+{
+    return PackJob{W, ly.wt, nullptr, nullptr, ly.cin, ly.cout, ly.ko_t, ly.nchunk_t, ly.ntile_t, 1};
+}
+void launch_pack(hipStream_t s, const PackJobs &jobs, int count)
+{
+    int64_t most = 1;
+    for (int k = 0; k < count; k++) most = std::max(most, (int64_t)jobs.j[k].ntile * jobs.j[k].nchunk * 64);
+    hipLaunchKernelGGL(k_pack_weights, dim3(nblk(most), (unsigned)count), dim3(kNBlock), 0, s, jobs);
 }
 
 mg_status hip_ok() { return hipPeekAtLastError() == hipSuccess ? MG_OK : MG_ERR_HIP; }
@@ -528,7 +528,7 @@ void backward(nn_ctx *c, float *grad)
         launch_conv(s, da, true, n, c->dzA, g.ch[l], 0, nullptr, 0, 0, nullptr, f32_out(g.ch[l], c->skipg[l]),
                     f32_out(g.ch[l + 1], c->upg));
         const u16 *zref = (l + 1 == L - 1) ? c->zb[L - 1] : c->zdb[l + 1];
-        const int64_t e = c->V[l + 1] * g.ch[l + 1];
+        const int64_t nc = c->nl[l + 1], e = nc * nc * ((nc + 1) / 2) * (g.ch[l + 1] / 4);
         hipLaunchKernelGGL(k_up_adjoint_dsilu, dim3(nblk(e)), dim3(kNBlock), 0, s, (const float *)c->upg,
                            g.ch[l + 1], c->nl[l + 1], zref, c->dzB);
     }
@@ -545,7 +545,7 @@ void backward(nn_ctx *c, float *grad)
         }
         launch_wgrad(s, la, n, c->pl[l], g.ch[l - 1], 0, nullptr, 0, c->dzA, g.ch[l]);
         launch_conv(s, la, true, n, c->dzA, g.ch[l], 0, nullptr, 0, 0, nullptr, f32_out(g.ch[l - 1], c->pg), none);
-        const int64_t e = c->V[l - 1] * g.ch[l - 1];
+        const int64_t e = c->V[l - 1] * (g.ch[l - 1] / 4);
         hipLaunchKernelGGL(k_pool_adjoint_dsilu, dim3(nblk(e)), dim3(kNBlock), 0, s, (const float *)c->pg,
                            (const float *)c->skipg[l - 1], g.ch[l - 1], n, (const u16 *)c->zb[l - 1], c->dzB);
     }
@@ -609,7 +609,14 @@ void nn_destroy(nn_ctx *c)
 mg_status nn_load_params(nn_ctx *c, const float *d_params)
 {
     if (!c || !d_params) return MG_ERR_INVALID;
-    for (int k = 0; k < c->nlayers; k++) pack_layer(c->s, c->layer[k], d_params);
+    PackJobs jobs;
+    int count = 0;
+    for (int k = 0; k < c->nlayers; k++) {
+        const Layer &ly = c->layer[k];
+        jobs.j[count++] = pack_forward(ly, d_params + ly.w_off, d_params + ly.b_off);
+        if (ly.ntile_t) jobs.j[count++] = pack_transposed(ly, d_params + ly.w_off);
+    }
+    launch_pack(c->s, jobs, count);
     return hip_ok();
 }
 
@@ -627,7 +634,7 @@ mg_status nn_mse(nn_ctx *c, const float *d_out, const uint16_t *d_target, double
     const unsigned nb = nblk(V * 8);
     hipLaunchKernelGGL(k_mse, dim3(nb), dim3(kNBlock), 0, c->s, d_out, d_target, c->cfg.c_out, V, c->dzH,
                        c->dpart);
-    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kNBlock), 0, c->s, (const double *)c->dpart, (int64_t)nb,
+    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kSumBlock), 0, c->s, (const double *)c->dpart, (int64_t)nb,
                        c->dpart + nb);
     if (hipMemcpyAsync(c->hpin, c->dpart + nb, sizeof(double), hipMemcpyDeviceToHost, c->s) != hipSuccess)
         return MG_ERR_HIP;
@@ -689,9 +696,9 @@ mg_status nn_moments(nn_ctx *c, const double *d_x, const double *d_y, int64_t co
     if (!c || !d_x || count < 0 || !h_out) return MG_ERR_INVALID;
     const int B = kMomentBlocks;
     hipLaunchKernelGGL(k_moments, dim3(B), dim3(kNBlock), 0, c->s, d_x, d_y, count, c->dpart);
-    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kNBlock), 0, c->s, (const double *)c->dpart, (int64_t)B,
+    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kSumBlock), 0, c->s, (const double *)c->dpart, (int64_t)B,
                        c->dpart + 2 * B);
-    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kNBlock), 0, c->s, (const double *)(c->dpart + B), (int64_t)B,
+    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kSumBlock), 0, c->s, (const double *)(c->dpart + B), (int64_t)B,
                        c->dpart + 2 * B + 1);
     if (hipMemcpyAsync(c->hpin, c->dpart + 2 * B, 2 * sizeof(double), hipMemcpyDeviceToHost, c->s) != hipSuccess)
         return MG_ERR_HIP;
@@ -841,9 +848,9 @@ mg_status nn_conv3_forward(int32_t n, int32_t cin, int32_t cout, const uint16_t 
     ly.wf = (u32x4 *)((char *)d_scratch + o.wf);
     ly.wt = nullptr;
     ly.ntile_t = 0;
-    const int64_t nf = (int64_t)ly.ntile * ly.nchunk * 64;
-    hipLaunchKernelGGL(k_pack_weights, dim3(nblk(nf)), dim3(kNBlock), 0, s, d_w, cin, cout, ly.ko, ly.nchunk,
-                       ly.ntile, 0, ly.wf);
+    PackJobs jobs;
+    jobs.j[0] = pack_forward(ly, d_w, nullptr);
+    launch_pack(s, jobs, 1);
     Out oy, none;
     oy.channels = cout;
     oy.mode = kEpStoreF32;
@@ -861,9 +868,9 @@ mg_status nn_conv3_backward_data(int32_t n, int32_t cin, int32_t cout, const uin
     hipStream_t s = (hipStream_t)stream;
     Layer ly = op_layer(cin, cout);
     ly.wt = (u32x4 *)((char *)d_scratch + o.wt);
-    const int64_t nt = (int64_t)ly.ntile_t * ly.nchunk_t * 64;
-    hipLaunchKernelGGL(k_pack_weights, dim3(nblk(nt)), dim3(kNBlock), 0, s, d_w, cin, cout, ly.ko_t, ly.nchunk_t,
-                       ly.ntile_t, 1, ly.wt);
+    PackJobs jobs;
+    jobs.j[0] = pack_transposed(ly, d_w);
+    launch_pack(s, jobs, 1);
     Out ox, none;
     ox.channels = cin;
     ox.mode = kEpStoreF32;

@@ -12,6 +12,7 @@ import torch
 from oracle import nn_oracle as nn
 from paper_2501_13046_amd import grtnn as gn
 from test_gpu_nn import bf, cf, cl, silu_bf, to_dev
+from test_gpu_nn import test_network_gradients as network_gradients
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +54,8 @@ def test_weight_gradient_on_any_side(n, cin, cout, act):
     eb = np.abs(db.cpu().numpy() - rb).max() / np.sqrt(np.mean(rb ** 2))
     print(f"n={n} {cin}->{cout} act={act}: dW {eW:.2e} db {eb:.2e}", flush=True)
     assert eW < (1e-2 if act else 1e-4) and eb < 1e-4
+
+
+# an odd coarse side: the upsampling's adjoint takes coarse cells in pairs along z
+def test_network_gradients_on_an_odd_coarse_side():
+    network_gradients(6, 2, (16, 32))
