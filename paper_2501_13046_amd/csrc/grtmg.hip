@@ -496,9 +496,10 @@ bool ragged_residual(int n) { return n % 2 == 0 && n >= 18 && (double)n * n * n 
 // psi kernels on bricks (mg_brick.hpp) from this side on (the wrapped overhang of a brick stays
 // inside grids of at least 18 cells per axis); rows of 64 cells where they divide the side,
 // else of 32.  Below, one thread per z pair: its single round of loads takes 3.0-4.7 us up to
-// 64^3 (FP32) where a brick's two rounds took 5.4-8.5; at 80^3 the brick is level with it (6.7
+// 64^3 (FP32) where a brick's two rounds took 5.4-8.5, and 72 overhangs bricks by a third (a
+// 72^3 solve 2.66 ms on bricks, 2.58 on pairs); at 80^3 the brick is level with it (6.7
 // against 6.2 us) and at 160^3 ahead (18.0 against 28.3).
-constexpr int kBrickMin = 72;
+constexpr int kBrickMin = 80;
 bool psi_bricks(int n) { return n % 2 == 0 && n >= kBrickMin; }
 bool brick_rows_64(int n) { return n % 64 == 0; }
 

@@ -1496,24 +1496,47 @@ __device__ __forceinline__ void block_sums(double v[NV], double (*part)[kGjWaves
     __syncthreads();
 }
 
-template <int BC, typename T>
+// E cells per thread (m <= E 1024).  Each cell's taps are in registers (their source cells, so
+// that no ghosts are written between the steps, and their weights).
+template <int BC, typename T, int E>
 __device__ __forceinline__ bool coarse_psi_krylov_block(const Geo &g, int m, const T *c, const T *r, T *x, double *vec,
                                                         double (*part)[kGjWaves])
 {
-    constexpr int E = kKrylovCpt;
     constexpr int NT = kGjWaves * kWave;
-    CoarseOp<BC, E> op;
-    op.init(g, m, c, threadIdx.x, NT);
-    for (int t = threadIdx.x; t < (g.n + 4) * (g.n + 4) * (g.n + 4); t += NT) vec[t] = 0.0;
-    double b[E];
+    int src[E][12];
+    double w[E][12], dg[E], b[E];
 #pragma unroll
-    for (int e = 0; e < E; e++) b[e] = op.own(e) ? (double)r[threadIdx.x + NT * e] : 0.0;
-    __syncthreads();
-    // y = A v for the owned cells
+    for (int e = 0; e < E; e++) {
+        const int q = threadIdx.x + NT * e;
+        if (q < m) {
+            coarse_taps<BC>(g, q, src[e], w[e]);
+            dg[e] = -90.0 * g.inv12h2 + (double)c[q];
+            b[e] = (double)r[q];
+        } else {
+#pragma unroll
+            for (int t = 0; t < 12; t++) {
+                src[e][t] = 0;
+                w[e][t] = 0.0;
+            }
+            dg[e] = 0.0;
+            b[e] = 0.0;
+        }
+    }
+    // y = A v for the owned cells (v staged in LDS by every thread first)
     auto apply = [&](const double (&v)[E], double (&y)[E]) {
-        op.put(vec, v);
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            const int q = threadIdx.x + NT * e;
+            if (q < m) vec[q] = v[e];
+        }
         __syncthreads();
-        op.get(vec, v, y);
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            double s = dg[e] * v[e];
+#pragma unroll
+            for (int t = 0; t < 12; t++) s += w[e][t] * vec[src[e][t]];
+            y[e] = s;
+        }
         __syncthreads();
     };
     double t3[3];
@@ -1772,7 +1795,8 @@ __device__ __forceinline__ void coarse_psi_eliminate(const Geo &g, int m, const 
 // which needs no barrier between its steps (125 cells: 58 us as a block of 16 waves); a system
 // the Krylov solve does not accept is eliminated (m <= 64) or raises the flag.  x keeps its
 // values when the flag is raised.  Called by every thread of a block of kGjWaves waves.
-template <int BC, typename T>
+// E: cells per thread of the block's solve.
+template <int BC, typename T, int E>
 __device__ __forceinline__ void coarse_psi_solve(const Geo &g, int m, const T *c, const T *r, T *x, double *flag,
                                                  CoarseScratch &cs)
 {
@@ -1789,7 +1813,7 @@ __device__ __forceinline__ void coarse_psi_solve(const Geo &g, int m, const T *c
             return;
         }
     }
-    if (!coarse_psi_krylov_block<BC, T>(g, m, c, r, x, cs.kr.vec, cs.kr.part) && threadIdx.x == 0) *flag = 1.0;
+    if (!coarse_psi_krylov_block<BC, T, E>(g, m, c, r, x, cs.kr.vec, cs.kr.part) && threadIdx.x == 0) *flag = 1.0;
 }
 
 template <int BC, typename T>
@@ -1800,7 +1824,7 @@ __global__ void __launch_bounds__(kGjWaves *kWave) k_coarse_psi(Geo g, int m, co
     r = zsh(r, g.zs);
     x = zsh(x, g.zs);
     flag = zsh(flag, g.zs);
-    coarse_psi_solve<BC, T>(g, m, c, r, x, flag, cs);
+    coarse_psi_solve<BC, T, kKrylovCpt>(g, m, c, r, x, flag, cs);
 }
 
 // ---------------------------------------------------------------------------------------
