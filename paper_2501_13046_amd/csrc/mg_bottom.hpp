@@ -184,17 +184,18 @@ __global__ void __launch_bounds__(kBottomThreads) k_bottom_psi(const BottomArgs<
     int end = 0; // of the levels' arrays
     for (int l = 0; l < L; l++) end += bottom_level_values(A.geo[l].n, l == 0);
     double *weights = reinterpret_cast<double *>(buf + end); // of every smoothed level (kBottomWeights)
-    T *scratch = buf + end;
+    int scratch_at = end;
     for (int t = tid; t < end; t += kBottomThreads) buf[t] = T(0);
     if constexpr (kBottomWeights<BC, T>) {
-        double *w = weights;
+        int o = 0;
         for (int l = 0; l + 1 < L; l++) {
             const int cw = 12 * A.geo[l].n * A.geo[l].n;
-            for (int t = tid; t < cw; t += kBottomThreads) w[t] = A.geo[l].gw[t];
-            w += cw;
+            for (int t = tid; t < cw; t += kBottomThreads) weights[o + t] = A.geo[l].gw[t];
+            o += cw;
         }
-        scratch = reinterpret_cast<T *>(w);
+        scratch_at += o * (int)(sizeof(double) / sizeof(T));
     }
+    T *scratch = buf + scratch_at;
     __syncthreads();
     T *D = buf; // the current level's padded array
 #pragma unroll 1
@@ -213,8 +214,23 @@ __global__ void __launch_bounds__(kBottomThreads) k_bottom_psi(const BottomArgs<
             bottom_fill_ghosts<BC>(A.geo[l + 1], below);
             bottom_prolong<BC>(g, gw, D, below, scratch, A.cubic != 0);
         }
-        const T *R = l ? D + bottom_padded(n) : gr0, *C = l ? R + m : gc0;
         BottomPairs<T> B;
+        // (a copy for each address space: a pointer that may be either makes generic loads)
+        auto load = [&](const T *R, const T *C) {
+#pragma unroll
+            for (int q = 0; q < kBottomPairs; q++) {
+                const int it = min(tid + q * kBottomThreads, cnt - 1);
+#pragma unroll
+                for (int e = 0; e < 2; e++) {
+                    B.r[q][e] = R[2 * it + e];
+                    B.c[q][e] = C[2 * it + e];
+                }
+            }
+        };
+        if (l)
+            load(D + bottom_padded(n), D + bottom_padded(n) + m);
+        else
+            load(gr0, gc0);
 #pragma unroll
         for (int q = 0; q < kBottomPairs; q++) {
             const int it = min(tid + q * kBottomThreads, cnt - 1);
@@ -223,11 +239,6 @@ __global__ void __launch_bounds__(kBottomThreads) k_bottom_psi(const BottomArgs<
             B.i[q] = row / n;
             B.j[q] = row - B.i[q] * n;
             B.a[q] = ((B.i[q] + 2) * P + B.j[q] + 2) * P + B.k[q] + 2;
-#pragma unroll
-            for (int e = 0; e < 2; e++) {
-                B.r[q][e] = R[2 * it + e];
-                B.c[q][e] = C[2 * it + e];
-            }
         }
 #pragma unroll
         for (int q = 0; q < kBottomPairs; q++) {
@@ -295,8 +306,9 @@ __global__ void __launch_bounds__(kBottomThreads) k_bottom_psi(const BottomArgs<
             continue;
         }
         // the coarsest level: solved into the scratch, then into its padded array
-        CoarseScratch &cs =
-            *reinterpret_cast<CoarseScratch *>((reinterpret_cast<uintptr_t>(scratch + mc) + 15) & ~uintptr_t(15));
+        // (at a constant offset at the end of lds: of an address rounded up as an integer the
+        // compiler does not know any more that it is in LDS)
+        CoarseScratch &cs = *reinterpret_cast<CoarseScratch *>(lds + kBottomBytes - (sizeof(CoarseScratch) + 15) / 16 * 16);
         for (int t = tid; t < mc; t += kBottomThreads) scratch[t] = T(0); // stays 0 if singular
         __syncthreads();
         coarse_psi_solve<BC, T, 1>(A.geo[l + 1], mc, Rc + mc, Rc, scratch, zsh(A.flag, zs), cs);

@@ -1320,8 +1320,17 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
     return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
+// Orders the memory accesses of one wave among its lanes: what a lane wrote before, every lane
+// reads after.  Costs no instruction where the accesses are LDS ones.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 // One wave, E cells per lane (m <= 64 E; cell lane + 64 e).  Needs no block barrier: the vector
-// being multiplied passes through LDS (vec, m values), whose accesses a wave makes in order.
+// being multiplied passes through LDS (vec, m values), ordered by wave_sync.
 // A step is a chain of latencies (LDS round, sums, reduction, division), so the reductions are
 // merged: conjugate gradients in the single-reduction form of Chronopoulos and Gear, whose
 // <r, r> hides behind the operator, and BiCGSTAB with three reduction points a step.  Writes x
@@ -1331,26 +1340,32 @@ __device__ __forceinline__ bool coarse_psi_krylov_wave(const Geo &g, int m, cons
 {
     const int lane = threadIdx.x & (kWave - 1);
     int src[E][12];
-    double w[E][12], dg[E], b[E];
+    double w[E][12], h2[E], dg[E], b[E]; // a cell past the last one has weights of 0
 #pragma unroll
     for (int e = 0; e < E; e++) {
         const int q = lane + kWave * e < m ? lane + kWave * e : 0;
         const bool own = lane + kWave * e < m;
         coarse_taps<BC>(g, q, src[e], w[e]);
+        if constexpr (BC == kBcPeriodic) {
+            h2[e] = own ? g.inv12h2 : 0.0;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 12; k++) w[e][k] = own ? w[e][k] : 0.0;
+        }
         dg[e] = own ? -90.0 * g.inv12h2 + (double)c[q] : 0.0;
         b[e] = own ? (double)r[q] : 0.0;
     }
+    // no branch on the cells a lane has, and every load of a cell issued before its first use
     auto apply = [&](const double (&v)[E], double (&y)[E]) {
-        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int e = 0; e < E; e++)
-            if (lane + kWave * e < m) vec[lane + kWave * e] = v[e];
-        asm volatile("" ::: "memory");
+        for (int e = 0; e < E; e++) vec[lane + kWave * e] = v[e];
+        wave_sync();
 #pragma unroll
         for (int e = 0; e < E; e++) {
             double t[12], s[3];
 #pragma unroll
             for (int k = 0; k < 12; k++) t[k] = vec[src[e][k]];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int ax = 0; ax < 3; ax++) {
                 if constexpr (BC == kBcPeriodic)
@@ -1360,9 +1375,9 @@ __device__ __forceinline__ bool coarse_psi_krylov_wave(const Geo &g, int m, cons
                             (w[e][4 * ax] * t[4 * ax] + w[e][4 * ax + 3] * t[4 * ax + 3]);
             }
             const double o = s[0] + s[1] + s[2];
-            y[e] = lane + kWave * e < m ? (BC == kBcPeriodic ? o * g.inv12h2 : o) + dg[e] * v[e] : 0.0;
+            y[e] = (BC == kBcPeriodic ? o * h2[e] : o) + dg[e] * v[e];
         }
-        asm volatile("" ::: "memory");
+        wave_sync();
     };
     auto part = [&](const double (&u)[E], const double (&v)[E]) {
         double s = u[0] * v[0];
@@ -1701,15 +1716,18 @@ __device__ __forceinline__ void coarse_psi_eliminate(const Geo &g, int m, const 
     auto &pdiag = cs.gj.pdiag;
     auto &piv = cs.gj.piv;
     auto &perm = cs.gj.perm;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // (masks of these are worked out here and not kept over the rare call's surroundings)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int n = g.n;
-    if (threadIdx.x < M) {
-        const int row = threadIdx.x;
+    if (tid < M) {
+        const int row = tid;
         for (int j = 0; j < NC; j++) A[row][j] = row >= m && j == row ? 1.0 : 0.0;
     }
-    if ((int)threadIdx.x < m) {
-        const int row = threadIdx.x;
+    if (tid < m) {
+        const int row = tid;
         const int k = row % n, j = (row / n) % n, i = row / (n * n);
         const double wt[5] = {-1.0, 16.0, -30.0, 16.0, -1.0};
         for (int ax = 0; ax < 3; ax++)
@@ -1780,7 +1798,7 @@ __device__ __forceinline__ void coarse_psi_eliminate(const Geo &g, int m, const 
         }
     });
     if (singular) {
-        if (threadIdx.x == 0) *flag = 1.0;
+        if (tid == 0) *flag = 1.0;
         return;
     }
     // the right-hand side column (held by one wave) through LDS
@@ -1788,7 +1806,7 @@ __device__ __forceinline__ void coarse_psi_eliminate(const Geo &g, int m, const 
     for (int q = 0; q < S; q++)
         if (wave + kGjWaves * q == M && lane < M) A[lane][M] = v[q];
     __syncthreads();
-    if ((int)threadIdx.x < m) x[threadIdx.x] = (T)(A[perm[threadIdx.x]][M] / pdiag[threadIdx.x]);
+    if (tid < m) x[tid] = (T)(A[perm[tid]][M] / pdiag[tid]);
 }
 
 // (L_h + c) x = r on the coarsest level (m <= kKrylovMax cells): up to 128 cells on one wave,
