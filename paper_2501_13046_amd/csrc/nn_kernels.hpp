@@ -590,23 +590,41 @@ __global__ void __launch_bounds__(kNBlock, 2) k_conv3_wgrad(WgtArgs a)
     f32x4 acc[7];
 #pragma unroll
     for (int t = 0; t < 7; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    load(first);
-    for (int bi = first; bi < last; bi++) {
-        B::store(halo, stg);
-        dys[tid] = dst[0];
-        dys[tid + kNBlock] = dst[1];
-        __syncthreads();
-        if (bi + 1 < last) load(bi + 1);
+    // the products of a staged brick.  Past: cells of it lie past the grid (nx, ny and nz cells are
+    // inside); the halo has grid cells' values there, whose product with the zero output gradient
+    // is no zero where they are infinite, so they are taken as zeros too
+    auto consume = [&](auto past, int nx, int ny, int nz) {
+        constexpr bool Past = decltype(past)::value;
+        uint32_t mz[2]; // inside along z: the two pairs of this lane's four cells
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            const int z = 4 * g % BZ + 2 * j;
+            mz[j] = (z < nz ? 0xffffu : 0u) | (z + 1 < nz ? 0xffff0000u : 0u);
+        }
         static_for<8>([&](auto sc) {
             constexpr int r0 = 2 * decltype(sc)::value, r1 = r0 + 1; // tile rows: x = r / 4, tile r % 4 of y
             constexpr int h0 = ((r0 / 4) * B::HY + (r0 % 4) * B::MY) * B::HZ * 32;
             constexpr int h1 = ((r1 / 4) * B::HY + (r1 % 4) * B::MY) * B::HZ * 32;
             const u32x2 d0 = read_turned(db + r0 * 512), d1 = read_turned(db + r1 * 512);
             const u32x4 dv = {d0[0], d0[1], d1[0], d1[1]};
+            uint32_t mk[4] = {~0u, ~0u, ~0u, ~0u};
+            if constexpr (Past) {
+                const bool in0 = r0 / 4 < nx && (r0 % 4) * B::MY + 4 * g / BZ < ny;
+                const bool in1 = r1 / 4 < nx && (r1 % 4) * B::MY + 4 * g / BZ < ny;
+#pragma unroll
+                for (int j = 0; j < 2; j++) {
+                    mk[j] = in0 ? mz[j] : 0u;
+                    mk[2 + j] = in1 ? mz[j] : 0u;
+                }
+            }
 #pragma unroll
             for (int t = 0; t < 7; t++) {
                 const u32x2 v0 = read_turned(hb[t] + h0), v1 = read_turned(hb[t] + h1);
                 u32x4 av = {v0[0], v0[1], v1[0], v1[1]};
+                if constexpr (Past) {
+#pragma unroll
+                    for (int j = 0; j < 4; j++) av[j] &= mk[j];
+                }
                 if (t == 6) {
 #pragma unroll
                     for (int j = 0; j < 4; j++) av[j] = wave == 3 ? kOnes : av[j];
@@ -614,6 +632,24 @@ __global__ void __launch_bounds__(kNBlock, 2) k_conv3_wgrad(WgtArgs a)
                 acc[t] = mfma(av, dv, acc[t]);
             }
         });
+    };
+    load(first);
+    for (int bi = first; bi < last; bi++) {
+        B::store(halo, stg);
+        dys[tid] = dst[0];
+        dys[tid + kNBlock] = dst[1];
+        __syncthreads();
+        if (bi + 1 < last) load(bi + 1);
+        if constexpr (BZ == 16) {
+            consume(std::false_type{}, B::BX, BY, BZ); // bricks of 16 divide the sides they serve
+        } else {
+            const int t = bi / nbz, bx = t / nby;
+            const int nx = n - bx * B::BX, ny = n - (t - bx * nby) * BY, nz = n - (bi - t * nbz) * BZ;
+            if (nx >= B::BX && ny >= BY && nz >= BZ)
+                consume(std::false_type{}, nx, ny, nz);
+            else
+                consume(std::true_type{}, nx, ny, nz);
+        }
         __syncthreads(); // the staged brick is consumed
     }
     float *out = a.part + (((int64_t)blockIdx.z * a.cot + blockIdx.x) * a.cit + blockIdx.y) * kWgtTile;

@@ -59,3 +59,25 @@ def test_weight_gradient_on_any_side(n, cin, cout, act):
 # an odd coarse side: the upsampling's adjoint takes coarse cells in pairs along z
 def test_network_gradients_on_an_odd_coarse_side():
     network_gradients(6, 2, (16, 32))
+
+
+# bricks that overhang the grid read wrapped cells for the cells past it: an infinite
+# activation there must not turn a gradient into NaN (0 * infinity)
+@pytest.mark.parametrize("n", [7, 9, 12, 18, 20, 34])
+def test_weight_gradient_of_infinite_activations(n):
+    cin, cout = 8, 16
+    rng = np.random.default_rng(n)
+    x = bf(rng.standard_normal((cin, n, n, n)))
+    dy = bf(rng.standard_normal((cout, n, n, n)))
+    cells = {1: (0, 0, 0), 2: (n - 1, n - 1, n - 1), 3: (0, n // 2, n - 1)}
+    for ci, w in cells.items():
+        x[(ci,) + w] = np.inf
+    dW, db = gn.conv3_backward_weight(to_dev(cl(x), torch.bfloat16), to_dev(cl(dy), torch.bfloat16), n, cin, cout,
+                                      False)
+    dW = dW.cpu().numpy().reshape(cout, cin, 3, 3, 3)
+    for ci, w in cells.items():
+        for t in np.ndindex(3, 3, 3):  # dW[t] = sum_v dy[v] x[v + t - 1]
+            v = tuple((w[a] - t[a] + 1) % n for a in range(3))
+            np.testing.assert_array_equal(dW[(slice(None), ci) + t], np.sign(dy[(slice(None),) + v]) * np.inf)
+    finite = [ci for ci in range(cin) if ci not in cells]
+    assert np.isfinite(dW[:, finite]).all() and np.isfinite(db.cpu().numpy()).all()
