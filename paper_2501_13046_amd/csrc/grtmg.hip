@@ -329,8 +329,7 @@ void carve(mg_ctx *c, Carver &cv)
 
 // Coarsest psi systems below which a psi tail may be chosen.
 bool wave_solvable(int m) { return m == 8 || m == 27 || m == 64; }
-static_assert(kMaxCoarsePsi <= kKrylovMax && kMaxCoarsePsi <= 12 * 12 * 12 && kPaddedCoarse >= 16 * 16 * 16,
-              "every coarsest psi system has a solver");
+static_assert(kMaxCoarsePsi <= kKrylovMax, "every coarsest psi system has a solver");
 
 TileMap tilemap_rt(int n, int tx)
 {
@@ -406,7 +405,8 @@ void init_geo(mg_ctx *c)
                 c->tail_W = l;
                 break;
             }
-    // the tails prolong trilinearly inside: none with cubic prolongation
+    // none to choose with cubic prolongation (the W tail prolongs trilinearly inside; the psi
+    // levels in one workgroup, which do both, start at their own level)
     if (c->p.flags & MG_FLAG_CUBIC_PROLONG) c->tail_psi = c->tail_W = -1;
     c->tail_psi_min = c->tail_psi;
     c->tail_W_min = c->tail_W;
@@ -519,9 +519,9 @@ void launch_psi_tiled(hipStream_t s, const Geo &g, const TileMap &tm, const T *i
 {
     const dim3 blk(kLanes, kTY), grid(ntiles(tm), 1, g.gz);
     switch (tm.tx) {
-    case 2: hipLaunchKernelGGL((k_pass_psi_tiled<kBcPeriodic, T, 2>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
-    case 8: hipLaunchKernelGGL((k_pass_psi_tiled<kBcPeriodic, T, 8>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
-    default: hipLaunchKernelGGL((k_pass_psi_tiled<kBcPeriodic, T, 4>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
+    case 2: hipLaunchKernelGGL((k_pass_psi_tiled<T, 2>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
+    case 8: hipLaunchKernelGGL((k_pass_psi_tiled<T, 8>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
+    default: hipLaunchKernelGGL((k_pass_psi_tiled<T, 4>), grid, blk, 0, s, g, tm, in, out, r, cf, colour); break;
     }
 }
 

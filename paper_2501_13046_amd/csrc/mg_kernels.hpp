@@ -1148,17 +1148,11 @@ __device__ __forceinline__ double readlane_f64(double x, int l)
 }
 
 // ---------------------------------------------------------------------------------------
-// Krylov solves of the coarsest psi system (L_h + c) x = r in FP64.  Periodic grids
-// give a symmetric matrix: conjugate gradients (Hestenes-Stiefel); Robin ghosts make
-// it slightly non-symmetric: BiCGSTAB (van der Vorst).  Either is accepted only when
-// the true residual |r - A x| is below 1e-12 |r| afterwards; the caller otherwise
-// solves by elimination.
-//
-// ---------------------------------------------------------------------------------------
 // Padded arrays of (n + 4)^3 values in LDS: a level with the two ghost layers the boundary rule
 // gives, so that every tap is a fixed offset from its cell.  padded_store writes v to the cell
 // at word a and to its ghosts along the axes; gv: the ghost values of a cell on a face under the
 // Robin rule (padded_ghosts), first and second layer of each axis.
+// ---------------------------------------------------------------------------------------
 template <int BC, typename T>
 __device__ __forceinline__ void padded_store(T *D, int a, int n, int i, int j, int k, T v, const T (&gv)[3][2])
 {
@@ -1211,6 +1205,14 @@ __device__ __forceinline__ T padded_lap(const T *D, int a, int P, T v)
     return x + y + z;
 }
 
+// ---------------------------------------------------------------------------------------
+// Krylov solves of the coarsest psi system (L_h + c) x = r in FP64.  Periodic grids
+// give a symmetric matrix: conjugate gradients (Hestenes-Stiefel); Robin ghosts make
+// it slightly non-symmetric: BiCGSTAB (van der Vorst).  Either is accepted only when
+// the true residual |r - A x| is below 1e-12 |r| afterwards; the caller otherwise
+// solves by elimination.
+// ---------------------------------------------------------------------------------------
+
 // The 12 off-centre taps of L_h at a cell, as (source cell, weight) pairs with the
 // boundary rule folded in (ghost_source).  A tap may name the cell itself.
 template <int BC>
@@ -1241,63 +1243,6 @@ __device__ __forceinline__ double quick_rcp(double x)
     y = fma(fma(-x, y, 1.0), y, y);
     return fma(fma(-x, y, 1.0), y, y);
 }
-
-// The operator L_h + c of the cells first, first + stride, ... that a thread owns (E of them) on
-// a padded vector in LDS.
-template <int BC, int E>
-struct CoarseOp {
-    int i[E], j[E], k[E], a[E], n, m, first, stride;
-    double dg[E], w[E][BC == kBcRobin ? 3 : 1][2], inv12h2;
-    __device__ __forceinline__ bool own(int e) const { return first + stride * e < m; }
-    template <typename T>
-    __device__ __forceinline__ void init(const Geo &g, int m_, const T *c, int first_, int stride_)
-    {
-        n = g.n;
-        m = m_;
-        first = first_;
-        stride = stride_;
-        inv12h2 = g.inv12h2;
-#pragma unroll
-        for (int e = 0; e < E; e++) {
-            const int q = own(e) ? first + stride * e : 0;
-            k[e] = q % n;
-            j[e] = (q / n) % n;
-            i[e] = q / (n * n);
-            a[e] = ((i[e] + 2) * (n + 4) + j[e] + 2) * (n + 4) + k[e] + 2;
-            dg[e] = own(e) ? (double)c[q] : 0.0;
-            if constexpr (BC == kBcRobin) {
-                const int pos[3] = {i[e], j[e], k[e]}, A[3] = {j[e], i[e], i[e]}, B[3] = {k[e], k[e], j[e]};
-#pragma unroll
-                for (int ax = 0; ax < 3; ax++) {
-                    const double *t = g.gw + (2 * ax + (pos[ax] ? 1 : 0)) * 2 * n * n + A[ax] * n + B[ax];
-                    w[e][ax][0] = t[0];
-                    w[e][ax][1] = t[n * n];
-                }
-            }
-        }
-    }
-    __device__ __forceinline__ void put(double *vec, const double (&v)[E]) const
-    {
-#pragma unroll
-        for (int e = 0; e < E; e++)
-            if (own(e)) {
-                double gv[3][2];
-                if constexpr (BC == kBcRobin) {
-#pragma unroll
-                    for (int ax = 0; ax < 3; ax++) {
-                        gv[ax][0] = v[e] * w[e][ax][0];
-                        gv[ax][1] = v[e] * w[e][ax][1];
-                    }
-                }
-                padded_store<BC>(vec, a[e], n, i[e], j[e], k[e], v[e], gv);
-            }
-    }
-    __device__ __forceinline__ void get(const double *vec, const double (&v)[E], double (&y)[E]) const
-    {
-#pragma unroll
-        for (int e = 0; e < E; e++) y[e] = own(e) ? padded_lap(vec, a[e], n + 4, v[e]) * inv12h2 + dg[e] * v[e] : 0.0;
-    }
-};
 
 // One 64-bit DPP lane move (both halves with the same control).
 template <int CTRL>
@@ -1485,7 +1430,7 @@ __device__ __forceinline__ bool coarse_psi_krylov_wave(const Geo &g, int m, cons
 
 // The same for up to kGjWaves * kWave * CPT cells on a block of kGjWaves waves: every
 // thread owns CPT cells (q = tid + kGjWaves * kWave * e), the vector being multiplied
-// is staged in LDS (padded), and inner products are block reductions.  Writes x and returns
+// is staged in LDS, and inner products are block reductions.  Writes x and returns
 // true (in every thread) when accepted; called by every thread of the block.
 constexpr int kKrylovCpt = 2;
 constexpr int kKrylovMax = kGjWaves * kWave * kKrylovCpt;
@@ -1688,12 +1633,11 @@ __device__ __forceinline__ bool coarse_psi_krylov_block(const Geo &g, int m, con
     return ok;
 }
 
-constexpr int kPaddedCoarse = 16 * 16 * 16; // coarsest psi levels hold at most 12^3 cells
 // LDS of the coarsest solve.
 struct CoarseScratch {
     union {
         struct {
-            double vec[kPaddedCoarse], part[3][kGjWaves];
+            double vec[kKrylovMax], part[3][kGjWaves];
         } kr;
         struct {
             double A[kWave][kWave + 2], fac[2][kWave], pdiag[kWave];

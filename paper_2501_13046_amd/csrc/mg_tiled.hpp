@@ -109,58 +109,32 @@ __global__ void __launch_bounds__(kBlock) k_prolong_add_pairs(Geo gc, const T *_
     }
 }
 
-// Stage brick + halo of one field.  A staged row (fixed x, y) holds the 66
+// Stage brick + halo of one field (periodic).  A staged row (fixed x, y) holds the 66
 // aligned z pairs (z0 - 2 + 2P, z0 - 1 + 2P), P = 0..65; pair P lands at
 // words P (even z) and kHalf + P (odd z).  Every lane of wave w moves pair
 // P = lane of rows w, w + kTY, ...; the two remaining pairs of every row are
 // spread over the whole block.  All global loads are issued before any LDS
 // store.  Offsets are 32-bit (fields up to 2^31 elements).
-template <int BC, typename T, int TX>
-__device__ __forceinline__ void load_brick(T (*s)[kPY][kPZ], const Acc<BC, T> &A, int x0, int y0, int z0)
+template <typename T, int TX>
+__device__ __forceinline__ void load_brick(T (*s)[kPY][kPZ], const T *__restrict__ a, int n, int x0, int y0, int z0)
 {
     using V2 = typename Vec2<T>::type;
     constexpr int NROW = (TX + 4) * kPY;
     constexpr int RPW = NROW / kTY; // rows per wave
     static_assert(NROW % kTY == 0, "rows must divide among the waves");
     static_assert(2 * NROW <= kTY * kLanes, "one extra pair per thread at most");
-    const int n = A.g.n;
     const int w = threadIdx.y, lane = threadIdx.x;
     const int tid = w * kLanes + lane;
-    auto row_base = [&](int row, bool &inside) -> int {
-        const int xg = x0 + row / kPY - 2, yg = y0 + row % kPY - 2;
-        inside = (unsigned)xg < (unsigned)n && (unsigned)yg < (unsigned)n;
-        return (wrap(xg, n) * n + wrap(yg, n)) * n;
-    };
+    auto row_base = [&](int row) { return (wrap(x0 + row / kPY - 2, n) * n + wrap(y0 + row % kPY - 2, n)) * n; };
     auto pair_z = [&](int P) { return wrap(z0 - 2 + 2 * P, n); };
     V2 v[RPW];
 #pragma unroll
-    for (int i = 0; i < RPW; i++) {
-        const int row = w + i * kTY;
-        bool inside;
-        const int base = row_base(row, inside);
-        const int zp = pair_z(lane);
-        if (BC == kBcPeriodic || (inside && z0 - 2 + 2 * lane >= 0)) {
-            v[i] = *reinterpret_cast<const V2 *>(A.a + base + zp);
-        } else {
-            const int xg = x0 + row / kPY - 2, yg = y0 + row % kPY - 2;
-            v[i].x = A(xg, yg, z0 - 2 + 2 * lane);
-            v[i].y = A(xg, yg, z0 - 1 + 2 * lane);
-        }
-    }
+    for (int i = 0; i < RPW; i++)
+        v[i] = *reinterpret_cast<const V2 *>(a + row_base(w + i * kTY) + pair_z(lane));
     // extra pairs: thread tid < 2 NROW moves pair 64 + (tid & 1) of row tid / 2
     V2 e;
     const int erow = tid >> 1, ep = kLanes + (tid & 1);
-    if (tid < 2 * NROW) {
-        bool inside;
-        const int base = row_base(erow, inside);
-        if (BC == kBcPeriodic || (inside && z0 - 2 + 2 * ep + 1 < n)) {
-            e = *reinterpret_cast<const V2 *>(A.a + base + pair_z(ep));
-        } else {
-            const int xg = x0 + erow / kPY - 2, yg = y0 + erow % kPY - 2;
-            e.x = A(xg, yg, z0 - 2 + 2 * ep);
-            e.y = A(xg, yg, z0 - 1 + 2 * ep);
-        }
-    }
+    if (tid < 2 * NROW) e = *reinterpret_cast<const V2 *>(a + row_base(erow) + pair_z(ep));
 #pragma unroll
     for (int i = 0; i < RPW; i++) {
         const int row = w + i * kTY;
@@ -254,11 +228,11 @@ __device__ __forceinline__ void deltaL_taps(const Taps<T, PAR, TT> &F0, const Ta
 }
 
 // ---------------------------------------------------------------------------------------
-// psi smoother colour pass on a brick.  For every (x, y) row a lane owns the z
+// psi smoother colour pass (periodic) on a brick.  For every (x, y) row a lane owns the z
 // pair (z0 + 2 lane, z0 + 2 lane + 1): it updates the member of the active
 // colour and copies the other, so no lane idles on the checkerboard.
 // ---------------------------------------------------------------------------------------
-template <int BC, typename T, int PAR, int TT>
+template <typename T, int PAR, int TT>
 __device__ __forceinline__ void psi_cell(const Geo &g, const T *row0, const T *__restrict__ r,
                                          const T *__restrict__ c, T *__restrict__ out, int x, int y, int z0,
                                          int lane, T h2, T dlap)
@@ -269,16 +243,11 @@ __device__ __forceinline__ void psi_cell(const Geo &g, const T *row0, const T *_
     const T v = D.c();
     const T cv = c[qrow + za];
     const T Ad = (D.dxx(v) + D.dyy(v) + D.dzz(v)) * h2 + cv * v;
-    T diag;
-    if constexpr (BC == kBcPeriodic)
-        diag = dlap + cv;
-    else
-        diag = pinned((T)(lap_diag_sum<BC>(g, x, y, za) * g.inv12h2)) + cv;
-    out[qrow + za] = v + (r[qrow + za] - Ad) / diag;
+    out[qrow + za] = v + (r[qrow + za] - Ad) / (dlap + cv);
     out[qrow + zb] = D.template at<0, 0, (PAR ? -1 : 1)>();
 }
 
-template <int BC, typename T, int TX, int TT>
+template <typename T, int TX, int TT>
 __device__ __forceinline__ void psi_cells(const Geo &g, const T *row0, const T *__restrict__ r,
                                           const T *__restrict__ c, T *__restrict__ out, int x0, int y, int z0,
                                           int lane, int colour, T h2, T dlap)
@@ -286,14 +255,14 @@ __device__ __forceinline__ void psi_cells(const Geo &g, const T *row0, const T *
     if constexpr (TT < TX) {
         const int x = x0 + TT;
         if (((colour + x + y + z0) & 1) == 0)
-            psi_cell<BC, T, 0, TT>(g, row0, r, c, out, x, y, z0, lane, h2, dlap);
+            psi_cell<T, 0, TT>(g, row0, r, c, out, x, y, z0, lane, h2, dlap);
         else
-            psi_cell<BC, T, 1, TT>(g, row0, r, c, out, x, y, z0, lane, h2, dlap);
-        psi_cells<BC, T, TX, TT + 1>(g, row0, r, c, out, x0, y, z0, lane, colour, h2, dlap);
+            psi_cell<T, 1, TT>(g, row0, r, c, out, x, y, z0, lane, h2, dlap);
+        psi_cells<T, TX, TT + 1>(g, row0, r, c, out, x0, y, z0, lane, colour, h2, dlap);
     }
 }
 
-template <int BC, typename T, int TX>
+template <typename T, int TX>
 __global__ void __launch_bounds__(kTY *kLanes) k_pass_psi_tiled(Geo g, TileMap tm, const T *__restrict__ in,
                                                                T *__restrict__ out, const T *__restrict__ r,
                                                                const T *__restrict__ c, int colour)
@@ -306,11 +275,11 @@ __global__ void __launch_bounds__(kTY *kLanes) k_pass_psi_tiled(Geo g, TileMap t
     int x0, y0, z0;
     brick_of(tm, x0, y0, z0);
     const int ty = threadIdx.y, lane = threadIdx.x;
-    load_brick<BC, T, TX>(lds, Acc<BC, T>{in, g}, x0, y0, z0);
+    load_brick<T, TX>(lds, in, g.n, x0, y0, z0);
     __syncthreads();
     const T h2 = (T)g.inv12h2;
     const T dlap = pinned((T)(-90.0 * g.inv12h2));
-    psi_cells<BC, T, TX, 0>(g, &lds[0][ty][0], r, c, out, x0, y0 + ty, z0, lane, colour, h2, dlap);
+    psi_cells<T, TX, 0>(g, &lds[0][ty][0], r, c, out, x0, y0 + ty, z0, lane, colour, h2, dlap);
 }
 
 // ---------------------------------------------------------------------------------------
