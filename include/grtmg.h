@@ -454,22 +454,25 @@ mg_status mg_fmg_start(mg_ctx *cc, mg_ctx *cf, double *d_uc, double *d_Wc, doubl
  * 8 and 16 march a column of that many x planes through a ring of staged
  * planes; residual {2, 4, 8, 16}, where 2 and 4 stage bricks and 8 and 16
  * (periodic only) march columns of that many x planes.
- * Two further families choose how the coarse levels of each V-cycle run: as
- * separate grid launches (0, the default) or as one workgroup-resident "tail"
- * kernel per V-cycle (1) that runs every level from its first one down to the
+ * Two further families choose where one workgroup-resident "tail" kernel per
+ * V-cycle takes over: it runs every level from its first one down to the
  * coarsest and back, phase by phase with block barriers, on arrays held in
- * LDS (same per-cell arithmetic; the restriction sums group the 8 children
- * differently, so results agree to rounding).  The tail starts at the first
+ * LDS.  1: the tail starts at the entry's `level`.  0 (the default): for W no
+ * tail, every level as grid launches; for psi the library's own start, the first
+ * level of at most 16^3 cells where the levels below it fit that kernel (its
+ * coarsest system has at most 128 unknowns; grid launches otherwise).  psi levels
+ * that fit therefore never run as grid launches inside a V-cycle (mg_kernel_op does
+ * launch them one by one).  Results agree to rounding: the restriction sums group
+ * the 8 children differently, and the psi passes multiply by a stored reciprocal of
+ * the diagonal where the grid passes divide.  A tail may start at the first
  * level from which the cells of all levels down to the coarsest sum to at
  * most 4680 (psi, FP32, periodic) or 1971 (psi otherwise; W), spanning at
- * most 4 levels (e.g. 16^3 for psi and 8^3 for W, FP32 periodic), or from any
- * level below it down to the one above the coarsest.  For psi, 0 means the
- * library's own start of that kernel: the first level of at most 16^3 cells (one
- * launch is quicker there than a launch per step).  Their `level` is the tail's
- * first level: mg_autotune times one whole V-cycle with the tail off and starting
- * at each such level and reports the fastest start (chosen 1) or the fastest
- * start tried (chosen 0, the tail off); mg_set_tile(family, level, 1) starts the
- * tail at `level`, (family, level, 0) turns it off.
+ * most 4 levels (e.g. 16^3 for psi and 8^3 for W, FP32 periodic), or at any
+ * level below it down to the one above the coarsest.  mg_autotune times one whole
+ * V-cycle with the default (0) and with the tail starting at each such level and
+ * reports the fastest start (chosen 1) or the fastest start tried (chosen 0, the
+ * default kept); mg_set_tile(family, level, 1) starts the tail at `level`,
+ * (family, level, 0) goes back to the default.
  * MG_TUNE_FOURIER_W (FP32 periodic contexts with momentum whose levels include a
  * 16^3 one below the finest; `level` is that level): the W V-cycle solves that
  * level exactly by discrete Fourier modes in one workgroup (1, the default) or

@@ -497,8 +497,11 @@ bool ragged_residual(int n) { return n % 2 == 0 && n >= 18 && (double)n * n * n 
 // inside grids of at least 18 cells per axis); rows of 64 cells where they divide the side,
 // else of 32.  Below, one thread per z pair: its single round of loads takes 3.0-4.7 us up to
 // 64^3 (FP32) where a brick's two rounds took 5.4-8.5, and 72 overhangs bricks by a third (a
-// 72^3 solve 2.66 ms on bricks, 2.58 on pairs); at 80^3 the brick is level with it (6.7
-// against 6.2 us) and at 160^3 ahead (18.0 against 28.3).
+// 72^3 FP64 solve 2.67 ms on bricks, 2.59 on pairs).  At 80^3 it depends on the solve: coupled
+// 4.05 ms on bricks, 4.12 on pairs; psi alone 2.42 against 2.36 (FP64, periodic), 3.14 against 2.80
+// (FP64, mirror), 1.56 against 1.52 (FP32, Robin).  88^3 is level within 3 %; 96^3 is ahead on bricks
+// (in the same three 2.49 against 2.93, 3.06 against 3.39 and 1.69 against 1.97 ms), 160^3 by 1.2
+// to 1.5 times.
 constexpr int kBrickMin = 80;
 bool psi_bricks(int n) { return n % 2 == 0 && n >= kBrickMin; }
 bool brick_rows_64(int n) { return n % 64 == 0; }

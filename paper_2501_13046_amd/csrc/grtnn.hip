@@ -25,8 +25,10 @@ namespace {
 // target grid of the weight-gradient kernel: two blocks per CU (16 -> 16 channels at 64^3:
 // 13 us with two bricks each, 16.5 with one block per CU and four)
 constexpr int kWgradBlocks = 512;
-// blocks that a large convolution is dealt to: what is resident at once (four per CU, two
-// with slices of 32 channels, by LDS), in one round
+// blocks that a large convolution is dealt to at least: what is resident at once (four per CU, two
+// with slices of 32 channels, by LDS).  A block takes whole bricks, rounded down, so that it is one
+// round where these numbers divide bricks x tiles (64^3, 128^3) and a second, short one elsewhere
+// (96^3: 1152 blocks)
 constexpr int kConvBlocks = 1024, kConvBlocks32 = 512;
 // bricks x channel tiles from which the larger bricks keep up: at 32^3 with 48 channels
 // (384) 12.2 against 16.0 us; the 16^3 levels (48 to 64) would leave three CUs of four idle

@@ -4,9 +4,11 @@
 // the coarsest solve and back, every step of the V-cycle runs in one workgroup of 16 waves on
 // arrays in LDS.  As separate launches each of these steps costs a launch and a round of
 // memory latency (3-4 us for a colour pass of 8^3 or 16^3 cells, 19 launches from 16^3 to 4^3
-// and back: 75 us and the gaps between them in a 128^3 FP32 cycle).  Here a 16^3 pass takes
-// 1.4 us (FP64 1.7, Robin 2.4), an 8^3 pass 0.6 us and the whole V(1,3) from 16^3 to 4^3 and back
-// 37-48 us, of which the 4^3 solve is 8-13.
+// and back: 75 us and the gaps between them in a 128^3 FP32 cycle).  Here the whole V(1,3)
+// from 16^3 to 4^3 and back takes 40 us (FP64 43, Robin 74 and 93): the 4^3 solve 11 (Robin 20), the
+// 8^3 level around it 9 (Robin 20), the 16^3 level 20 to 23 (Robin 35 to 51).  With the scratch of
+// the coarsest solve behind generic pointers, 0.5 to 5 us more (10^3 over 5^3: 33 -> 26 us, Robin
+// 149 -> 80).
 //
 // Corrections d live in padded arrays of (n + 4)^3 values whose ghost layers hold what the
 // boundary rule gives there, so that every tap is a fixed offset from its cell whatever the
@@ -170,8 +172,9 @@ __device__ __forceinline__ void bottom_fill_ghosts(const Geo &g, T *D)
 }
 
 // One pass of the code below runs every level on the way down (leg = level) and again on the
-// way up (leg = 2 (L - 1) - 1 - level): one copy of the smoother serves all of them.  Bound by
-// instruction issue (16 waves on one CU) and, on the smallest levels, by barriers.
+// way up (leg = 2 (L - 1) - 1 - level): one copy of the smoother serves all of them.  FP64 from
+// 16^3: the vector units issue in half of a SIMD's cycles (four waves each); the rest is waiting, a
+// quarter of the time for the one wave of the coarsest solve, else at barriers.
 template <int BC, typename T>
 __global__ void __launch_bounds__(kBottomThreads) k_bottom_psi(const BottomArgs<T> A)
 {

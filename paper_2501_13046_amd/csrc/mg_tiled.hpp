@@ -459,7 +459,8 @@ __global__ void __launch_bounds__(kTY *kLanes) k_pass_W_tiled(Geo g, TileMap tm,
 //
 // LX = 0 serves grids of any even side from 18 cells on (rows of 32 cells, four per wave,
 // 16 per workgroup): the column length comes from the map, columns overhang the grid in y and
-// z (wrapped loads of the overhang, no stores) and the last column in x may be shorter.
+// z (wrapped loads of the overhang, no stores).  The kernels take a shorter last column in x too,
+// which no accepted side has (coarsest levels are small, so a side is a multiple of its length).
 // Such levels had one thread per cell with 135 loads through the caches and half its lanes
 // idle: 160^3 FP32 pass 106 -> 43 us (147 MB, 3.4 TB/s), 80^3 16.4 -> 11.7, defect restriction
 // at 160^3 311 -> 66 us, residual 342 -> 179 us.
