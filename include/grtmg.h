@@ -584,7 +584,9 @@ mg_status mg_batch_launch_mode(mg_batch *b, int32_t request, int32_t *chosen, do
  * Kernel timing probe (measurement support).  mg_probe(ctx, kernel, level)
  * starts recording a HIP event pair around every later launch of one kernel
  * family on one level (kernel = MG_PROBE_*, level = multigrid level, or -1
- * for all levels); kernel = MG_PROBE_NONE stops recording.  Up to 4096
+ * for all levels); kernel = MG_PROBE_NONE stops recording.  Levels that run inside
+ * one workgroup-resident kernel launch nothing of their own: that kernel counts as
+ * MG_PROBE_COARSE on the coarsest level.  Up to 4096
  * launches are recorded; later ones are not.  mg_probe_result synchronises
  * the stream and returns the number of recorded launches and the summed
  * event-to-event time in milliseconds, then clears the record.  Events are
