@@ -474,8 +474,16 @@ void coarse_psi(mg_ctx *c, const T *r, T *x)
     Probe pr(c, MG_PROBE_COARSE, l);
     with_rule(c->p.bc, [&](auto bcx) {
         constexpr int BCX = decltype(bcx)::value;
-        hipLaunchKernelGGL((k_coarse_psi<BCX, T>), dim3(1, 1, c->gz), dim3(kGjWaves * kWave), 0, c->s, c->geo[l],
-                           c->m_psi, (const T *)c->pc[l], r, x, c->scal + S_FLAG_PSI);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(1, 1, c->gz), dim3(kGjWaves * kWave), 0, c->s, c->geo[l], c->m_psi,
+                               (const T *)c->pc[l], r, x, c->scal + S_FLAG_PSI);
+        };
+        if (c->m_psi <= kWaveMax)
+            launch(k_coarse_psi<BCX, T>);
+        else if (c->m_psi <= kGjWaves * kWave)
+            launch(k_coarse_psi_block<BCX, T, 1>);
+        else
+            launch(k_coarse_psi_block<BCX, T, kKrylovCpt>);
     });
 }
 

@@ -62,7 +62,7 @@ inline bool bottom_fits(const int *n, int nl)
     // more cells than one wave solves take the block's Krylov steps, whose registers (taps and
     // vectors of two cells a thread) this kernel does not have beside its own: 14^3 over 7^3 in
     // here, 56^3 solves took 2 to 3 times as long
-    if (n[nl - 1] * n[nl - 1] * n[nl - 1] > 2 * kWave) return false;
+    if (n[nl - 1] * n[nl - 1] * n[nl - 1] > kWaveMax) return false;
     size_t b = 0;
     for (int l = 0; l < nl; l++) b += (size_t)bottom_level_values(n[l], l == 0) * sizeof(T);
     for (int l = 0; l + 1 < nl && sizeof(T) == 4; l++) b += 12 * (size_t)n[l] * n[l] * sizeof(double);
@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(kBottomThreads) k_bottom_psi(const BottomArgs<
         CoarseScratch &cs = *reinterpret_cast<CoarseScratch *>(lds + kBottomBytes - (sizeof(CoarseScratch) + 15) / 16 * 16);
         for (int t = tid; t < mc; t += kBottomThreads) scratch[t] = T(0); // stays 0 if singular
         __syncthreads();
-        coarse_psi_solve<BC, T, 1>(A.geo[l + 1], mc, Rc + mc, Rc, scratch, zsh(A.flag, zs), cs);
+        coarse_psi_solve<BC, T>(A.geo[l + 1], mc, Rc + mc, Rc, scratch, zsh(A.flag, zs), cs);
         __syncthreads();
         const int Q = np + 4;
         for (int t = tid; t < mc; t += kBottomThreads) {

@@ -1637,7 +1637,7 @@ __device__ __forceinline__ bool coarse_psi_krylov_block(const Geo &g, int m, con
 struct CoarseScratch {
     union {
         struct {
-            double vec[kKrylovMax], part[3][kGjWaves];
+            double vec[kGjWaves * kWave], part[3][kGjWaves];
         } kr;
         struct {
             double A[kWave][kWave + 2], fac[2][kWave], pdiag[kWave];
@@ -1753,29 +1753,28 @@ __device__ __forceinline__ void coarse_psi_eliminate(const Geo &g, int m, const 
     if (tid < m) x[tid] = (T)(A[perm[tid]][M] / pdiag[tid]);
 }
 
-// (L_h + c) x = r on the coarsest level (m <= kKrylovMax cells): up to 128 cells on one wave,
-// which needs no barrier between its steps (125 cells: 58 us as a block of 16 waves); a system
-// the Krylov solve does not accept is eliminated (m <= 64) or raises the flag.  x keeps its
-// values when the flag is raised.  Called by every thread of a block of kGjWaves waves.
-// E: cells per thread of the block's solve.
-template <int BC, typename T, int E>
+// (L_h + c) x = r on a coarsest level of m <= kWaveMax cells: on one wave, which needs no barrier
+// between its steps (125 cells: 58 us as a block of 16 waves); a system the Krylov solve does
+// not accept is eliminated (m <= 64) or left to the block's Krylov solve, which may raise the
+// flag.  x keeps its values when the flag is raised.  Called by every thread of a block of kGjWaves
+// waves.
+constexpr int kWaveMax = 2 * kWave;
+template <int BC, typename T>
 __device__ __forceinline__ void coarse_psi_solve(const Geo &g, int m, const T *c, const T *r, T *x, double *flag,
                                                  CoarseScratch &cs)
 {
-    if (m <= 2 * kWave) {
-        if (threadIdx.x < kWave) {
-            const bool ok = m <= kWave ? coarse_psi_krylov_wave<BC, T, 1>(g, m, c, r, x, cs.kr.vec)
-                                       : coarse_psi_krylov_wave<BC, T, 2>(g, m, c, r, x, cs.kr.vec);
-            if (threadIdx.x == 0) cs.ok = ok ? 1 : 0;
-        }
-        __syncthreads();
-        if (cs.ok) return;
-        if (m <= kWave) {
-            coarse_psi_eliminate<BC, T>(g, m, c, r, x, flag, cs);
-            return;
-        }
+    if (threadIdx.x < kWave) {
+        const bool ok = m <= kWave ? coarse_psi_krylov_wave<BC, T, 1>(g, m, c, r, x, cs.kr.vec)
+                                   : coarse_psi_krylov_wave<BC, T, 2>(g, m, c, r, x, cs.kr.vec);
+        if (threadIdx.x == 0) cs.ok = ok ? 1 : 0;
     }
-    if (!coarse_psi_krylov_block<BC, T, E>(g, m, c, r, x, cs.kr.vec, cs.kr.part) && threadIdx.x == 0) *flag = 1.0;
+    __syncthreads();
+    if (cs.ok) return;
+    if (m <= kWave) {
+        coarse_psi_eliminate<BC, T>(g, m, c, r, x, flag, cs);
+        return;
+    }
+    if (!coarse_psi_krylov_block<BC, T, 1>(g, m, c, r, x, cs.kr.vec, cs.kr.part) && threadIdx.x == 0) *flag = 1.0;
 }
 
 template <int BC, typename T>
@@ -1786,7 +1785,23 @@ __global__ void __launch_bounds__(kGjWaves *kWave) k_coarse_psi(Geo g, int m, co
     r = zsh(r, g.zs);
     x = zsh(x, g.zs);
     flag = zsh(flag, g.zs);
-    coarse_psi_solve<BC, T, kKrylovCpt>(g, m, c, r, x, flag, cs);
+    coarse_psi_solve<BC, T>(g, m, c, r, x, flag, cs);
+}
+
+// Larger coarsest levels (kWaveMax < m <= E kGjWaves kWave cells) on the block; a system it does
+// not solve raises the flag.  A kernel of its own, with as many cells a thread as m needs: beside
+// the wave's solve its loops reloaded spilled vectors (zero rule, 12^3 cells in FP64: 680 us, 621
+// apart), and one cell a thread needs no scratch memory under any rule.
+template <int BC, typename T, int E>
+__global__ void __launch_bounds__(kGjWaves *kWave) k_coarse_psi_block(Geo g, int m, const T *c, const T *r, T *x,
+                                                                     double *flag)
+{
+    __shared__ double vec[E * kGjWaves * kWave], part[3][kGjWaves];
+    c = zsh(c, g.zs);
+    r = zsh(r, g.zs);
+    x = zsh(x, g.zs);
+    flag = zsh(flag, g.zs);
+    if (!coarse_psi_krylov_block<BC, T, E>(g, m, c, r, x, vec, part) && threadIdx.x == 0) *flag = 1.0;
 }
 
 // ---------------------------------------------------------------------------------------

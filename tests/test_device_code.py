@@ -16,6 +16,10 @@ template __global__ void k_bottom_psi<kBcRobin, float>(const BottomArgs<float>);
 template __global__ void k_bottom_psi<kBcZero, double>(const BottomArgs<double>);
 template __global__ void k_coarse_psi<kBcPeriodic, double>(Geo, int, const double *, const double *, double *, double *);
 template __global__ void k_coarse_psi<kBcRobin, float>(Geo, int, const float *, const float *, float *, double *);
+template __global__ void k_coarse_psi_block<kBcRobin, double, 1>(Geo, int, const double *, const double *, double *,
+                                                                 double *);
+template __global__ void k_coarse_psi_block<kBcZero, double, 1>(Geo, int, const double *, const double *, double *,
+                                                                double *);
 }
 """
 
@@ -34,8 +38,15 @@ def kernels(tmp_path_factory):
 
 
 def test_coarsest_solve_addresses_lds(kernels):
-    assert len(kernels) == 5
+    assert len(kernels) == 7
     for name, body in kernels.items():
         assert len(re.findall(r"^\s*ds_(read|load)", body, re.M)) > 0, name
         generic = re.findall(r"^\s*flat_(?:load|store|atomic)\S*", body, re.M)
         assert not generic, (name, len(generic))
+
+
+def test_block_solve_keeps_its_vectors_in_registers(kernels):
+    """One cell a thread (up to 1024 cells): taps and Krylov vectors without scratch memory."""
+    for name, body in kernels.items():
+        if "k_coarse_psi_block" in name:
+            assert re.search(r"private_segment_fixed_size 0\b", body), name
