@@ -25,10 +25,8 @@ namespace {
 // target grid of the weight-gradient kernel: two blocks per CU (16 -> 16 channels at 64^3:
 // 13 us with two bricks each, 16.5 with one block per CU and four)
 constexpr int kWgradBlocks = 512;
-// blocks that a large convolution is dealt to at least: what is resident at once (four per CU, two
-// with slices of 32 channels, by LDS).  A block takes whole bricks, rounded down, so that it is one
-// round where these numbers divide bricks x tiles (64^3, 128^3) and a second, short one elsewhere
-// (96^3: 1152 blocks)
+// blocks that a large convolution is dealt to: what is resident at once (four per CU, two
+// with slices of 32 channels, by LDS)
 constexpr int kConvBlocks = 1024, kConvBlocks32 = 512;
 // bricks x channel tiles from which the larger bricks keep up: at 32^3 with 48 channels
 // (384) 12.2 against 16.0 us; the 16^3 levels (48 to 64) would leave three CUs of four idle
@@ -272,9 +270,10 @@ void launch_conv_slice(hipStream_t s, const ConvArgs &a)
         hipLaunchKernelGGL((k_conv3_small<CS, BZ>), dim3((unsigned)small, (unsigned)a.ntile), dim3(kNBlock), 0, s, a);
         return;
     }
-    const int per = std::max(1, (int)((int64_t)bricks * a.ntile / (CS == 32 ? kConvBlocks32 : kConvBlocks)));
-    hipLaunchKernelGGL((k_conv3_stream<CS, BZ>), dim3((unsigned)ceil_div(bricks, per), (unsigned)a.ntile), dim3(kNBlock),
-                       0, s, a, bricks, per);
+    // a multiple of the 8 XCDs per channel tile
+    const int blocks = std::min((CS == 32 ? kConvBlocks32 : kConvBlocks) / a.ntile / 8, ceil_div(bricks, 8)) * 8;
+    hipLaunchKernelGGL((k_conv3_stream<CS, BZ>), dim3((unsigned)std::max(blocks, 8), (unsigned)a.ntile), dim3(kNBlock),
+                       0, s, a, bricks);
 }
 
 void launch_conv(hipStream_t s, const Layer &ly, bool transposed, int n, const u16 *in1, int c1, int act1,

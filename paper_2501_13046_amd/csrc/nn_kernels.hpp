@@ -387,17 +387,21 @@ __global__ void __launch_bounds__(kNBlock, 2) k_conv3_small(ConvArgs a)
     conv_write<B, 1>(a, co0, x0 + cx, y0 + cy, z0 + cz, acc, bias);
 }
 
-// Convolution on large grids (any n): a block takes a range of bricks of ROWS = 4 and
+// Convolution on large grids (any n): a block takes several bricks of ROWS = 4 and
 // one tile of 16 output channels (blockIdx.y).  The slice's weights are in LDS, read
 // there once per four products: from L2 into every wave they cost more of the vector
 // cache's bandwidth than the halo (14 against 5 loads of 1 KB per wave and brick of 16
-// channels).  A range of bricks, so that the loads of the next are in flight: with
-// one brick per block the same arithmetic waited 70 % of its time.  The next halo (of the next slice or brick) and, where
-// the layer has several slices, the next weights are fetched into registers while
-// this one is consumed.  The four layers with 16 output channels at 128^3 (one of them
+// channels).  Several bricks, so that the loads of the next are in flight: with
+// one brick per block the same arithmetic waited 70 % of its time.  Blocks that run together
+// work on neighbouring bricks, whose halos and whose further slices then come from the L2.  (With
+// a run of consecutive bricks per block they fell out of step wherever the run and a row of
+// bricks did not divide each other: 112 -> 48 channels at 64^3 250 us against 123, 40 -> 8 at 112^3
+// 199 against 88, 32 -> 32 at 96^3 118 against 77.)  The next halo (of the next slice or
+// brick) and, where the layer has several slices, the next weights are fetched into
+// registers while this one is consumed.  The four layers with 16 output channels at 128^3 (one of them
 // of three slices) 350 -> 291 us, 112 -> 48 channels at 32^3 32 -> 24 us.
 template <int CS, int BZ>
-__global__ void __launch_bounds__(kNBlock, CS == 32 ? 2 : 4) k_conv3_stream(ConvArgs a, int bricks, int per_block)
+__global__ void __launch_bounds__(kNBlock, CS == 32 ? 2 : 4) k_conv3_stream(ConvArgs a, int bricks)
 {
     using B = Brick<BZ, 4, CS / 8>;
     constexpr int P = CS / 8, spp = B::kSteps;
@@ -407,7 +411,10 @@ __global__ void __launch_bounds__(kNBlock, CS == 32 ? 2 : 4) k_conv3_stream(Conv
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, r = lane & 15;
     const int n = a.n, nbz = (n + BZ - 1) / BZ, nby = (n + B::BY - 1) / B::BY;
-    const int first = brick_block(gridDim.x) * per_block, last = min(bricks, first + per_block);
+    // each XCD (block number modulo 8) walks an eighth of the bricks, its blocks side by side
+    const int xcd = blockIdx.x % 8, step = gridDim.x / 8;
+    const int first = (int)((int64_t)bricks * xcd / 8) + (int)blockIdx.x / 8;
+    const int last = (int)((int64_t)bricks * (xcd + 1) / 8);
     if (first >= last) return;
     int off[B::NE]; // cells from the halo's first one, inside the grid
 #pragma unroll
@@ -476,7 +483,7 @@ __global__ void __launch_bounds__(kNBlock, CS == 32 ? 2 : 4) k_conv3_stream(Conv
         B::store(smem, stg);
         if (nslice > 1) weight_store();
         __syncthreads();
-        const int nsl = sl + 1 < nslice ? sl + 1 : 0, nbi = nsl ? bi : bi + 1;
+        const int nsl = sl + 1 < nslice ? sl + 1 : 0, nbi = nsl ? bi : bi + step;
         const int px = x0 + cx, py = y0 + cy, pz = z0 + cz;
         if (nbi < last) {
             if (!nsl) brick_at(nbi);
