@@ -32,7 +32,6 @@ using namespace grtmg;
 
 namespace {
 
-constexpr int kMaxLevels = 16;
 constexpr int kMaxCoarsePsi = 1728; // coarsest psi unknowns (12^3)
 constexpr int kMaxCoarseW = 1536;   // coarsest W unknowns (3 * 8^3)
 constexpr int kSrcBlocks = 2048;    // grid of the source kernel (partials in scratch)
@@ -1777,9 +1776,16 @@ mg_status ctx_create(const mg_params *p, void *d_workspace, size_t bytes, hipStr
     }
     enter(c);
     fill<double>(c->s, c->scal, S_COUNT, 0.0);
-    for (int l = 0; l < c->L && c->p.bc == MG_BC_ROBIN; l++)
-        hipLaunchKernelGGL(k_ghost_weights, dim3(nblk((int64_t)c->n[l] * c->n[l]), 12), dim3(kBlock), 0, c->s,
-                           c->geo[l], c->gw[l]);
+    if (c->p.bc == MG_BC_ROBIN) {
+        GhostLevels lv;
+        std::memset(&lv, 0, sizeof(lv));
+        for (int l = 0; l < c->L; l++) {
+            lv.g[l] = c->geo[l];
+            lv.gw[l] = c->gw[l];
+        }
+        hipLaunchKernelGGL(k_ghost_weights, dim3(nblk((int64_t)c->n[0] * c->n[0]), 12, (unsigned)c->L), dim3(kBlock), 0,
+                           c->s, lv);
+    }
     if (c->momentum) {
         const int m = c->m_W;
         fill<double>(c->s, c->A_W, (int64_t)m * m, 0.0);

@@ -19,9 +19,18 @@
 
 namespace grtmg {
 
-// Robin weights of a level (face * 2 + layer, then the two in-face coordinates, row-major).
-__global__ void __launch_bounds__(kBlock) k_ghost_weights(Geo g, double *__restrict__ gw)
+// Robin weights of every level of a context (blockIdx.z) in one launch: at (face * 2 + layer) n^2,
+// then the two in-face coordinates, row-major.  A launch per level took 20 to 45 us of a context's
+// set-up.
+constexpr int kMaxLevels = 16;
+struct GhostLevels {
+    Geo g[kMaxLevels];
+    double *gw[kMaxLevels];
+};
+__global__ void __launch_bounds__(kBlock) k_ghost_weights(GhostLevels lv)
 {
+    const Geo &g = lv.g[blockIdx.z];
+    double *gw = lv.gw[blockIdx.z];
     const int n = g.n, t = (int)(blockIdx.x * kBlock + threadIdx.x);
     if (t >= n * n) return;
     const int a = t / n, b = t - a * n, face = (int)blockIdx.y >> 1, layer = (int)blockIdx.y & 1;
