@@ -20,7 +20,7 @@
 namespace grtmg {
 
 // Robin weights of every level of a context (blockIdx.z) in one launch: at (face * 2 + layer) n^2,
-// then the two in-face coordinates, row-major.  A launch per level took 20 to 45 us of a context's
+// then the two in-face coordinates, row-major.  A launch per level took 10 to 45 us of a context's
 // set-up.
 constexpr int kMaxLevels = 16;
 struct GhostLevels {
