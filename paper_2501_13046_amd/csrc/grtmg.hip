@@ -1575,10 +1575,9 @@ mg_status autotune(mg_ctx *c, const double *u, const double *W, int reps, mg_tun
     }
     mg_status st = MG_OK;
     int k = 0;
-    // V-cycle tails: one whole V-cycle (with the coefficient restriction it needs)
-    // timed with the tail off and on
+    // V-cycle tails: one whole V-cycle timed with the default start (none for W) and with each other
     // (the exact W bottom first: while it is on, the W tail below it never runs)
-    // A tail is timed off and starting at every level from the highest that fits down to
+    // A tail is timed at its default and starting at every level from the highest that fits down to
     // the one above the coarsest; the entry reports the fastest start as its level.
     for (int family : {MG_TUNE_FOURIER_W, MG_TUNE_TAIL_PSI, MG_TUNE_TAIL_W}) {
         if (st != MG_OK) break;

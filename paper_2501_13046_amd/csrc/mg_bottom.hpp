@@ -5,10 +5,10 @@
 // arrays in LDS.  As separate launches each of these steps costs a launch and a round of
 // memory latency (3-4 us for a colour pass of 8^3 or 16^3 cells, 19 launches from 16^3 to 4^3
 // and back: 75 us and the gaps between them in a 128^3 FP32 cycle).  Here the whole V(1,3)
-// from 16^3 to 4^3 and back takes 40 us (FP64 43, Robin 74 and 93): the 4^3 solve 11 (Robin 20), the
-// 8^3 level around it 9 (Robin 20), the 16^3 level 20 to 23 (Robin 35 to 51).  With the scratch of
-// the coarsest solve behind generic pointers, 0.5 to 5 us more (10^3 over 5^3: 33 -> 26 us, Robin
-// 149 -> 80).
+// from 16^3 to 4^3 and back takes 40 us (FP64 43, Robin 71 and 92): the 4^3 solve 11 (Robin 20), the
+// 8^3 level around it 9 (Robin 18 and 20), the 16^3 level 21 to 23 (Robin 34 and 51).  With the scratch
+// of the coarsest solve behind generic pointers it took 1 to 5 us more (10^3 over 5^3: 33 -> 26 us,
+// Robin 149 -> 72).
 //
 // Corrections d live in padded arrays of (n + 4)^3 values whose ghost layers hold what the
 // boundary rule gives there, so that every tap is a fixed offset from its cell whatever the
